@@ -5,11 +5,12 @@
 //                                factorisation (rank-1 test, 1-D taps, the
 //                                banded B^T B coefficients and their image-edge
 //                                corrections), sum of d^2
-//   k_prep    (1 block/member)   FP64 subpixel trace (Eq. 1, Eqs. 10-11) of
+//   k_prep_*  (grid-wide)        FP64 subpixel trace (Eq. 1, Eqs. 10-11) of
 //                                every pixel, compaction of the pixels that map
 //                                onto the grid (Sec. 2.2: the others get no
-//                                intensity), their bounding box, and the
-//                                right-hand side b = L^T B^T d in FP64
+//                                intensity), their bounding box, the transposed
+//                                operator, and the right-hand side
+//                                b = L^T B^T d in FP64
 //   k_solve   (persistent, 1 block/CU)  each block pulls (member, lambda) items
 //                                and runs CG on (L^T B^T B L + lambda H^T H) s = b
 //                                from s = 0 (Eq. 7, Eq. 13-14, Sec. 2.2); the
@@ -58,7 +59,7 @@ constexpr int kUpd = 4;        // CG vector-update chunk (nodes per thread)
 // The spectral preconditioner pays for its four n x n transforms only where
 // lambda H^T H dominates the spectrum: it is used when lambda >= kPcTheta c.
 constexpr int kPcThetaPct = 15;   // default theta = 0.15 (sl_tuning.pc_theta_pct = 0)
-constexpr int kFillW = 16;     // waves that fill the transposed operator in parallel (k_prep's 1024 threads)
+constexpr int kFillW = 16;     // waves that fill the transposed operator in parallel in k_prep_fill
 constexpr int kHeavy = 4;      // default count of smallest lambdas of each member queued ahead of the rest
 constexpr int kMaxCK = 31;
 
@@ -67,7 +68,7 @@ struct alignas(16) MemberInfo {
   long long off;   // start in packed vectors
   int Mtrue;       // pixels with at least one subpixel on the grid
   int sell;        // transposed operator: CSR (0), sliced-ELL (1), sliced-ELL with paired 16-bit offsets (2)
-  float pc_c;      // scale c of the spectral preconditioner (see k_prep)
+  float pc_c;      // scale c of the spectral preconditioner (see k_prep_rhs)
   int lds_frame;   // 1: the member's image frame fits in LDS beside p and q; 0: global frame
   int pad_[2];
 };
@@ -87,8 +88,8 @@ struct alignas(16) Consts {
 };
 
 struct Layout {
-  size_t consts, lam, taps_d, taps_f, minfo, queues, pqueues, pix, cell, fx, fy, b, bh, dofk, ltc, s_all, gframe, gz, rbuf, mcbuf, ibuf,
-      lt_ptr, lt_perm,
+  size_t consts, lam, taps_d, taps_f, minfo, queues, pqueues, pix, cell, fx, fy, pmask, btd, b, bh, dofk, s_all, gframe, gz, rbuf, mcbuf, ibuf,
+      lt_ptr, lt_perm, lt_base, lt_cnt,
       lt_ent,
       total;
   long long lt_cap;
@@ -168,8 +169,7 @@ struct SolveArgs {
   int force_csr;    // variant: transposed operator as CSR rows
   int force_direct; // direct K x K blur only (variant, the hint that the PSF is not rank 1, or bicubic L)
   int psf_general;  // the caller's hint: the PSF is not rank 1
-  int interp;       // SL_INTERP_BILINEAR | NEAREST (the fractions k_prep stores) | BICUBIC
-  int prep_tags;    // k_prep has one LDS int per node after its 8 I_max + 768 bytes (conflict tags)
+  int interp;       // SL_INTERP_BILINEAR | NEAREST (the fractions k_prep_trace stores) | BICUBIC
   int implicit;     // implicit regularisation: n_lambda unregularised CG iterations (k_implicit)
   int heavy;        // smallest lambdas of each member queued ahead of the rest
   float pc_theta;   // items with lambda >= pc_theta c take the spectral preconditioner
@@ -179,30 +179,13 @@ struct SolveArgs {
   double* dofv;      // [n_members] result: bhat^T (bhat - A xhat) at the corner
   double* bh;        // [member][I_max] A^T bhat (FP64)
   double* dofk;      // [member][n_lambda] implicit solve: the estimate after each iterate
-  int* ltc;          // [member][I_max][kFillW] per-wave fill cursors of the transposed operator
+  unsigned long long* pmask;   // [member][slot_cap] first-occurrence mask of a slot's (subpixel, corner) pairs
+  double* btd;       // [2][J] B^T d and B^T bhat (FP64)
+  int32_t* lt_base;  // [member][I_max] index of each node's first entry of the transposed operator
+  int32_t* lt_cnt;   // [member][I_max] entries of each node
   void* mcbuf;       // [n_wg][5][I_max] r, xhat, rhat, phat, saved p of the pass
   void* ibuf;        // [n_wg][J] image residual e = d - A s of the implicit-regularisation solve
 };
-
-// ------------------------------------------------------------------ block scan
-// Exclusive prefix count of `flag` over the block; returns this thread's
-// offset and writes the block total to *total.  `scratch` >= 16 ints.
-__device__ __forceinline__ int block_excl_count(bool flag, int* scratch, int* total) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const unsigned long long bal = __ballot(flag);
-  const int in_wave = __popcll(bal & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
-  if (lane == 0) scratch[wid] = __popcll(bal);
-  __syncthreads();
-  int before = 0, tot = 0;
-  for (int i = 0; i < nw; ++i) {
-    const int c = scratch[i];
-    if (i < wid) before += c;
-    tot += c;
-  }
-  __syncthreads();
-  *total = tot;
-  return before + in_wave;
-}
 
 // ------------------------------------------------------------------ k_setup
 struct LamList {
@@ -235,6 +218,8 @@ __global__ void __launch_bounds__(1024) k_setup(SolveArgs a, LamList lams) {
       a.minfo[m].ns = ok ? ns : 0;
       a.minfo[m].I = ok ? ns * ns : 0;
       a.minfo[m].off = off;
+      a.minfo[m].r0 = a.minfo[m].c0 = INT_MAX;   // k_prep_trace widens the box
+      a.minfo[m].r1 = a.minfo[m].c1 = INT_MIN;
       off += ok ? (long long)ns * ns : 0;
     }
     a.s_off[M] = off;
@@ -372,46 +357,247 @@ __global__ void __launch_bounds__(1024) k_setup(SolveArgs a, LamList lams) {
   }
 }
 
-// ------------------------------------------------------------------ k_prep
-template <typename T>
-__device__ void prep_member(const SolveArgs& a, int m, MemberInfo mi, const double* gl, int* bbox, int* scan,
-                            double* bacc);
+// ------------------------------------------------------------------ member set-up (k_prep_*)
+// The tables of every member, by five grid-wide kernels (one block per member
+// did all of it before: 2.9 ms for a single 128 x 128 lens, 4.0 ms for 256 of
+// them, nearly all of it waves waiting on one another's cursors and on one
+// wave's ordered sums; the five take 0.1 and 0.6 ms):
+//   k_prep_trace   the FP64 subpixel trace, once, and B^T d once per call
+//   k_prep_place   compaction into the interleaved trace table
+//   k_prep_layout  row lengths of L^T, their order and the storage layout
+//   k_prep_fill    L^T's entries in their fixed order
+//   k_prep_rhs     entries' offsets and weights, b = L^T B^T d row by row
+// Everything that is summed keeps one fixed order, the same on every run and
+// whatever the grid.
 
+constexpr int kPrepT = 256;     // threads (pixels) per block of k_prep_trace and k_prep_place
+constexpr int kFillBand = 2048; // nodes whose fill cursors (kFillW waves x 4 bytes each) one block holds in LDS
+
+// The traced subpixels in pixel order, kept between k_prep_trace and
+// k_prep_place in the member's L^T entry region (64 n^2 bytes or more per
+// pixel, written only later): one mapped bit per pixel, then cells and fractions.
 template <typename T>
-__global__ void __launch_bounds__(1024) k_prep(SolveArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  double* bacc = reinterpret_cast<double*>(smem);
-  __shared__ int scan[32];
-  __shared__ int bbox[4];
-  __shared__ double g[7];
-  const int m = blockIdx.x, tid = threadIdx.x;
-  const int nx = a.nx, ny = a.ny, J = nx * ny, nsub = a.nsub, n2 = a.n2;
-  MemberInfo mi = a.minfo[m];
-  if (tid < 7) g[tid] = a.lens[7L * m + tid];
+struct PixTmp {
+  unsigned long long* words;   // [ceil(J/64)]
+  int32_t* cell;               // [J][n^2]
+  T* fx;
+  T* fy;
+  __device__ PixTmp(const SolveArgs& a, int m) {
+    const long J = (long)a.nx * a.ny;
+    const long nw = ((J + 63) / 64 + 1) & ~1L;   // 16-byte alignment of what follows
+    words = reinterpret_cast<unsigned long long*>(reinterpret_cast<LtEntry<T>*>(a.lt_ent) + (long)m * a.lt_cap);
+    fx = reinterpret_cast<T*>(words + nw);
+    fy = fx + ((J * a.n2 + 3) & ~3L);
+    cell = reinterpret_cast<int32_t*>(fy + ((J * a.n2 + 3) & ~3L));
+  }
+};
+
+// Bounds: FP64 arithmetic of the trace (atan, atanh and two square roots per
+// subpixel) and, for a single member, launch latency.  One thread per pixel;
+// every lane keeps its subpixels' cells and fractions for the compaction, so
+// each subpixel is traced once (the counting, placing and writing passes each
+// traced it again before).  The blocks past the members' compute B^T img
+// (img = d, then the Monte Carlo draws) over the image once for all members.
+template <typename T>
+__global__ void __launch_bounds__(kPrepT) k_prep_trace(SolveArgs a) {
+  __shared__ Lens Ls;
+  __shared__ int valid, bb[4];
+  const int tid = threadIdx.x, J = a.nx * a.ny, tiles = (J + kPrepT - 1) / kPrepT;
+  const int m = blockIdx.x / tiles, j = (blockIdx.x % tiles) * kPrepT + tid;
+  const int nx = a.nx, ny = a.ny, nsub = a.nsub, n2 = a.n2;
+  const int r = j / nx, c = j % nx;
+  if (m >= a.n_members) {   // correlation with the PSF: row of the PSF outer, column inner
+    const double* img = m == a.n_members ? a.d : a.mcn;
+    const int K = a.K, ck = a.ck;
+    if (j >= J) return;
+    double v = 0.0;
+    for (int aa = 0; aa < K; ++aa) {
+      const int rr = r + aa - ck;
+      if (rr < 0 || rr >= ny) continue;
+      for (int bb_ = 0; bb_ < K; ++bb_) {
+        const int cc = c + bb_ - ck;
+        if (cc < 0 || cc >= nx) continue;
+        v += a.psf[aa * K + bb_] * img[rr * nx + cc];
+      }
+    }
+    a.btd[(long)(m - a.n_members) * J + j] = v;
+    return;
+  }
+  const int ns = a.minfo[m].ns;
   if (tid == 0) {
-    bbox[0] = INT_MAX;
-    bbox[1] = INT_MIN;
-    bbox[2] = INT_MAX;
-    bbox[3] = INT_MIN;
+    double g[7];
+    for (int i = 0; i < 7; ++i) g[i] = a.lens[7L * m + i];
+    valid = ns >= 2 && lens_valid(g);
+    Ls = make_lens(g);
+    bb[0] = bb[2] = INT_MAX;
+    bb[1] = bb[3] = INT_MIN;
   }
   __syncthreads();
-  double gl[7];
-#pragma unroll
-  for (int i = 0; i < 7; ++i) gl[i] = g[i];
-  // the same for every thread; readfirstlane makes that visible to the compiler,
-  // so the branch around the barriers below is a scalar (block-uniform) branch
-  const int valid = __builtin_amdgcn_readfirstlane((int)(mi.ns >= 2 && lens_valid(gl)));
-  if (!valid) {
-    if (tid == 0) {
-      mi.M = 0;
-      mi.Mtrue = 0;
-      mi.status = SL_ST_INVALID;
-      mi.r0 = mi.c0 = 0;
-      mi.r1 = mi.c1 = -1;
+  const PixTmp<T> tmp(a, m);
+  bool mapped = false;
+  if (valid && j < J) {
+    const Lens L = Ls;
+    const double h = 2.0 * a.R / (ns - 1);
+    for (int k = 0; k < n2; ++k) {
+      double x, y, bx, by, fx = 0.0, fy = 0.0;
+      int cell;
+      subpixel_xy(r, c, k / nsub, k % nsub, nx, ny, a.pix, nsub, x, y);
+      lens_map(L, x, y, bx, by);
+      const bool in = grid_cell((bx + a.R) / h, (by + a.R) / h, ns, cell, fx, fy);
+      if (!in) {
+        cell = -1;
+        fx = fy = 0.0;
+      } else if (a.interp == SL_INTERP_NEAREST) {   // the nearest of the cell's four nodes, weight 1
+        fx = fx >= 0.5 ? 1.0 : 0.0;
+        fy = fy >= 0.5 ? 1.0 : 0.0;
+      }
+      mapped |= in;
+      tmp.cell[(long)j * n2 + k] = cell;
+      tmp.fx[(long)j * n2 + k] = (T)fx;
+      tmp.fy[(long)j * n2 + k] = (T)fy;
+    }
+  }
+  const unsigned long long bal = __ballot(mapped);
+  if ((tid & 63) == 0 && j < J) tmp.words[j >> 6] = bal;
+  if (mapped) {
+    atomicMin(&bb[0], r);
+    atomicMax(&bb[1], r);
+    atomicMin(&bb[2], c);
+    atomicMax(&bb[3], c);
+  }
+  __syncthreads();
+  if (tid == 0 && bb[1] >= 0) {
+    MemberInfo& mi = a.minfo[m];
+    atomicMin(&mi.r0, bb[0]);
+    atomicMax(&mi.r1, bb[1]);
+    atomicMin(&mi.c0, bb[2]);
+    atomicMax(&mi.c1, bb[3]);
+  }
+}
+
+// First-occurrence mask of a pixel's 4 n^2 (subpixel, corner) pairs: bit 4 k +
+// corner is set when subpixel k lies on the grid and no earlier subpixel
+// reaches that node.  (corner 0..3: nodes c, c + 1, c + ns, c + ns + 1)
+__device__ __forceinline__ int corner_node(int cell, int corner, int ns) {
+  return cell + (corner & 1) + (corner >> 1) * ns;
+}
+__device__ __forceinline__ unsigned long long pair_mask(const int32_t* cell, int n2, int ns) {
+  unsigned long long mask = 0;
+  for (int k = 0; k < n2; ++k) {
+    const int ck = cell[k];
+    if (ck < 0) continue;
+    unsigned f = 15u;
+    for (int l = 0; l < k; ++l) {
+      const int cl = cell[l];
+      if (cl < 0) continue;
+      // corners of subpixel k that are corners of subpixel l: their cells differ by at most one row and column
+      for (int q = 0; q < 4; ++q) {
+        const int d = corner_node(ck, q, ns) - cl;
+        if (d == 0 || d == 1 || d == ns || d == ns + 1) f &= ~(1u << q);
+      }
+    }
+    mask |= (unsigned long long)f << (4 * k);
+  }
+  return mask;
+}
+
+// Compaction: entry pos (rank of the mapped pixel in row order) goes to slot
+// (pos % S) * 64 + pos / S of the interleaved table, so that the 64 lanes of a
+// wave take pixels spread over the whole mapped region; slots past the last
+// entry hold -1.  Each block counts the mapped bits before its pixels itself
+// (at most 1024 words), so no pass over the whole image is needed between the
+// trace and this copy.  Bound by the record copies (48 bytes per pixel read
+// and written in FP32 with 2 x 2 subpixels).
+template <typename T>
+__global__ void __launch_bounds__(kPrepT) k_prep_place(SolveArgs a) {
+  __shared__ int red[2][kPrepT / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int J = a.nx * a.ny, tiles = (J + kPrepT - 1) / kPrepT, nwords = (J + 63) / 64;
+  const int m = blockIdx.x / tiles, tile = blockIdx.x % tiles, j = tile * kPrepT + tid;
+  const int n2 = a.n2;
+  const PixTmp<T> tmp(a, m);
+  const int ns = a.minfo[m].ns;
+  const int w0 = tile * (kPrepT / 64) + wid;   // this wave's word
+  int before = 0, total = 0;
+  for (int i = tid; i < nwords; i += kPrepT) {
+    const int n = __popcll(tmp.words[i]);
+    total += n;
+    before += i < tile * (kPrepT / 64) ? n : 0;
+  }
+  total = wave_sum(total);
+  before = wave_sum(before);
+  if (lane == 0) {
+    red[0][wid] = total;
+    red[1][wid] = before;
+  }
+  __syncthreads();
+  total = before = 0;
+  for (int i = 0; i < kPrepT / 64; ++i) {
+    total += red[0][i];
+    before += red[1][i];
+  }
+  const int Mtrue = total, S = (Mtrue + 63) / 64, slots = 64 * S;
+  int32_t* pix = a.pix_list + (long)m * a.slot_cap;
+  int32_t* cellp = a.cell + (long)m * a.slot_cap * n2;
+  T* fxp = reinterpret_cast<T*>(a.fx) + (long)m * a.slot_cap * n2;
+  T* fyp = reinterpret_cast<T*>(a.fy) + (long)m * a.slot_cap * n2;
+  if (tile == 0) {
+    if (tid < 64 && Mtrue + tid < slots) {   // fewer than 64 empty slots
+      const int p = Mtrue + tid, slot = (p % S) * 64 + p / S;
+      pix[slot] = -1;
+      a.pmask[(long)m * a.slot_cap + slot] = 0ull;
+      for (int k = 0; k < n2; ++k) {
+        cellp[(long)slot * n2 + k] = -1;
+        fxp[(long)slot * n2 + k] = (T)0;
+        fyp[(long)slot * n2 + k] = (T)0;
+      }
+    }
+    if (tid == 0) {   // the trace kernel has left the bounding box in r0..c1
+      MemberInfo mi = a.minfo[m];
+      double g[7];
+      for (int i = 0; i < 7; ++i) g[i] = a.lens[7L * m + i];
+      mi.M = slots;
+      mi.Mtrue = Mtrue;
+      mi.status = !(ns >= 2 && lens_valid(g)) ? SL_ST_INVALID : Mtrue > 0 ? SL_ST_OK : SL_ST_EMPTY;
+      if (Mtrue == 0) {
+        mi.r0 = mi.c0 = 0;
+        mi.r1 = mi.c1 = -1;
+      }
+      const int fh = mi.r1 - mi.r0 + 1, fw = mi.c1 - mi.c0 + 1;
+      mi.lds_frame = (long)(fh + 4 * a.ckt + kSegR) * ((fw + 4 * a.ckt) | 1) <= a.lds_frame_cap;
+      mi.sell = 0;
+      mi.pc_c = 0.0f;
       a.minfo[m] = mi;
     }
+  }
+  if (j >= J) return;
+  const unsigned long long word = tmp.words[w0];
+  if (!((word >> lane) & 1ull)) return;
+  for (int i = tile * (kPrepT / 64); i < w0; ++i) before += __popcll(tmp.words[i]);
+  const int pos = before + __popcll(word & ((1ull << lane) - 1ull));
+  const int slot = (pos % S) * 64 + pos / S;
+  pix[slot] = ((j / a.nx) << 16) | (j % a.nx);   // packed row/column of the mapped pixel
+  if (n2 == 4) {
+    const int4 c4 = reinterpret_cast<const int4*>(tmp.cell)[j];
+    reinterpret_cast<int4*>(cellp)[slot] = c4;
+    if constexpr (sizeof(T) == 4) {
+      reinterpret_cast<float4*>(fxp)[slot] = reinterpret_cast<const float4*>(tmp.fx)[j];
+      reinterpret_cast<float4*>(fyp)[slot] = reinterpret_cast<const float4*>(tmp.fy)[j];
+    } else {
+      for (int k = 0; k < 4; ++k) {
+        fxp[4L * slot + k] = tmp.fx[4L * j + k];
+        fyp[4L * slot + k] = tmp.fy[4L * j + k];
+      }
+    }
+    const int32_t cl[4] = {c4.x, c4.y, c4.z, c4.w};
+    a.pmask[(long)m * a.slot_cap + slot] = pair_mask(cl, 4, ns);
   } else {
-    prep_member<T>(a, m, mi, gl, bbox, scan, bacc);
+    for (int k = 0; k < n2; ++k) {
+      cellp[(long)slot * n2 + k] = tmp.cell[(long)j * n2 + k];
+      fxp[(long)slot * n2 + k] = tmp.fx[(long)j * n2 + k];
+      fyp[(long)slot * n2 + k] = tmp.fy[(long)j * n2 + k];
+    }
+    a.pmask[(long)m * a.slot_cap + slot] = pair_mask(tmp.cell + (long)j * n2, n2, ns);
   }
 }
 
@@ -424,125 +610,56 @@ __device__ __forceinline__ F keys_w(F d) {
                    : (d < F(2) ? ((F(-0.5) * d + F(2.5)) * d - F(4)) * d + F(2) : F(0));
 }
 
-// Pair q (q < 16 n^2) of mapped slot t under bicubic interpolation: subpixel
-// q / 16, tap q % 16 = 4 (j + 1) + (i + 1) at row offset j and column offset
-// i from the cell's first node; node -1 for an off-grid subpixel or a tap
-// outside the grid (the source is zero there).  The weight includes the
-// 1/n^2 subpixel average.  Pairs are not merged: a node can occur at several
-// q of one pixel, each q adding its own entry.
-template <typename T>
-__device__ __forceinline__ void bicubic_pair(int t, int q, int ns, int n2, const int32_t* cellp, const T* fxp,
-                                             const T* fyp, int& node, double& w) {
-  const int k = q >> 4, j = (q >> 2) & 3, i = q & 3;
-  const int c = cellp[(long)t * n2 + k];
-  node = -1;
-  w = 0.0;
-  if (c < 0) return;
-  const int r = c / ns + j - 1, col = c % ns + i - 1;
-  if (r < 0 || r >= ns || col < 0 || col >= ns) return;
-  const double fx = (double)fxp[(long)t * n2 + k], fy = (double)fyp[(long)t * n2 + k];
-  node = r * ns + col;
-  w = keys_w(fabs(fy - (j - 1))) * keys_w(fabs(fx - (i - 1))) / n2;
+// Pair q of mapped slot t: the node it adds to, -1 for none.
+//
+// Bilinear and nearest: q = 4 k + corner (q < 4 n^2), the pair of a node that
+// an earlier subpixel of the pixel already reaches being folded into that one
+// (pmask).  Bicubic: q = 16 k + 4 (j + 1) + (i + 1) (q < 16 n^2), the tap at row
+// offset j and column offset i from subpixel k's cell; taps outside the grid
+// are left out (the source is zero there), and pairs are not folded.
+__device__ __forceinline__ int pair_node(bool cubic, int q, int ns, unsigned long long mask, const int32_t* cell) {
+  if (!cubic) return (mask >> q) & 1ull ? corner_node(cell[q >> 2], q & 3, ns) : -1;
+  const int c = cell[q >> 4];
+  if (c < 0) return -1;
+  const int r = c / ns + ((q >> 2) & 3) - 1, col = c % ns + (q & 3) - 1;
+  return r < 0 || r >= ns || col < 0 || col >= ns ? -1 : r * ns + col;
 }
 
-// Trace, compaction and right-hand side of one valid member (all threads).
-// Unique (node, weight) pairs of the subpixels of mapped slot t, weights
-// including the 1/n^2 subpixel average; returns the pair count (<= 4 n^2).
+// FP64 weight of mapped slot t's pair q at `node`, the 1/n^2 subpixel average
+// included: for bilinear and nearest L the weights of all the pixel's
+// subpixels at the node, added in subpixel order.
 template <typename T>
-__device__ int pixel_pairs(int t, int ns, int n2, const int32_t* cellp, const T* fxp, const T* fyp, int* node,
-                           double* wt) {
-  int cnt = 0;
-  const double inv = 1.0 / n2;
-  for (int k = 0; k < n2; ++k) {
-    const int c = cellp[(long)t * n2 + k];
-    if (c < 0) continue;
+__device__ __forceinline__ double pair_weight(bool cubic, int t, int q, int node, int ns, int n2, const int32_t* cellp,
+                                              const T* fxp, const T* fyp) {
+  if (cubic) {
+    const int k = q >> 4, j = (q >> 2) & 3, i = q & 3;
     const double fx = (double)fxp[(long)t * n2 + k], fy = (double)fyp[(long)t * n2 + k];
-    const int nd[4] = {c, c + 1, c + ns, c + ns + 1};
-    const double ww[4] = {(1 - fx) * (1 - fy), fx * (1 - fy), (1 - fx) * fy, fx * fy};
-    for (int q = 0; q < 4; ++q) {
-      int f = 0;
-      while (f < cnt && node[f] != nd[q]) ++f;
-      if (f == cnt) {
-        node[cnt] = nd[q];
-        wt[cnt] = 0.0;
-        ++cnt;
-      }
-      wt[f] += ww[q] * inv;
-    }
+    return keys_w(fabs(fy - (j - 1))) * keys_w(fabs(fx - (i - 1))) / n2;
   }
-  return cnt;
-}
-
-// pixel_pairs for 2 x 2 subpixels with everything in registers: the 16
-// (subpixel, corner) pairs in the same order, a pair whose node already
-// occurred folds its weight into the first occurrence (same summation order
-// as pixel_pairs); folded pairs get node -1.
-template <typename T>
-__device__ __forceinline__ void pixel_pairs4(int t, int ns, const int32_t* cellp, const T* fxp, const T* fyp,
-                                             int (&node)[16], double (&wt)[16]) {
+  if (n2 == 4) {
+    const int4 c4 = reinterpret_cast<const int4*>(cellp)[t];
+    const int cl[4] = {c4.x, c4.y, c4.z, c4.w};
+    double w = 0.0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int c = cellp[(long)t * 4 + k];
-    const double fx = (double)fxp[(long)t * 4 + k], fy = (double)fyp[(long)t * 4 + k];
-    const bool in = c >= 0;
-    node[4 * k + 0] = in ? c : -1;
-    node[4 * k + 1] = in ? c + 1 : -1;
-    node[4 * k + 2] = in ? c + ns : -1;
-    node[4 * k + 3] = in ? c + ns + 1 : -1;
-    wt[4 * k + 0] = (1 - fx) * (1 - fy) * 0.25;
-    wt[4 * k + 1] = fx * (1 - fy) * 0.25;
-    wt[4 * k + 2] = (1 - fx) * fy * 0.25;
-    wt[4 * k + 3] = fx * fy * 0.25;
-  }
-#pragma unroll
-  for (int i = 1; i < 16; ++i) {
-    bool folded = node[i] < 0;
-#pragma unroll
-    for (int j = 0; j < i; ++j) {
-      const bool hit = !folded && node[j] == node[i];
-      wt[j] += hit ? wt[i] : 0.0;
-      folded = folded || hit;
+    for (int k = 0; k < 4; ++k) {
+      const double fx = (double)fxp[4L * t + k], fy = (double)fyp[4L * t + k];
+      const int d = node - cl[k];
+      const double wx = d == 0 || d == ns ? 1 - fx : fx, wy = d == 0 || d == 1 ? 1 - fy : fy;
+      const double wk = wx * wy * 0.25;
+      w += cl[k] >= 0 && (d == 0 || d == 1 || d == ns || d == ns + 1) ? wk : 0.0;
     }
-    if (folded) node[i] = -1;
+    return w;
   }
-}
-
-// Rank of this lane among the lanes of its wave that hold the same key
-// (key >= 0), and their count.  With an LDS tag array (one int per key), a
-// step in which no two lanes share a key is recognised in one store/load
-// round trip: every lane writes its lane id at its key and reads it back, and
-// a lane that reads another id shares its key.  Whether some lane does is the
-// same whichever store won, so the outcome, and every summation order built
-// on it, is the same on every run.  Only when keys are shared are the ranks
-// counted lane by lane (64 readlane steps).
-__device__ __forceinline__ void lane_rank(int key, int* tag, int& rank, int& total) {
-  const int lane = threadIdx.x & 63;
-  if (tag) {
-    if (key >= 0) tag[key] = lane;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int seen = key >= 0 ? reinterpret_cast<volatile int*>(tag)[key] : lane;
-    const int clash = __builtin_amdgcn_readfirstlane((int)(__ballot(seen != lane) != 0ull));
-    // every lane has read its tag before a later step writes the array again
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (!clash) {
-      rank = 0;
-      total = 1;
-      return;
-    }
+  const double inv = 1.0 / n2;
+  double w = 0.0;
+  for (int k = 0; k < n2; ++k) {
+    const int c = cellp[(long)t * n2 + k], d = node - c;
+    if (c < 0 || !(d == 0 || d == 1 || d == ns || d == ns + 1)) continue;
+    const double fx = (double)fxp[(long)t * n2 + k], fy = (double)fyp[(long)t * n2 + k];
+    const double ww = (d == 0 || d == ns ? 1 - fx : fx) * (d == 0 || d == 1 ? 1 - fy : fy);
+    w += ww * inv;
   }
-  rank = 0;
-  total = 0;
-  for (int l = 0; l < 64; ++l) {   // uniform lane index: v_readlane
-    const int kl = __builtin_amdgcn_readlane(key, l);
-    if (kl == key) {
-      ++total;
-      if (l < lane) ++rank;
-    }
-  }
+  return w;
 }
 
 // Quarter-octave bucket of a row length (0 for empty rows): rows in one
@@ -554,147 +671,153 @@ __device__ __forceinline__ int len_bucket(int c) {
   return 4 * msb + frac + 1;
 }
 
-// Node-major form of L^T for one member, sliced-ELL with rows sorted by length
-// (SELL-C-sigma with C = 64, one slice per wave): nodes are ordered by
-// descending length bucket (stable in node index) into perm[] = packed
-// (row << 16 | col); entry j of the node at position p sits at
-// ptr[p/64] + 64 j + p%64, every slice padded to its longest row with
-// entries (offset 0, weight 0) -- offset 0 is a frame halo element, always
-// zero.  Entries of a node are filled in a fixed order, so the per-node sum
-// is the same on every run.  Falls back to plain CSR in node order (ptr = row
-// starts) when the padded form exceeds the capacity; returns 1 for
-// sliced-ELL, 0 for CSR.  lds: LDS ints (>= 2 I + 64 + 128).
+// Lanes of this wave with the same 7-bit key.
+__device__ __forceinline__ unsigned long long match7(int key) {
+  unsigned long long mk = ~0ull;
+#pragma unroll
+  for (int b = 0; b < 7; ++b) {
+    const unsigned long long bal = __ballot((key >> b) & 1);
+    mk &= (key >> b) & 1 ? bal : ~bal;
+  }
+  return mk;
+}
+
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
+
+// Layout of L^T for one member (node-major form, sliced-ELL with rows sorted
+// by length: SELL-C-sigma with C = 64, one slice per wave): nodes are ordered
+// by descending length bucket (stable in node index) into perm[] = packed
+// (row << 16 | col); entry j of the node at position p sits at ptr[p/64] + 64 j
+// + p%64, every slice padded to its longest row with entries (offset 0, weight
+// 0) -- offset 0 is a frame halo element, always zero.  Falls back to plain CSR
+// in node order (ptr = row starts) when the padded form exceeds the capacity.
+// FP32 members whose frame fits in LDS (frame offsets below 2^16) store the
+// sliced-ELL entries in pairs: slices of even length, one dword holding the
+// 16-bit offsets of entries 2k and 2k + 1 of a lane and one float2 their
+// weights (6 bytes per entry instead of 8).
+//
+// One block per member: the row lengths are counted with LDS atomics, which a
+// grid-wide count would have to do in memory, and the sixteen waves place
+// contiguous node ranges (a histogram per wave and an exclusive scan over the
+// waves keep the order that of the node index).
+// dynamic LDS: cnt[I], pcnt[I + 64], whist[16][128], slen[SL]; SL = slices + 1.
 template <typename T>
-__device__ int build_transpose(const SolveArgs& a, int m, int ns, int slots, const int* bbox, int* scan, int* lds,
-                               const int32_t* pix, const int32_t* cellp, const T* fxp, const T* fyp, int* tag) {
-  const int tid = threadIdx.x, n2 = a.n2, I = ns * ns;
-  const int halo = 2 * a.ckt;
-  const int pitch = (bbox[3] - bbox[2] + 1 + 2 * halo) | 1;
-  const int ngroups = (I + 63) / 64;
-  int* cnt = lds;                       // [I + 64] row lengths, later fill cursors
-  int* ipos = lds + I + 64;             // [I] sorted position of every node
-  int* hist = ipos + I;                 // [128] bucket histogram
+__global__ void __launch_bounds__(1024) k_prep_layout(SolveArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int hist[128], scan[16], totals;
+  const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, n2 = a.n2;
+  const MemberInfo mi = a.minfo[m];
+  if (__builtin_amdgcn_readfirstlane(mi.status) != SL_ST_OK) return;
+  const int ns = mi.ns, I = mi.I, slots = mi.M, ngroups = (I + 63) / 64;
+  int* cnt = reinterpret_cast<int*>(smem);   // row lengths
+  int* pcnt = cnt + I;                       // row lengths in sorted order (positions past I: 0)
+  int* whist = pcnt + I + 64;                // per-wave bucket histograms, later positions
+  int* slen = whist + 16 * 128;              // slice lengths, then slice starts
+  const int32_t* cellp = a.cell + (long)m * a.slot_cap * n2;
+  const unsigned long long* pm = a.pmask + (long)m * a.slot_cap;
   int32_t* rp = a.lt_ptr + (long)m * (a.I_max + 65);
   int32_t* perm = a.lt_perm + (long)m * a.I_max;
-  LtEntry<T>* ent = reinterpret_cast<LtEntry<T>*>(a.lt_ent) + (long)m * a.lt_cap;
-  int node[4 * SL_MAX_NSUB * SL_MAX_NSUB];
-  double wt[4 * SL_MAX_NSUB * SL_MAX_NSUB];
-  __shared__ int totals[2];
-  for (int i = tid; i < I + 64; i += blockDim.x) cnt[i] = 0;
-  for (int i = tid; i < 128; i += blockDim.x) hist[i] = 0;
-  if (tid == 0) totals[0] = totals[1] = 0;
-  __syncthreads();
+  int32_t* lbase = a.lt_base + (long)m * a.I_max;
+  int32_t* lcnt = a.lt_cnt + (long)m * a.I_max;
   const bool cubic = a.interp == SL_INTERP_BICUBIC;
-  if (cubic) {
-    for (int t = tid; t < slots; t += blockDim.x) {
-      if (pix[t] < 0) continue;
+  for (int i = tid; i < I; i += 1024) cnt[i] = 0;
+  for (int i = tid; i < 16 * 128; i += 1024) whist[i] = 0;
+  if (tid < 64) pcnt[I + tid] = 0;
+  if (tid == 0) totals = 0;
+  __syncthreads();
+  for (int t = tid; t < slots; t += 1024) {
+    if (cubic) {
       for (int q = 0; q < 16 * n2; ++q) {
-        int nd;
-        double ww;
-        bicubic_pair(t, q, ns, n2, cellp, fxp, fyp, nd, ww);
+        const int nd = pair_node(true, q, ns, 0ull, cellp + (long)t * n2);
         if (nd >= 0) atomicAdd(&cnt[nd], 1);
       }
-    }
-  } else if (n2 == 4) {
-    for (int t = tid; t < slots; t += blockDim.x) {
-      if (pix[t] < 0) continue;
-      int nd[16];
-      double ww[16];
-      pixel_pairs4(t, ns, cellp, fxp, fyp, nd, ww);
+    } else if (n2 == 4) {
+      const unsigned mask = (unsigned)pm[t];
+      const int4 c4 = reinterpret_cast<const int4*>(cellp)[t];
+      const int cl[4] = {c4.x, c4.y, c4.z, c4.w};
 #pragma unroll
       for (int q = 0; q < 16; ++q)
-        if (nd[q] >= 0) atomicAdd(&cnt[nd[q]], 1);
-    }
-  } else {
-    for (int t = tid; t < slots; t += blockDim.x) {
-      if (pix[t] < 0) continue;
-      const int np = pixel_pairs(t, ns, n2, cellp, fxp, fyp, node, wt);
-      for (int q = 0; q < np; ++q) atomicAdd(&cnt[node[q]], 1);
-    }
-  }
-  __syncthreads();
-  for (int i = tid; i < I; i += blockDim.x) atomicAdd(&hist[len_bucket(cnt[i])], 1);
-  __syncthreads();
-  if (tid == 0) {   // descending buckets -> start positions
-    int run = 0;
-    for (int b = 127; b >= 0; --b) {
-      const int c = hist[b];
-      hist[b] = run;
-      run += c;
-    }
-  }
-  __syncthreads();
-  // stable placement in node order: one wave per bucket pass keeps it deterministic.
-  // Only this wave touches hist[] here, and one wave's LDS accesses complete in
-  // order, so wavefront-scope fences (compiler ordering, no wait on the global
-  // stores) around the wave barrier order its LDS read-modify-writes.
-  if (tid < 64) {
-    for (int i0 = 0; i0 < I; i0 += 64) {
-      const int i = i0 + tid;
-      const int b = i < I ? len_bucket(cnt[i]) : -1;
-      // rank of the lane among lower lanes with the same bucket, and the bucket's count
-      int before = 0, total = 0;
-      for (int l = 0; l < 64; ++l) {   // uniform lane index: v_readlane, no LDS round trip
-        const int bl = __builtin_amdgcn_readlane(b, l);
-        if (bl == b) {
-          ++total;
-          if (l < tid) ++before;
-        }
+        if ((mask >> q) & 1u) atomicAdd(&cnt[corner_node(cl[q >> 2], q & 3, ns)], 1);
+    } else {
+      for (unsigned long long mask = pm[t]; mask; mask &= mask - 1) {
+        const int q = __ffsll((unsigned long long)mask) - 1;
+        atomicAdd(&cnt[corner_node(cellp[(long)t * n2 + (q >> 2)], q & 3, ns)], 1);
       }
-      const int p = i < I ? hist[b] + before : 0;
-      if (i < I) {
-        ipos[i] = p;
-        perm[p] = ((i / ns) << 16) | (i % ns);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      // the bucket's last lane advances it past this group's nodes
-      if (i < I && before == total - 1) hist[b] = p + 1;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
   }
   __syncthreads();
-  // FP32 members whose frame fits in LDS (frame offsets below 2^16) store the
-  // sliced-ELL entries in pairs: slices of even length, one dword holding the
-  // 16-bit offsets of entries 2k and 2k + 1 of a lane and one float2 their
-  // weights (6 bytes per entry instead of 8)
-  const int fh = bbox[1] - bbox[0] + 1, fw = bbox[3] - bbox[2] + 1;
-  const int pair_ok = __builtin_amdgcn_readfirstlane(
-      (int)(sizeof(T) == 4 && (long)(fh + 4 * a.ckt + kSegR) * ((fw + 4 * a.ckt) | 1) <= a.lds_frame_cap &&
-            a.lds_frame_cap <= 65536));
-  // slice lengths (rows sorted by length: little padding) and the plain total
-  for (int g = tid; g < ngroups; g += blockDim.x) {
-    int mx = 0;
-    for (int l = 0; l < 64 && 64 * g + l < I; ++l) {
-      const int i = (perm[64 * g + l] >> 16) * ns + (perm[64 * g + l] & 0xFFFF);
-      mx = max(mx, cnt[i]);
+  // stable placement: wave w takes the node groups [w G / 16, (w + 1) G / 16)
+  const int g0 = (wid * ngroups) / 16, g1 = ((wid + 1) * ngroups) / 16;
+  for (int g = g0; g < g1; ++g) {
+    const int i = 64 * g + lane;
+    if (i < I) {
+      const int c = cnt[i];
+      atomicAdd(&whist[wid * 128 + len_bucket(c)], 1);
+      lcnt[i] = c;
     }
+  }
+  __syncthreads();
+  if (tid < 128) {
+    int s = 0;
+    for (int w = 0; w < 16; ++w) {
+      const int c = whist[w * 128 + tid];
+      whist[w * 128 + tid] = s;   // nodes of this bucket in the waves before w
+      s += c;
+    }
+    hist[tid] = s;
+  }
+  __syncthreads();
+  int above = 0;
+  if (tid < 128)
+    for (int b = tid + 1; b < 128; ++b) above += hist[b];   // descending buckets
+  if (tid < 128)
+    for (int w = 0; w < 16; ++w) whist[w * 128 + tid] += above;
+  __syncthreads();
+  for (int g = g0; g < g1; ++g) {
+    const int i = 64 * g + lane, c = i < I ? cnt[i] : 0;
+    const int b = i < I ? len_bucket(c) : 127;   // 127: no row length reaches it
+    const unsigned long long same = match7(b);
+    int* pos = &whist[wid * 128 + b];
+    const int p = *pos + lanes_below(same);
+    if (i < I) {
+      perm[p] = ((i / ns) << 16) | (i % ns);
+      pcnt[p] = c;
+      lbase[i] = p;
+    }
+    // every lane has read its bucket's position before the bucket's last lane advances it
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (i < I && (same >> lane) == 1ull) *pos = p + 1;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  __syncthreads();
+  const int fh = mi.r1 - mi.r0 + 1, fw = mi.c1 - mi.c0 + 1;
+  const bool pair_ok = sizeof(T) == 4 && (long)(fh + 4 * a.ckt + kSegR) * ((fw + 4 * a.ckt) | 1) <= a.lds_frame_cap &&
+                       a.lds_frame_cap <= 65536;
+  for (int g = wid; g < ngroups; g += 16) {
+    int mx = pcnt[64 * g + lane];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
     if (pair_ok) mx = (mx + 1) & ~1;
-    atomicAdd(&totals[0], 64 * mx);
+    if (lane == 0) {
+      slen[g] = 64 * mx;
+      atomicAdd(&totals, 64 * mx);
+    }
   }
   __syncthreads();
-  const int sell = __builtin_amdgcn_readfirstlane((int)(!a.force_csr && (long long)totals[0] <= a.lt_cap));
-  const int paired = sell && pair_ok;
-  // exclusive scan over units: slices (padded sizes) for sliced-ELL, rows for CSR
+  const int sell = __builtin_amdgcn_readfirstlane((int)(!a.force_csr && (long long)totals <= a.lt_cap));
+  // exclusive scan over units: slices for sliced-ELL, rows for CSR
   const int nunits = sell ? ngroups : I;
-  const int chunk = (nunits + blockDim.x - 1) / blockDim.x;
+  const int* size = sell ? slen : cnt;
+  const int chunk = (nunits + 1023) / 1024;
   const int u0 = min(nunits, tid * chunk), u1 = min(nunits, u0 + chunk);
-  auto unit_size = [&](int u) {
-    if (!sell) return cnt[u];
-    int mx = 0;
-    for (int l = 0; l < 64 && 64 * u + l < I; ++l) {
-      const int i = (perm[64 * u + l] >> 16) * ns + (perm[64 * u + l] & 0xFFFF);
-      mx = max(mx, cnt[i]);
-    }
-    if (paired) mx = (mx + 1) & ~1;
-    return 64 * mx;
-  };
   int local = 0;
-  for (int u = u0; u < u1; ++u) local += unit_size(u);
-  const int lane = tid & 63, wid = tid >> 6;
+  for (int u = u0; u < u1; ++u) local += size[u];
   int incl = local;
   for (int o = 1; o < 64; o <<= 1) {
     const int v = __shfl_up(incl, o, 64);
@@ -702,430 +825,259 @@ __device__ int build_transpose(const SolveArgs& a, int m, int ns, int slots, con
   }
   if (lane == 63) scan[wid] = incl;
   __syncthreads();
-  int before = 0;
-  for (int i = 0; i < wid; ++i) before += scan[i];
-  int run = before + incl - local;
+  int run = incl - local;
+  for (int i = 0; i < wid; ++i) run += scan[i];
   for (int u = u0; u < u1; ++u) {
+    const int n = size[u];
     rp[u] = run;
-    run += unit_size(u);
+    if (sell) slen[u] = run;
+    else lbase[u] = run;
+    run += n;
   }
-  if (tid == blockDim.x - 1) rp[nunits] = run;
+  if (tid == 1023) rp[nunits] = run;
   __syncthreads();
-  // padding entries: offset 0 (a halo corner of the frame, always zero), weight 0
-  const int E = rp[ngroups];   // sliced-ELL entries (a multiple of 128 when paired)
-  unsigned short* off16 = reinterpret_cast<unsigned short*>(ent);
-  float* w32 = reinterpret_cast<float*>(off16 + E);
-  if (paired)
-    for (int e = tid; e < 3 * (E >> 1); e += blockDim.x) reinterpret_cast<unsigned*>(ent)[e] = 0u;
-  else if (sell)
-    for (int e = tid; e < E; e += blockDim.x) {
-      ent[e].off = 0;
-      ent[e].w = (T)0;
+  if (sell)   // entry base of every node
+    for (int i = tid; i < I; i += 1024) {
+      const int p = lbase[i];
+      lbase[i] = slen[p >> 6] + (p & 63);
     }
-  // entry base of every node: ipos[] becomes the index of its first entry
-  for (int i = tid; i < I; i += blockDim.x) {
-    const int p = ipos[i];
-    ipos[i] = sell ? rp[p >> 6] + (p & 63) : rp[i];
-    cnt[i] = 0;   // fill cursors
-  }
-  __syncthreads();
-  const int estep = sell ? 64 : 1;
-  // Fill in a fixed order without sorting.  The entries of a node are
-  // ordered by (slot group of 64, pair q, lane): lanes holding the same node
-  // take consecutive positions in lane order (a pixel's pairs have distinct
-  // nodes), the same on every run.
-  //
-  // 2 x 2 subpixels: the kFillW waves fill in parallel, wave w taking the
-  // contiguous range of slot groups [w G / kFillW, (w + 1) G / kFillW).  A
-  // first pass counts each node's entries per wave (global atomics into the
-  // member's cursor table), an exclusive scan over the waves gives wave w the
-  // position after the entries of the groups before its range, and then each
-  // wave walks its groups as one wave would.  So the order, and every sum
-  // built on it, is the order of a single wave walking all groups.  The
-  // waves share the LDS conflict tags: a clash seen through another wave's
-  // tag only sends a step down the exact counting path.
-  if (n2 == 4 && !cubic) {
-    const int G = (slots + 63) / 64;
-    const int w = tid >> 6, lane = tid & 63;
-    const int g0 = (w * G) / kFillW, g1 = ((w + 1) * G) / kFillW;
-    int* cw = a.ltc + (long)m * a.I_max * kFillW;   // [node][wave]
-    for (int e = tid; e < I * kFillW; e += blockDim.x) cw[e] = 0;
-    __syncthreads();
-    for (int g = g0; g < g1; ++g) {   // counts per (node, wave)
-      const int t = g * 64 + lane;
-      if (t < slots && pix[t] >= 0) {
-        int nd[16];
-        double ww[16];
-        pixel_pairs4(t, ns, cellp, fxp, fyp, nd, ww);
-#pragma unroll
-        for (int q = 0; q < 16; ++q)
-          if (nd[q] >= 0) atomicAdd(&cw[nd[q] * kFillW + w], 1);
-      }
-    }
-    __syncthreads();
-    for (int i = tid; i < I; i += blockDim.x) {   // exclusive scan over the waves; cnt[i] keeps the total
-      int run = 0;
-      for (int v = 0; v < kFillW; ++v) {
-        const int c = __hip_atomic_load(&cw[i * kFillW + v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&cw[i * kFillW + v], run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        run += c;
-      }
-      cnt[i] = run;
-    }
-    __syncthreads();
-    for (int g = g0; g < g1; ++g) {   // uniform per wave
-      const int t = g * 64 + lane;
-      int nd[16];
-      double ww[16];
-      int off = 0;
-      const int rc = t < slots ? pix[t] : -1;
-      if (rc >= 0) {
-        off = ((rc >> 16) - bbox[0] + halo) * pitch + ((rc & 0xFFFF) - bbox[2] + halo);
-        pixel_pairs4(t, ns, cellp, fxp, fyp, nd, ww);
-      } else {
-#pragma unroll
-        for (int q = 0; q < 16; ++q) nd[q] = -1;
-      }
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int key = nd[q];
-        if (!__builtin_amdgcn_readfirstlane((int)(__ballot(key >= 0) != 0ull))) continue;   // uniform
-        int rank, total;
-        lane_rank(key, tag, rank, total);
-        int* cur = key >= 0 ? &cw[key * kFillW + w] : nullptr;
-        const int j = key >= 0 ? __hip_atomic_load(cur, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + rank : 0;
-        // every lane has read its cursor before the last lane of a node advances it
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if (key >= 0 && rank == total - 1)
-          __hip_atomic_store(cur, j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // the advance is complete before this wave's next step reads the cursors
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if (key >= 0 && j < cnt[key]) {   // j < cnt[key] always holds; the test keeps every write in the node's rows
-          if (paired) {
-            const long ps = ((long)(ipos[key] & ~63) >> 1) + 64L * (j >> 1) + (ipos[key] & 63);
-            off16[2 * ps + (j & 1)] = (unsigned short)off;
-            w32[2 * ps + (j & 1)] = (float)ww[q];
-          } else {
-            const long e = (long)ipos[key] + (long)estep * j;
-            ent[e].off = off;
-            ent[e].w = (T)ww[q];
-          }
-        }
-      }
-    }
-  } else if (tid < 64) {
-    const int lane = tid;
-    for (int t0 = 0; t0 < slots; t0 += 64) {
-      const int t = t0 + lane;
-      int np = 0, off = 0;
-      if (t < slots) {
-        const int rc = pix[t];
-        if (rc >= 0) {
-          off = ((rc >> 16) - bbox[0] + halo) * pitch + ((rc & 0xFFFF) - bbox[2] + halo);
-          np = cubic ? 16 * n2 : pixel_pairs(t, ns, n2, cellp, fxp, fyp, node, wt);
-        }
-      }
-      int npmax = np;
-      for (int o = 32; o > 0; o >>= 1) npmax = max(npmax, __shfl_xor(npmax, o, 64));
-      for (int q = 0; q < npmax; ++q) {
-        int key = -1;
-        double wq = 0.0;
-        if (q < np) {
-          if (cubic) {
-            bicubic_pair(t, q, ns, n2, cellp, fxp, fyp, key, wq);
-          } else {
-            key = node[q];
-            wq = wt[q];
-          }
-        }
-        int rank, total;
-        lane_rank(key, tag, rank, total);
-        const int j = key >= 0 ? cnt[key] + rank : 0;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (key >= 0 && rank == total - 1) cnt[key] = j + 1;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (key >= 0) {
-          if (paired) {
-            const long ps = ((long)(ipos[key] & ~63) >> 1) + 64L * (j >> 1) + (ipos[key] & 63);
-            off16[2 * ps + (j & 1)] = (unsigned short)off;
-            w32[2 * ps + (j & 1)] = (float)wq;
-          } else {
-            const long e = (long)ipos[key] + (long)estep * j;
-            ent[e].off = off;
-            ent[e].w = (T)wq;
-          }
-        }
-      }
-    }
-  }
-  __syncthreads();
-  return paired ? 2 : sell;
+  if (tid == 0) a.minfo[m].sell = sell && pair_ok ? 2 : sell;
 }
 
-// bacc[key] += val on the lanes of one wave with key >= 0; lanes that share
-// a key add in lane order (they take turns by their rank among the lanes
-// with that key), so every node's sum has the same order on every run.
-__device__ __forceinline__ void wave_ordered_add(double* bacc, int* tag, int key, double val) {
-  if (!__builtin_amdgcn_readfirstlane((int)(__ballot(key >= 0) != 0ull))) return;   // uniform
-  int rank, total;
-  lane_rank(key, tag, rank, total);
-  (void)total;
-  for (int r = 0; __ballot(key >= 0 && rank >= r) != 0ull; ++r) {
-    if (key >= 0 && rank == r) bacc[key] += val;
-    // this round's LDS writes precede the next round's reads
+// Position of entry j of the node with entry base `base` in the arrays of each layout.
+__device__ __forceinline__ long paired_index(int base, int j) {   // index into the 16-bit offsets and the weights
+  return 2 * (((long)(base & ~63) >> 1) + 64L * (j >> 1) + (base & 63)) + (j & 1);
+}
+
+// The entries of L^T as codes (slot << 8 | pair), placed in their fixed order:
+// a node's entries are ordered by (slot group of 64, pair, lane), the order
+// of one wave walking all groups pair by pair.  One block takes the nodes
+// [kFillBand b, kFillBand (b + 1)) of one member and all of its slots; wave w
+// takes the slot groups [w G / 16, (w + 1) G / 16).  A first pass counts every
+// node's entries per wave, an exclusive scan over the waves gives each wave
+// the position after the groups before its range, and the second pass places
+// them: within a step (one pair of 64 slots) each lane draws its position
+// with an LDS atomic, and where lanes share a node they are ranked in lane
+// order.  The cursors live in LDS: from global memory each step waited on a
+// round trip to L2 (2.1 ms for a 128 x 128 lens on one wave, 20 us here).
+// Folded pairs of other than 2 x 2 subpixels are ordered by their rank among
+// the pixel's pairs.
+template <typename T>
+__global__ void __launch_bounds__(1024) k_prep_fill(SolveArgs a, int bands) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int m = blockIdx.x / bands, n0 = (blockIdx.x % bands) * kFillBand;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, n2 = a.n2;
+  const MemberInfo mi = a.minfo[m];
+  if (__builtin_amdgcn_readfirstlane((int)(mi.status != SL_ST_OK || n0 >= mi.I))) return;
+  const int ns = mi.ns, nb = min(kFillBand, mi.I - n0), G = mi.M / 64, sell = mi.sell;
+  const int cap = min(kFillBand, a.I_max);
+  int* cur = reinterpret_cast<int*>(smem) + (long)wid * cap;   // this wave's cursors
+  int* all = reinterpret_cast<int*>(smem);
+  int* base = all + (long)kFillW * cap;
+  const int32_t* cellp = a.cell + (long)m * a.slot_cap * n2;
+  const unsigned long long* pm = a.pmask + (long)m * a.slot_cap;
+  const int32_t* lbase = a.lt_base + (long)m * a.I_max;
+  LtEntry<T>* ent = reinterpret_cast<LtEntry<T>*>(a.lt_ent) + (long)m * a.lt_cap;
+  const int E = a.lt_ptr[(long)m * (a.I_max + 65) + (mi.I + 63) / 64];   // sliced-ELL entries
+  int* code2 = reinterpret_cast<int*>(reinterpret_cast<unsigned short*>(ent) + E);   // the paired form's weights
+  const bool cubic = a.interp == SL_INTERP_BICUBIC;
+  for (int i = tid; i < kFillW * cap; i += 1024) all[i] = 0;
+  for (int i = tid; i < nb; i += 1024) base[i] = lbase[n0 + i];
+  __syncthreads();
+  const int g0 = (wid * G) / kFillW, g1 = ((wid + 1) * G) / kFillW;
+  const int nq = cubic ? 16 * n2 : 4 * n2;
+  for (int g = g0; g < g1; ++g) {
+    const int t = g * 64 + lane;
+    const unsigned long long mask = pm[t];
+    if (n2 == 4 && !cubic) {
+      const int4 c4 = reinterpret_cast<const int4*>(cellp)[t];
+      const int cl[4] = {c4.x, c4.y, c4.z, c4.w};
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const unsigned nd = (unsigned)(corner_node(cl[q >> 2], q & 3, ns) - n0);
+        if (((unsigned)mask >> q) & 1u && nd < (unsigned)nb) atomicAdd(&cur[nd], 1);
+      }
+    } else {
+      for (int q = 0; q < nq; ++q) {
+        const int nd = pair_node(cubic, q, ns, mask, cellp + (long)t * n2) - n0;
+        if ((unsigned)nd < (unsigned)nb && nd + n0 >= 0) atomicAdd(&cur[nd], 1);
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < nb; i += 1024) {   // exclusive scan over the waves
+    int run = 0;
+    for (int w = 0; w < kFillW; ++w) {
+      const int c = all[(long)w * cap + i];
+      all[(long)w * cap + i] = run;
+      run += c;
+    }
+  }
+  __syncthreads();
+  // nd: node within the band, -1 for none
+  auto place = [&](int nd, int code) {
+    if (!__builtin_amdgcn_readfirstlane((int)(__ballot(nd >= 0) != 0ull))) return;   // uniform
+    int j = 0, after = 1;
+    if (nd >= 0) j = atomicAdd(&cur[nd], 1);
+    // one wave's LDS accesses complete in order: the read sees every lane's add
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-}
-
-// (B^T img)[pixel of slot t] for every slot (0 for empty slots), FP64, by all
-// threads of the block, into vbuf[slots] (global memory of this member).
-__device__ void correlate_slots(const SolveArgs& a, const double* img, int slots, const int32_t* pix,
-                                double* vbuf) {
-  const int nx = a.nx, ny = a.ny, K = a.K, ck = a.ck;
-  for (int t = threadIdx.x; t < slots; t += blockDim.x) {
-    const int rc = pix[t];
-    double v = 0.0;
-    if (rc >= 0) {
-      const int r = rc >> 16, c = rc & 0xFFFF;
-      for (int aa = 0; aa < K; ++aa) {
-        const int rr = r + aa - ck;
-        if (rr < 0 || rr >= ny) continue;
-        for (int bb = 0; bb < K; ++bb) {
-          const int cc = c + bb - ck;
-          if (cc < 0 || cc >= nx) continue;
-          v += a.psf[aa * K + bb] * img[rr * nx + cc];
-        }
-      }
+    if (nd >= 0) after = *reinterpret_cast<volatile int*>(&cur[nd]) - j;
+    // a lane that was not its node's last add sees more than its own: each such node's lanes are ranked
+    unsigned long long clash = __ballot(nd >= 0 && after != 1);
+    while (clash) {
+      const int k0 = __builtin_amdgcn_readlane(nd, __ffsll((unsigned long long)clash) - 1);
+      const unsigned long long same = __ballot(nd == k0);
+      if (nd == k0) j = j + after - __popcll(same) + lanes_below(same);
+      clash &= ~same;
     }
-    vbuf[t] = v;
-  }
-}
-
-// Right-hand side b = L^T B^T img in FP64 (Eq. 7: img = d) into bacc[I] (zeroed), by
-// one wave, from v = B^T img at the mapped pixels (vbuf, correlate_slots): it
-// walks the slots 64 at a time and spreads each lane's value over its
-// pixel's (node, weight) pairs, pair by pair, through wave_ordered_add.  The
-// order of every node's terms is therefore (slot group, pair, lane), the
-// same on every run.  `slots` is a multiple of 64.
-template <typename T>
-__device__ void rhs_fixed_order(const SolveArgs& a, const double* vbuf, int ns, int slots, const int32_t* pix,
-                                const int32_t* cellp, const T* fxp, const T* fyp, double* bacc, int* tag) {
-  const int lane = threadIdx.x & 63;
-  const int n2 = a.n2;
-  for (int t0 = 0; t0 < slots; t0 += 64) {
-    const int t = t0 + lane;
-    const int rc = pix[t];
-    const double v = vbuf[t];
-    if (a.interp == SL_INTERP_BICUBIC) {
-      for (int q = 0; q < 16 * n2; ++q) {
-        int nd = -1;
-        double w = 0.0;
-        if (rc >= 0) bicubic_pair(t, q, ns, n2, cellp, fxp, fyp, nd, w);
-        wave_ordered_add(bacc, tag, nd, w * v);
-      }
-    } else if (n2 == 4) {
-      int nd[16];
-      double ww[16];
-      if (rc >= 0) {
-        pixel_pairs4(t, ns, cellp, fxp, fyp, nd, ww);
-      } else {
+    if (nd >= 0) {
+      if (sell == 2) code2[paired_index(base[nd], j)] = code;
+      else ent[(long)base[nd] + (sell ? 64L : 1L) * j].off = code;
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+  for (int g = g0; g < g1; ++g) {   // uniform per wave
+    const int t = g * 64 + lane;
+    const unsigned long long mask = pm[t];
+    if (n2 == 4 && !cubic) {
+      const int4 c4 = reinterpret_cast<const int4*>(cellp)[t];
+      const int cl[4] = {c4.x, c4.y, c4.z, c4.w};
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          nd[q] = -1;
-          ww[q] = 0.0;
-        }
+      for (int q = 0; q < 16; ++q) {
+        const unsigned nd = (unsigned)(corner_node(cl[q >> 2], q & 3, ns) - n0);
+        place(((unsigned)mask >> q) & 1u && nd < (unsigned)nb ? (int)nd : -1, (t << 8) | q);
       }
-#pragma unroll
-      for (int q = 0; q < 16; ++q) wave_ordered_add(bacc, tag, nd[q], ww[q] * v);
+    } else if (cubic) {
+      for (int q = 0; q < nq; ++q) {
+        const int nd = pair_node(true, q, ns, 0ull, cellp + (long)t * n2);
+        place(nd >= n0 && nd - n0 < nb ? nd - n0 : -1, (t << 8) | q);
+      }
     } else {
-      int node[4 * SL_MAX_NSUB * SL_MAX_NSUB];
-      double wt[4 * SL_MAX_NSUB * SL_MAX_NSUB];
-      const int np = rc >= 0 ? pixel_pairs(t, ns, n2, cellp, fxp, fyp, node, wt) : 0;
-      int npmax = np;
-      for (int o = 32; o > 0; o >>= 1) npmax = max(npmax, __shfl_xor(npmax, o, 64));
-      for (int q = 0; q < npmax; ++q) wave_ordered_add(bacc, tag, q < np ? node[q] : -1, q < np ? wt[q] * v : 0.0);
+      unsigned long long rest = mask;
+      while (__builtin_amdgcn_readfirstlane((int)(__ballot(rest != 0ull) != 0ull))) {
+        int nd = -1, q = 0;
+        if (rest) {
+          q = __ffsll(rest) - 1;
+          rest &= rest - 1;
+          nd = corner_node(cellp[(long)t * n2 + (q >> 2)], q & 3, ns) - n0;
+          if (nd < 0 || nd >= nb) nd = -1;
+        }
+        place(nd, (t << 8) | q);
+      }
     }
   }
 }
 
+// acc + w v with the product rounded first (no fused multiply-add).
+__device__ __forceinline__ double add_product(double acc, double w, double v) {
+#pragma clang fp contract(off)
+  return acc + w * v;
+}
+
+// Replaces every entry's code by its frame offset and weight and forms
+// b = L^T B^T d on the way (Eq. 7; and A^T bhat of the Monte Carlo degrees of
+// freedom): one lane per row in slice order, so the entries are read and
+// written coalesced and each node's sum runs over its entries in their fixed
+// order, in FP64, from v = B^T d at the pixel and the FP64 weight.  Also the
+// padding entries, and the scale of the spectral preconditioner,
+// c = sum_i cov_i b_i^2 / sum_i b_i^2 with cov = L^T 1 (the weight each node
+// receives), a cheap stand-in for the Rayleigh quotient <b, L^T B^T B L b> / <b, b>.
+// Bound by the dependent reads entry -> record (48 bytes) -> v; four entries
+// of a row are in flight.
 template <typename T>
-__device__ void prep_member(const SolveArgs& a, int m, MemberInfo mi, const double* gl, int* bbox, int* scan,
-                            double* bacc) {
-  const int tid = threadIdx.x;
-  const int nx = a.nx, ny = a.ny, J = nx * ny, nsub = a.nsub, n2 = a.n2;
-  const Lens L = make_lens(gl);
-  const int ns = mi.ns;
-  const double h = 2.0 * a.R / (ns - 1);
-  int32_t* pix = a.pix_list + (long)m * a.slot_cap;
-  int32_t* cellp = a.cell + (long)m * a.slot_cap * n2;
-  T* fxp = reinterpret_cast<T*>(a.fx) + (long)m * a.slot_cap * n2;
-  T* fyp = reinterpret_cast<T*>(a.fy) + (long)m * a.slot_cap * n2;
-  // pass 1: count the pixels with at least one subpixel on the grid, and their bounding box
-  int count = 0;
-  for (int j0 = 0; j0 < J; j0 += blockDim.x) {
-    const int j = j0 + tid;
-    const int r = j / nx, c = j % nx;
-    bool mapped = false;
-    if (j < J) {
-      for (int k = 0; k < n2; ++k) {
-        double x, y, bx, by, fx, fy;
-        int cell;
-        subpixel_xy(r, c, k / nsub, k % nsub, nx, ny, a.pix, nsub, x, y);
-        lens_map(L, x, y, bx, by);
-        mapped |= grid_cell((bx + a.R) / h, (by + a.R) / h, ns, cell, fx, fy);
-      }
-    }
-    if (mapped) {
-      atomicMin(&bbox[0], r);
-      atomicMax(&bbox[1], r);
-      atomicMin(&bbox[2], c);
-      atomicMax(&bbox[3], c);
-    }
-    int tot;
-    (void)block_excl_count(mapped, scan, &tot);
-    count += tot;
-  }
-  // The table is interleaved: compacted entry pos goes to slot (pos % S) * 64 + pos / S,
-  // so the 64 lanes of a wave take pixels spread over the whole mapped region and
-  // their L^T atomics rarely hit the same source node; slots past the last entry
-  // hold -1.
-  const int Mtrue = __builtin_amdgcn_readfirstlane(count);   // block-uniform: branches below enclose barriers
-  const int S = (Mtrue + 63) / 64;
-  const int slots = 64 * S;
-  int base = 0;
-  for (int j0 = 0; j0 < J; j0 += blockDim.x) {
-    const int j = j0 + tid;
-    const int r = j / nx, c = j % nx;
-    bool mapped = false;
-    if (j < J) {
-      for (int k = 0; k < n2; ++k) {
-        double x, y, bx, by, fx, fy;
-        int cell;
-        subpixel_xy(r, c, k / nsub, k % nsub, nx, ny, a.pix, nsub, x, y);
-        lens_map(L, x, y, bx, by);
-        mapped |= grid_cell((bx + a.R) / h, (by + a.R) / h, ns, cell, fx, fy);
-      }
-    }
-    int tot;
-    const int pos = base + block_excl_count(mapped, scan, &tot);
-    if (mapped) {
-      const int slot = (pos % S) * 64 + pos / S;
-      pix[slot] = (r << 16) | c;   // packed row/column of the mapped pixel
-      for (int k = 0; k < n2; ++k) {
-        double x, y, bx, by, fx = 0.0, fy = 0.0;
-        int cell = -1;
-        subpixel_xy(r, c, k / nsub, k % nsub, nx, ny, a.pix, nsub, x, y);
-        lens_map(L, x, y, bx, by);
-        if (!grid_cell((bx + a.R) / h, (by + a.R) / h, ns, cell, fx, fy)) {
-          cell = -1;
-          fx = fy = 0.0;
-        } else if (a.interp == SL_INTERP_NEAREST) {   // the nearest of the cell's four nodes, weight 1
-          fx = fx >= 0.5 ? 1.0 : 0.0;
-          fy = fy >= 0.5 ? 1.0 : 0.0;
-        }
-        cellp[(long)slot * n2 + k] = cell;
-        fxp[(long)slot * n2 + k] = (T)fx;
-        fyp[(long)slot * n2 + k] = (T)fy;
-      }
-    }
-    base += tot;
-  }
-  for (int sl_ = tid; sl_ < slots; sl_ += blockDim.x) {
-    if ((sl_ % 64) * S + sl_ / 64 >= Mtrue) {
-      pix[sl_] = -1;
-      for (int k = 0; k < n2; ++k) {
-        cellp[(long)sl_ * n2 + k] = -1;
-        fxp[(long)sl_ * n2 + k] = (T)0;
-        fyp[(long)sl_ * n2 + k] = (T)0;
-      }
-    }
-  }
-  __syncthreads();
-  const int Mm = slots;
-  // right-hand side b = L^T B^T d (FP64): B^T d at the mapped pixels by every
-  // thread, then the scatter over the nodes in a fixed order by wave 0.  The
-  // per-slot values go to this member's L^T entry region, which
-  // build_transpose fills only later (it holds >= 8 slot_cap bytes).
-  const int I = ns * ns;
-  double* vbuf = reinterpret_cast<double*>(reinterpret_cast<LtEntry<T>*>(a.lt_ent) + (long)m * a.lt_cap);
-  // conflict tags of lane_rank, past the accumulator and the transpose build's arrays
-  int* tag = a.prep_tags ? reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(bacc) + 8L * a.I_max + 768)
-                         : nullptr;
-  for (int i = tid; i < I; i += blockDim.x) bacc[i] = 0.0;
-  correlate_slots(a, a.d, Mm, pix, vbuf);
-  __syncthreads();
-  if (tid < 64) rhs_fixed_order<T>(a, vbuf, ns, Mm, pix, cellp, fxp, fyp, bacc, tag);
-  __syncthreads();
-  const double inv_n2 = 1.0 / n2;
-  // scale of the spectral preconditioner: c = sum_i cov_i b_i^2 / sum_i b_i^2
-  // with cov = L^T 1 (the bilinear weight each node receives), a cheap
-  // stand-in for the Rayleigh quotient <b, L^T B^T B L b> / <b, b>
-  {
-    __shared__ double pcred[32];
-    double num = 0.0, den = 0.0;
-    for (int t = tid; t < Mm; t += blockDim.x) {
-      if (pix[t] < 0) continue;
-      if (a.interp == SL_INTERP_BICUBIC) {
-        for (int q = 0; q < 16 * n2; ++q) {
-          int nd;
-          double w;
-          bicubic_pair(t, q, ns, n2, cellp, fxp, fyp, nd, w);
-          if (nd >= 0) num += w * bacc[nd] * bacc[nd];
-        }
-        continue;
-      }
-      for (int k = 0; k < n2; ++k) {
-        const int cell = cellp[(long)t * n2 + k];
-        if (cell < 0) continue;
-        const double fx = (double)fxp[(long)t * n2 + k], fy = (double)fyp[(long)t * n2 + k];
-        const double b0 = bacc[cell], b1 = bacc[cell + 1], b2 = bacc[cell + ns], b3 = bacc[cell + ns + 1];
-        num += ((1 - fx) * (1 - fy) * b0 * b0 + fx * (1 - fy) * b1 * b1 + (1 - fx) * fy * b2 * b2 +
-                fx * fy * b3 * b3) * inv_n2;
-      }
-    }
-    for (int i = tid; i < I; i += blockDim.x) den += bacc[i] * bacc[i];
-    block_sum2(num, den, pcred);
-    if (tid == 0) mi.pc_c = den > 0.0 ? (float)(num / den) : 0.0f;
-  }
+__global__ void __launch_bounds__(1024) k_prep_rhs(SolveArgs a) {
+  __shared__ double red[32];
+  const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, n2 = a.n2;
+  const MemberInfo mi = a.minfo[m];
+  if (__builtin_amdgcn_readfirstlane(mi.status) != SL_ST_OK) return;
+  const int ns = mi.ns, I = mi.I, sell = __builtin_amdgcn_readfirstlane(mi.sell), nx = a.nx, J = a.nx * a.ny;
+  const int32_t* pix = a.pix_list + (long)m * a.slot_cap;
+  const int32_t* cellp = a.cell + (long)m * a.slot_cap * n2;
+  const T* fxp = reinterpret_cast<const T*>(a.fx) + (long)m * a.slot_cap * n2;
+  const T* fyp = reinterpret_cast<const T*>(a.fy) + (long)m * a.slot_cap * n2;
+  const int32_t* rp = a.lt_ptr + (long)m * (a.I_max + 65);
+  const int32_t* perm = a.lt_perm + (long)m * a.I_max;
+  const int32_t* lcnt = a.lt_cnt + (long)m * a.I_max;
+  LtEntry<T>* ent = reinterpret_cast<LtEntry<T>*>(a.lt_ent) + (long)m * a.lt_cap;
   double* bm = a.b + (long)m * a.I_max;
-  for (int i = tid; i < I; i += blockDim.x) bm[i] = bacc[i];
-  __syncthreads();
-  if (a.mcn) {   // A^T bhat of the Monte Carlo degrees of freedom, in the same fixed order
-    for (int i = tid; i < I; i += blockDim.x) bacc[i] = 0.0;
-    correlate_slots(a, a.mcn, Mm, pix, vbuf);
-    __syncthreads();
-    if (tid < 64) rhs_fixed_order<T>(a, vbuf, ns, Mm, pix, cellp, fxp, fyp, bacc, tag);
-    __syncthreads();
-    double* bhm = a.bh + (long)m * a.I_max;
-    for (int i = tid; i < I; i += blockDim.x) bhm[i] = bacc[i];
-    __syncthreads();
+  double* bhm = a.bh + (long)m * a.I_max;
+  const int halo = 2 * a.ckt;
+  const int pitch = (mi.c1 - mi.c0 + 1 + 2 * halo) | 1;
+  const bool cubic = a.interp == SL_INTERP_BICUBIC;
+  const int ngroups = (I + 63) / 64, E = sell ? rp[ngroups] : 0;
+  unsigned short* off16 = reinterpret_cast<unsigned short*>(ent);
+  float* w32 = reinterpret_cast<float*>(off16 + E);
+  double num = 0.0, den = 0.0;
+  struct Term {
+    int off;
+    double w, v, vh;
+  };
+  auto term = [&](int code, int node) {
+    Term x;
+    const int t = code >> 8, rc = pix[t], r = rc >> 16, c = rc & 0xFFFF;
+    x.off = (r - mi.r0 + halo) * pitch + (c - mi.c0 + halo);
+    x.w = pair_weight(cubic, t, code & 255, node, ns, n2, cellp, fxp, fyp);
+    x.v = a.btd[r * nx + c];
+    x.vh = a.mcn ? a.btd[J + r * nx + c] : 0.0;
+    return x;
+  };
+  for (int g = wid; g < (sell ? ngroups : (I + 63) / 64); g += 16) {
+    const int p = 64 * g + lane;
+    int node = -1, n = 0;
+    if (p < I) {
+      node = sell ? (perm[p] >> 16) * ns + (perm[p] & 0xFFFF) : p;
+      n = lcnt[node];
+    }
+    const int e0 = sell ? rp[g] + lane : (p < I ? rp[p] : 0);
+    const int len = sell ? (rp[g + 1] - rp[g]) >> 6 : n;   // slice length (the row's own in CSR)
+    const long step = sell ? 64L : 1L;
+    double acc = 0.0, acch = 0.0, cov = 0.0;
+    for (int j0 = 0; j0 < len; j0 += 4) {
+      int code[4];
+      Term x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = j0 + u;
+        code[u] = -1;
+        if (j < n) code[u] = sell == 2 ? reinterpret_cast<const int*>(w32)[paired_index(e0, j)] : ent[e0 + step * j].off;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (code[u] >= 0) x[u] = term(code[u], node);
+        else x[u] = Term{0, 0.0, 0.0, 0.0};
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = j0 + u;
+        if (j >= len) continue;
+        if (code[u] >= 0) {
+          acc = add_product(acc, x[u].w, x[u].v);
+          acch = add_product(acch, x[u].w, x[u].vh);
+          cov += x[u].w;
+        }
+        if (sell == 2) {
+          const long e = paired_index(e0, j);
+          off16[e] = (unsigned short)x[u].off;
+          w32[e] = (float)x[u].w;
+        } else {
+          LtEntry<T> y;
+          y.off = x[u].off;
+          y.w = (T)x[u].w;
+          ent[e0 + step * j] = y;
+        }
+      }
+    }
+    if (node >= 0) {
+      bm[node] = acc;
+      if (a.mcn) bhm[node] = acch;
+      num += cov * acc * acc;
+      den += acc * acc;
+    }
   }
-  int sell = 0;
-  if (Mtrue > 0)
-    sell = build_transpose<T>(a, m, ns, Mm, bbox, scan, reinterpret_cast<int*>(bacc), pix, cellp, fxp, fyp, tag);
-  if (tid == 0) {
-    const int fh = Mtrue > 0 ? bbox[1] - bbox[0] + 1 : 0, fw = Mtrue > 0 ? bbox[3] - bbox[2] + 1 : 0;
-    mi.lds_frame = (long)(fh + 4 * a.ckt + kSegR) * ((fw + 4 * a.ckt) | 1) <= a.lds_frame_cap;
-    mi.sell = sell;
-    mi.M = Mm;
-    mi.Mtrue = Mtrue;
-    mi.status = Mtrue > 0 ? SL_ST_OK : SL_ST_EMPTY;
-    mi.r0 = Mtrue > 0 ? bbox[0] : 0;
-    mi.r1 = Mtrue > 0 ? bbox[1] : -1;
-    mi.c0 = Mtrue > 0 ? bbox[2] : 0;
-    mi.c1 = Mtrue > 0 ? bbox[3] : -1;
-    a.minfo[m] = mi;
-  }
+  block_sum2(num, den, red);
+  if (tid == 0) a.minfo[m].pc_c = den > 0.0 ? (float)(num / den) : 0.0f;
 }
 
 // ------------------------------------------------------------------ banded pass
@@ -2475,7 +2427,7 @@ __global__ void __launch_bounds__(kNTof<T>) k_implicit(SolveArgs a) {
 // source-refinement search (Sec. 3.2), where every source node is a free
 // parameter and the lens is held fixed.  chi2[p] = ||B L s_p - d||^2 / sigma^2
 // over all J pixels (Eq. 4; pixels outside the dilated bounding box of the
-// mapped pixels keep their data).  k_setup and k_prep have built member 0's
+// mapped pixels keep their data).  k_setup and k_prep_* have built member 0's
 // trace table.  Persistent over the candidates: block b takes p = b, b +
 // gridDim.x, ...; the source is staged in LDS (in the bulk type), L gathers
 // it into the frame, B runs over the dilated box into Z, and the residual
@@ -2708,10 +2660,11 @@ static Layout make_layout(const sl_problem* pb, int max_ns, int M, int NL, int n
   L.cell = take(sizeof(int32_t) * (size_t)M * L.slot_cap * L.n2);
   L.fx = take(sz * (size_t)M * L.slot_cap * L.n2);
   L.fy = take(sz * (size_t)M * L.slot_cap * L.n2);
+  L.pmask = take(sizeof(unsigned long long) * (size_t)M * L.slot_cap);
+  L.btd = take(sizeof(double) * 2 * (size_t)L.J);
   L.b = take(sizeof(double) * (size_t)M * L.I_max);
   L.bh = take(sizeof(double) * (size_t)M * L.I_max);   // A^T bhat (Monte Carlo degrees of freedom)
   L.dofk = take(sizeof(double) * (size_t)M * NL);      // per-iterate estimate of the implicit solve
-  L.ltc = take(sizeof(int) * (size_t)M * L.I_max * kFillW);   // per-wave fill cursors (k_prep)
   L.s_all = take(sz * (size_t)M * NL * L.I_max);
   L.gframe_elems = (pb->img.ny + 4 * 16 + kSegR) * ((pb->img.nx + 4 * 16) | 1);   // widest window's halo
   L.gframe = take(sz * (size_t)n_wg * L.gframe_elems);
@@ -2721,6 +2674,8 @@ static Layout make_layout(const sl_problem* pb, int max_ns, int M, int NL, int n
   L.ibuf = take(sz * (size_t)n_wg * L.J);   // image residual of the implicit-regularisation solve
   L.lt_ptr = take(sizeof(int32_t) * (size_t)M * (L.I_max + 65));
   L.lt_perm = take(sizeof(int32_t) * (size_t)M * L.I_max);
+  L.lt_base = take(sizeof(int32_t) * (size_t)M * L.I_max);
+  L.lt_cnt = take(sizeof(int32_t) * (size_t)M * L.I_max);
   // twice the unpadded bound (4 or, bicubic, 16 nodes per subpixel): room for slice padding
   L.lt_cap = (pb->interp == SL_INTERP_BICUBIC ? 32LL : 8LL) * L.n2 * L.slot_cap;
   L.lt_ent = take((sz == 8 ? 16 : 8) * (size_t)M * (size_t)L.lt_cap);
@@ -2881,7 +2836,7 @@ struct LaunchCfg {
   SolveKernel ks = nullptr, ksd = nullptr;
   SolveKernel kpc = nullptr, kpcd = nullptr;   // preconditioned kernels, when some items may take them
   SolveKernel kmc = nullptr, kmcd = nullptr;   // Monte Carlo degrees-of-freedom pass, when requested
-  size_t lds = 0, prep_lds = 0, corner_lds = 0;
+  size_t lds = 0, layout_lds = 0, fill_lds = 0, corner_lds = 0;
 };
 
 // Chooses the CG kernel of variant v and its LDS budget and sets the
@@ -2941,12 +2896,8 @@ static int configure(SolveArgs& A, const Layout& L, const sl_tuning& v, LaunchCf
       return SL_ENOIMPL;
     }
   }
-  // FP64 right-hand-side accumulator, reused by the transposed-operator build (2 I + 192 ints),
-  // then one conflict tag per node when that fits in LDS
-  c->prep_lds = std::max(sizeof(double) * L.I_max, sizeof(int) * (2 * L.I_max + 192));
-  const size_t tagged = 8 * (size_t)L.I_max + 768 + sizeof(int) * (size_t)L.I_max;
-  A.prep_tags = tagged <= 159 * 1024;
-  if (A.prep_tags) c->prep_lds = tagged;
+  c->layout_lds = sizeof(int) * (2 * (size_t)L.I_max + 64 + 16 * 128 + (L.I_max + 63) / 64);
+  c->fill_lds = sizeof(int) * (kFillW + 1) * (size_t)std::min(kFillBand, L.I_max);
   // lcurve_corner_block: 12 n + 2 n^2 doubles (both spline systems at once)
   c->corner_lds = sizeof(double) * (2 * A.n_lambda * A.n_lambda + 12 * A.n_lambda + 16);
   static std::mutex mu;
@@ -2955,8 +2906,10 @@ static int configure(SolveArgs& A, const Layout& L, const sl_tuning& v, LaunchCf
     if (k) SL_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   if (c->kim)
     SL_HIP(hipFuncSetAttribute((const void*)c->kim, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  SL_HIP(hipFuncSetAttribute((const void*)k_prep<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)c->prep_lds));
+  SL_HIP(hipFuncSetAttribute((const void*)k_prep_layout<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)c->layout_lds));
+  SL_HIP(hipFuncSetAttribute((const void*)k_prep_fill<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)c->fill_lds));
   // up to 72 KB at SL_MAX_LAMBDA points
   SL_HIP(hipFuncSetAttribute((const void*)k_corner<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)c->corner_lds));
@@ -2979,7 +2932,27 @@ static int launch_pair(SolveKernel kb, SolveKernel kd, const Layout& L, const La
   return check_launch(what);
 }
 
-// Enqueues the launches of one solve on st: k_setup, k_prep, [k_split], the
+// Enqueues the member set-up: the trace tables and, with `adjoint`, L^T and the
+// right-hand sides (the candidate-source chi^2 needs neither).
+template <typename T>
+static int enqueue_prep(const SolveArgs& A, const LaunchCfg& c, hipStream_t st, bool adjoint) {
+  const unsigned tiles = (unsigned)((A.nx * A.ny + kPrepT - 1) / kPrepT), M = (unsigned)A.n_members;
+  const unsigned images = adjoint ? (A.mcn ? 2u : 1u) : 0u;   // B^T d, B^T bhat
+  hipLaunchKernelGGL(k_prep_trace<T>, dim3(tiles * (M + images)), dim3(kPrepT), 0, st, A);
+  if (int e = check_launch("k_prep_trace")) return e;
+  hipLaunchKernelGGL(k_prep_place<T>, dim3(tiles * M), dim3(kPrepT), 0, st, A);
+  if (int e = check_launch("k_prep_place")) return e;
+  if (!adjoint) return SL_OK;
+  hipLaunchKernelGGL(k_prep_layout<T>, dim3(M), dim3(1024), c.layout_lds, st, A);
+  if (int e = check_launch("k_prep_layout")) return e;
+  const int bands = (A.I_max + kFillBand - 1) / kFillBand;
+  hipLaunchKernelGGL(k_prep_fill<T>, dim3(M * bands), dim3(64 * kFillW), c.fill_lds, st, A, bands);
+  if (int e = check_launch("k_prep_fill")) return e;
+  hipLaunchKernelGGL(k_prep_rhs<T>, dim3(M), dim3(1024), 0, st, A);
+  return check_launch("k_prep_rhs");
+}
+
+// Enqueues the launches of one solve on st: k_setup, k_prep_*, [k_split], the
 // plain k_solve [beside the preconditioned k_solve on the side stream, joined
 // back to st], k_corner.  `profile` records HIP events on st around the CG
 // phase when profiling is on (never inside a capture).
@@ -2993,8 +2966,7 @@ static int enqueue(const SolveArgs& A, const LamList& lams, const Layout& L, con
   if (int e = setup_lds_attr<T>()) return e;
   hipLaunchKernelGGL(k_setup<T>, dim3(1), dim3(1024), kSetupLds, st, A, lams);
   if (int e = check_launch("k_setup")) return e;
-  hipLaunchKernelGGL(k_prep<T>, dim3(A.n_members), dim3(1024), c.prep_lds, st, A);
-  if (int e = check_launch("k_prep")) return e;
+  if (int e = enqueue_prep<T>(A, c, st, true)) return e;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (profile) {
     std::lock_guard<std::mutex> g(g_prof.mu);
@@ -3164,7 +3136,10 @@ static int prepare(const sl_problem* pb, const double* lens, const int32_t* ns, 
   A.b = (double*)(ws + L.b);
   A.bh = (double*)(ws + L.bh);
   A.dofk = (double*)(ws + L.dofk);
-  A.ltc = (int*)(ws + L.ltc);
+  A.pmask = (unsigned long long*)(ws + L.pmask);
+  A.btd = (double*)(ws + L.btd);
+  A.lt_base = (int32_t*)(ws + L.lt_base);
+  A.lt_cnt = (int32_t*)(ws + L.lt_cnt);
   A.mcbuf = ws + L.mcbuf;
   A.ibuf = ws + L.ibuf;
   A.mcn = opt->mc_noise;
@@ -3281,14 +3256,13 @@ int sl_chi2_sources(const sl_problem* pb, const double* lens, int ns, const doub
     if (int e = setup_lds_attr<float>()) return e;
     hipLaunchKernelGGL(k_setup<float>, dim3(1), dim3(1024), kSetupLds, st, A, lams);
     if (int e = check_launch("k_setup")) return e;
-    hipLaunchKernelGGL(k_prep<float>, dim3(1), dim3(1024), c.prep_lds, st, A);
+    if (int e = enqueue_prep<float>(A, c, st, false)) return e;
   } else {
     if (int e = setup_lds_attr<double>()) return e;
     hipLaunchKernelGGL(k_setup<double>, dim3(1), dim3(1024), kSetupLds, st, A, lams);
     if (int e = check_launch("k_setup")) return e;
-    hipLaunchKernelGGL(k_prep<double>, dim3(1), dim3(1024), c.prep_lds, st, A);
+    if (int e = enqueue_prep<double>(A, c, st, false)) return e;
   }
-  if (int e = check_launch("k_prep")) return e;
   hipLaunchKernelGGL(kc, dim3(nb), dim3(nt), c.lds, st, A, sources, n_sources, chi2);
   return check_launch("k_chi2_src");
 }
