@@ -88,7 +88,7 @@ struct alignas(16) Consts {
 };
 
 struct Layout {
-  size_t consts, lam, taps_d, taps_f, minfo, queues, pqueues, pix, cell, fx, fy, pmask, btd, b, bh, dofk, s_all, gframe, gz, rbuf, mcbuf, ibuf,
+  size_t consts, lam, taps_d, taps_f, minfo, queues, pqueues, pix, cell, fx, fy, pmask, btd, pcpart, b, bh, dofk, s_all, gframe, gz, rbuf, mcbuf, ibuf,
       lt_ptr, lt_perm, lt_base, lt_cnt,
       lt_ent,
       total;
@@ -181,6 +181,8 @@ struct SolveArgs {
   double* dofk;      // [member][n_lambda] implicit solve: the estimate after each iterate
   unsigned long long* pmask;   // [member][slot_cap] first-occurrence mask of a slot's (subpixel, corner) pairs
   double* btd;       // [2][J] B^T d and B^T bhat (FP64)
+  double* pcpart;    // [member][rhs_blocks][2] parts of the preconditioner scale's two sums
+  int rhs_blocks;    // blocks of k_prep_rhs per member
   int32_t* lt_base;  // [member][I_max] index of each node's first entry of the transposed operator
   int32_t* lt_cnt;   // [member][I_max] entries of each node
   void* mcbuf;       // [n_wg][5][I_max] r, xhat, rhat, phat, saved p of the pass
@@ -192,158 +194,219 @@ struct LamList {
   double v[SL_MAX_LAMBDA];
 };
 
+// Inclusive sum over the block's 1024 threads of a 64-bit value; `sc` holds 17
+// values of LDS.  Returns the inclusive prefix, *total the block's sum.
+__device__ __forceinline__ long long block_scan64(long long v, long long* sc, long long* total) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  for (int o = 1; o < 64; o <<= 1) {
+    const long long u = __shfl_up(v, o, 64);
+    if (lane >= o) v += u;
+  }
+  if (lane == 63) sc[wid] = v;
+  __syncthreads();
+  long long before = 0, all = 0;
+  for (int i = 0; i < 16; ++i) {
+    if (i < wid) before += sc[i];
+    all += sc[i];
+  }
+  __syncthreads();
+  *total = all;
+  return before + v;
+}
+
+// Lanes of this wave with the same key of up to 8 bits.
+__device__ __forceinline__ unsigned long long match8(int key) {
+  unsigned long long mk = ~0ull;
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const unsigned long long bal = __ballot((key >> b) & 1);
+    mk &= (key >> b) & 1 ? bal : ~bal;
+  }
+  return mk;
+}
+
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
+
+// One block; what bounds it is the latency of its dependent steps, so each of
+// them (offsets, sort, queues, factorisation, autocorrelations, edges) is
+// spread over the threads, every value computed as one thread would compute
+// it.  (One thread doing them in turn took 129 us for a 15 x 15 PSF and one
+// member, 345 us for 256 members x 16 lambdas, 560 us for a 21 x 21 PSF and
+// 24 lambdas.)
 template <typename T>
 __global__ void __launch_bounds__(1024) k_setup(SolveArgs a, LamList lams) {
-  // the tap table is built by thread 0 in LDS from the PSF staged there (in
-  // global memory every read of its loops waited on the stores before it) and
-  // copied out by all threads
   extern __shared__ __align__(16) unsigned char smem_setup[];
-  double* tsh = reinterpret_cast<double*>(smem_setup);
+  double* tp = reinterpret_cast<double*>(smem_setup);   // the tap table, built here and copied out
   __shared__ double red[32];
-  if (threadIdx.x < a.n_lambda) a.lamv[threadIdx.x] = lams.v[threadIdx.x];
-  __shared__ int counts[4097];
-  const int tid = threadIdx.x;
+  __shared__ long long scan64[16];
+  __shared__ int start[256], wcnt[16][256], sh_sep, sh_am[16];
+  __shared__ double sh_pm[16];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int M = a.n_members, K = a.K, ck = a.ck;
-  // the PSF staged in LDS beside the tap table, by all threads
-  double* psh = tsh + TapIdx(SL_MAX_PSF).total;
-  for (int i = tid; i < K * K; i += blockDim.x) psh[i] = a.psf[i];
+  const TapIdx ti(K);
+  double* psh = tp + TapIdx(SL_MAX_PSF).total;   // the PSF
+  if (tid < a.n_lambda) a.lamv[tid] = lams.v[tid];
+  for (int i = tid; i < K * K; i += 1024) psh[i] = a.psf[i];
+  for (int i = tid; i < ti.total; i += 1024) tp[i] = 0.0;
+  if (tid < 256) start[tid] = 0;
+  for (int i = tid; i < 16 * 256; i += 1024) (&wcnt[0][0])[i] = 0;
+  if (tid == 0) sh_sep = 1;
   __syncthreads();
-  // offsets of packed solutions; invalid ns contribute nothing
-  if (tid == 0) {
-    long long off = 0;
-    for (int m = 0; m < M; ++m) {
-      const int ns = a.ns[m];
-      const bool ok = ns >= 2 && ns <= a.max_ns;
+  // offsets of packed solutions (invalid ns contribute nothing) and the count of members per grid side
+  long long off0 = 0;
+  for (int m0 = 0; m0 < M; m0 += 1024) {
+    const int m = m0 + tid;
+    const int ns = m < M ? a.ns[m] : 0;
+    const bool ok = ns >= 2 && ns <= a.max_ns;
+    long long total;
+    const long long I = ok ? (long long)ns * ns : 0;
+    const long long off = off0 + block_scan64(I, scan64, &total) - I;
+    if (m < M) {
+      atomicAdd(&start[ok ? ns : 0], 1);
       a.s_off[m] = off;
-      a.minfo[m].ns = ok ? ns : 0;
-      a.minfo[m].I = ok ? ns * ns : 0;
-      a.minfo[m].off = off;
-      a.minfo[m].r0 = a.minfo[m].c0 = INT_MAX;   // k_prep_trace widens the box
-      a.minfo[m].r1 = a.minfo[m].c1 = INT_MIN;
-      off += ok ? (long long)ns * ns : 0;
+      MemberInfo& mi = a.minfo[m];
+      mi.ns = ok ? ns : 0;
+      mi.I = (int)I;
+      mi.off = off;
+      mi.r0 = mi.c0 = INT_MAX;   // k_prep_trace widens the box
+      mi.r1 = mi.c1 = INT_MIN;
     }
-    a.s_off[M] = off;
+    off0 += total;
   }
-  // counting sort of members by descending ns -> XCD queues round-robin
-  for (int i = tid; i <= 4096; i += blockDim.x) counts[i] = 0;
+  if (tid == 0) a.s_off[M] = off0;
+  // largest |P| (the first of equals) for the rank-1 test
+  double pm = 0.0;
+  int pi = INT_MAX;
+  for (int i = tid; i < K * K; i += 1024)
+    if (fabs(psh[i]) > pm) {
+      pm = fabs(psh[i]);
+      pi = i;
+    }
+  for (int o = 32; o > 0; o >>= 1) {
+    const double v = __shfl_xor(pm, o, 64);
+    const int i = __shfl_xor(pi, o, 64);
+    if (v > pm || (v == pm && i < pi)) {
+      pm = v;
+      pi = i;
+    }
+  }
+  if (lane == 0) {
+    sh_pm[wid] = pm;
+    sh_am[wid] = pi;
+  }
   __syncthreads();
-  if (tid == 0) {
-    for (int m = 0; m < M; ++m) {
-      const int ns = a.ns[m];
-      counts[(ns >= 2 && ns <= a.max_ns) ? ns : 0]++;
+  for (int w = 0; w < 16; ++w)
+    if (sh_pm[w] > pm || (sh_pm[w] == pm && sh_am[w] < pi)) {
+      pm = sh_pm[w];
+      pi = sh_am[w];
     }
-    int start = 0;   // exclusive prefix in descending ns order (keys are at most max_ns)
-    for (int v = a.max_ns < 4096 ? a.max_ns : 4096; v >= 0; --v) {
-      const int c = counts[v];
-      counts[v] = start;
-      start += c;
-    }
-    // rank r -> queue r % 8; the sort is stable in member index.  Within a
-    // queue the `heavy` smallest lambdas of every member come first (their
-    // solves take the most CG iterations, so starting them early shortens
-    // the tail of the launch), then the other lambdas; both parts keep the
-    // members in order, so the blocks of an XCD share few members at a time
-    // and their tables stay in its L2.
-    for (int m = 0; m < M; ++m) {
-      const int ns = a.ns[m];
-      const int key = (ns >= 2 && ns <= a.max_ns) ? ns : 0;
-      const int r = counts[key]++;
+  const int am = pm > 0.0 ? pi / K : 0, bm = pm > 0.0 ? pi % K : 0;
+  // start of every grid side in descending order (sides are at most 128)
+  int above = 0;
+  if (tid < 256)
+    for (int v = tid + 1; v < 256; ++v) above += start[v];
+  __syncthreads();
+  if (tid < 256) start[tid] = above;
+  // PSF factorisation P[a][b] = gy[a] * gx[b]
+  for (int i = tid; i < K * K; i += 1024) tp[ti.psf + i] = psh[i];
+  if (pm > 0.0 && tid < K) {
+    tp[ti.gy + tid] = psh[tid * K + bm];
+    tp[ti.gx + tid] = psh[am * K + tid] / psh[am * K + bm];
+  }
+  __syncthreads();
+  for (int i = tid; i < K * K; i += 1024)
+    if (fabs(psh[i] - tp[ti.gy + i / K] * tp[ti.gx + i % K]) > 1e-12 * pm) sh_sep = 0;
+  // Counting sort of the members by descending ns, stable in member index:
+  // rank r -> queue r % 8, position r / 8.  Within a queue the `heavy`
+  // smallest lambdas of every member come first (their solves take the most
+  // CG iterations, so starting them early shortens the tail of the launch),
+  // then the other lambdas; both parts keep the members in order, so the
+  // blocks of an XCD share few members at a time and their tables stay in its
+  // L2.
+  const int NL = a.n_lambda, H = min(NL, a.heavy);
+  for (int m0 = 0; m0 < M; m0 += 1024) {
+    const int m = m0 + tid;
+    const int ns = m < M ? a.ns[m] : 0;
+    const int key = m < M ? (ns >= 2 && ns <= a.max_ns ? ns : 0) : 255;   // 255: past the last member
+    const unsigned long long same = match8(key);
+    const int before = lanes_below(same);
+    if (before == 0) wcnt[wid][key] = __popcll(same);
+    __syncthreads();
+    if (m < M) {
+      int r = start[key] + before;
+      for (int w = 0; w < wid; ++w) r += wcnt[w][key];
       const int q = r & 7, t = r >> 3;
       const int nmq = (M - q + 7) / 8;   // members in queue q
-      const int H = a.n_lambda < a.heavy ? a.n_lambda : a.heavy;
-      for (int k = 0; k < a.n_lambda; ++k)
-        a.queues[q * a.qcap + (k < H ? t * H + k : nmq * H + t * (a.n_lambda - H) + (k - H))] = m * a.n_lambda + k;
+      int* Q = a.queues + q * a.qcap;
+      for (int k = 0; k < H; ++k) Q[t * H + k] = m * NL + k;
+      for (int k = H; k < NL; ++k) Q[nmq * H + t * (NL - H) + (k - H)] = m * NL + k;
     }
-    for (int q = 0; q < 8; ++q) {
-      // members with rank r = q + 8 t fill queue q densely
-      const int nm = (M > q) ? (M - q + 7) / 8 : 0;
-      a.consts->qcount[q] = nm * a.n_lambda;
-      a.consts->qhead[q] = 0;
-      a.consts->pqcount[q] = 0;
-      a.consts->pqhead[q] = 0;
-    }
-    // PSF: rank-1 test and factorisation P[a][b] = gy[a] * gx[b]
-    const TapIdx ti(K);
-    int am = 0, bm = 0;
-    double pmax = 0.0;
-    for (int i = 0; i < K * K; ++i)
-      if (fabs(psh[i]) > pmax) {
-        pmax = fabs(psh[i]);
-        am = i / K;
-        bm = i % K;
+    __syncthreads();
+    if (tid < 256) {
+      int n = 0;
+      for (int w = 0; w < 16; ++w) {
+        n += wcnt[w][tid];
+        wcnt[w][tid] = 0;
       }
-    double* tp = tsh;
-    for (int i = 0; i < ti.total; ++i) tp[i] = 0.0;
-    for (int i = 0; i < K * K; ++i) tp[ti.psf + i] = psh[i];
-    int sep = pmax > 0.0;
-    if (sep) {
-      for (int x = 0; x < K; ++x) {
-        tp[ti.gy + x] = psh[x * K + bm];
-        tp[ti.gx + x] = psh[am * K + x] / psh[am * K + bm];
-      }
-      for (int x = 0; x < K && sep; ++x)
-        for (int y = 0; y < K; ++y)
-          if (fabs(psh[x * K + y] - tp[ti.gy + x] * tp[ti.gx + y]) > 1e-12 * pmax) {
-            sep = 0;
-            break;
-          }
+      start[tid] += n;
     }
-    // the banded path needs the kernel's window to cover +-2ck
-    if (ck > a.ckt || a.force_direct) sep = 0;
-    a.consts->sep = sep;
-    if (sep) {
-      // autocorrelations a[d] = sum_i g[i] g[i-d], stored at index d + 2*kMaxCK
-      for (int dd = -(K - 1); dd <= K - 1; ++dd) {
-        double sx = 0.0, sy = 0.0;
-        for (int i = 0; i < K; ++i) {
-          const int j = i - dd;
-          if (j < 0 || j >= K) continue;
-          sx += tp[ti.gx + i] * tp[ti.gx + j];
-          sy += tp[ti.gy + i] * tp[ti.gy + j];
+    __syncthreads();
+  }
+  if (tid < 8) {   // members with rank q + 8 t fill queue q densely
+    const int nm = M > tid ? (M - tid + 7) / 8 : 0;
+    a.consts->qcount[tid] = nm * NL;
+    a.consts->qhead[tid] = 0;
+    a.consts->pqcount[tid] = 0;
+    a.consts->pqhead[tid] = 0;
+  }
+  // the banded path needs the kernel's window to cover +-2ck
+  const bool sep = pm > 0.0 && sh_sep && ck <= a.ckt && !a.force_direct;
+  if (tid == 0) a.consts->sep = sep;
+  if (sep) {
+    // autocorrelations a[d] = sum_i g[i] g[i-d], stored at index d + 2*kMaxCK
+    for (int e = tid; e < 2 * (2 * K - 1); e += 1024) {
+      const int dd = e / 2 - (K - 1), g0 = e & 1 ? ti.gy : ti.gx;
+      double s = 0.0;
+      for (int i = 0; i < K; ++i) {
+        const int j = i - dd;
+        if (j < 0 || j >= K) continue;
+        s += tp[g0 + i] * tp[g0 + j];
+      }
+      tp[(e & 1 ? ti.ay : ti.ax) + dd + 2 * kMaxCK] = s;
+    }
+    // edge corrections: the truncated 1-D convolution C has (C^T C)[c][c']
+    // = a[c'-c] - sum over intermediate indices k outside the image
+    for (int e = tid; e < 4 * ck * ck; e += 1024) {
+      const int p = (e >> 2) / ck, q = (e >> 2) % ck, g0 = e & 1 ? ti.gy : ti.gx;
+      double s = 0.0;
+      if (!(e & 2)) {
+        for (int k = -ck; k < 0; ++k) {
+          const int i1 = k - p + ck, i2 = k - q + ck;
+          if (i1 >= 0 && i1 < K && i2 >= 0 && i2 < K) s += tp[g0 + i1] * tp[g0 + i2];
         }
-        tp[ti.ax + dd + 2 * kMaxCK] = sx;
-        tp[ti.ay + dd + 2 * kMaxCK] = sy;
-      }
-      // edge corrections: the truncated 1-D convolution C has (C^T C)[c][c']
-      // = a[c'-c] - sum over intermediate indices k outside the image
-      for (int p = 0; p < ck; ++p)
-        for (int q = 0; q < ck; ++q) {
-          double lx = 0.0, ly = 0.0, rx = 0.0, ry = 0.0;
-          for (int k = -ck; k < 0; ++k) {
-            const int i1 = k - p + ck, i2 = k - q + ck;
-            if (i1 >= 0 && i1 < K && i2 >= 0 && i2 < K) {
-              lx += tp[ti.gx + i1] * tp[ti.gx + i2];
-              ly += tp[ti.gy + i1] * tp[ti.gy + i2];
-            }
-          }
-          // right edge: outputs c = n - ck + p, inputs c' = n - ck + q, k = n + kk
-          for (int kk = 0; kk < ck; ++kk) {
-            const int i1 = kk + 2 * ck - p, i2 = kk + 2 * ck - q;   // k - c + ck, k - c' + ck
-            if (i1 >= 0 && i1 < K && i2 >= 0 && i2 < K) {
-              rx += tp[ti.gx + i1] * tp[ti.gx + i2];
-              ry += tp[ti.gy + i1] * tp[ti.gy + i2];
-            }
-          }
-          tp[ti.elx + p * ck + q] = lx;
-          tp[ti.ely + p * ck + q] = ly;
-          tp[ti.erx + p * ck + q] = rx;
-          tp[ti.ery + p * ck + q] = ry;
+        tp[(e & 1 ? ti.ely : ti.elx) + p * ck + q] = s;
+      } else {
+        // right edge: outputs c = n - ck + p, inputs c' = n - ck + q, k = n + kk
+        for (int kk = 0; kk < ck; ++kk) {
+          const int i1 = kk + 2 * ck - p, i2 = kk + 2 * ck - q;   // k - c + ck, k - c' + ck
+          if (i1 >= 0 && i1 < K && i2 >= 0 && i2 < K) s += tp[g0 + i1] * tp[g0 + i2];
         }
+        tp[(e & 1 ? ti.ery : ti.erx) + p * ck + q] = s;
+      }
     }
   }
   __syncthreads();
-  {
-    const TapIdx ti(K);
-    T* tt = reinterpret_cast<T*>(a.taps_t);
-    for (int i = tid; i < ti.total; i += blockDim.x) {
-      a.taps_d[i] = tsh[i];
-      tt[i] = (T)tsh[i];
-    }
+  T* tt = reinterpret_cast<T*>(a.taps_t);
+  for (int i = tid; i < ti.total; i += 1024) {
+    a.taps_d[i] = tp[i];
+    tt[i] = (T)tp[i];
   }
   // sums of d^2 and of the Monte Carlo draws squared, in FP64
   double acc = 0.0, accn = 0.0;
   const int J = a.nx * a.ny;
-  for (int j = tid; j < J; j += blockDim.x) {
+  for (int j = tid; j < J; j += 1024) {
     acc += a.d[j] * a.d[j];
     if (a.mcn) accn += a.mcn[j] * a.mcn[j];
   }
@@ -361,7 +424,7 @@ __global__ void __launch_bounds__(1024) k_setup(SolveArgs a, LamList lams) {
 // The tables of every member, by five grid-wide kernels (one block per member
 // did all of it before: 2.9 ms for a single 128 x 128 lens, 4.0 ms for 256 of
 // them, nearly all of it waves waiting on one another's cursors and on one
-// wave's ordered sums; the five take 0.1 and 0.6 ms):
+// wave's ordered sums; the five take 0.14 and 0.95 ms):
 //   k_prep_trace   the FP64 subpixel trace, once, and B^T d once per call
 //   k_prep_place   compaction into the interleaved trace table
 //   k_prep_layout  row lengths of L^T, their order and the storage layout
@@ -414,10 +477,17 @@ __global__ void __launch_bounds__(kPrepT) k_prep_trace(SolveArgs a) {
     for (int aa = 0; aa < K; ++aa) {
       const int rr = r + aa - ck;
       if (rr < 0 || rr >= ny) continue;
-      for (int bb_ = 0; bb_ < K; ++bb_) {
-        const int cc = c + bb_ - ck;
-        if (cc < 0 || cc >= nx) continue;
-        v += a.psf[aa * K + bb_] * img[rr * nx + cc];
+      for (int b0 = 0; b0 < K; b0 += 8) {   // eight taps in flight; a tap off the image adds zero
+        double x[8], p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int cc = c + b0 + u - ck;
+          const bool on = b0 + u < K && cc >= 0 && cc < nx;
+          x[u] = on ? img[rr * nx + cc] : 0.0;
+          p[u] = b0 + u < K ? a.psf[aa * K + b0 + u] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += p[u] * x[u];
       }
     }
     a.btd[(long)(m - a.n_members) * J + j] = v;
@@ -625,6 +695,21 @@ __device__ __forceinline__ int pair_node(bool cubic, int q, int ns, unsigned lon
   return r < 0 || r >= ns || col < 0 || col >= ns ? -1 : r * ns + col;
 }
 
+// The weight below for 2 x 2 subpixels with cells cl and fractions f, g.
+template <typename T>
+__device__ __forceinline__ double pair_weight4(int node, int ns, const int32_t* cl, const T* f, const T* g) {
+  double w = 0.0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double fx = (double)f[k], fy = (double)g[k];
+    const int d = node - cl[k];
+    const double wx = d == 0 || d == ns ? 1 - fx : fx, wy = d == 0 || d == 1 ? 1 - fy : fy;
+    const double wk = wx * wy * 0.25;
+    w += cl[k] >= 0 && (d == 0 || d == 1 || d == ns || d == ns + 1) ? wk : 0.0;
+  }
+  return w;
+}
+
 // FP64 weight of mapped slot t's pair q at `node`, the 1/n^2 subpixel average
 // included: for bilinear and nearest L the weights of all the pixel's
 // subpixels at the node, added in subpixel order.
@@ -639,16 +724,7 @@ __device__ __forceinline__ double pair_weight(bool cubic, int t, int q, int node
   if (n2 == 4) {
     const int4 c4 = reinterpret_cast<const int4*>(cellp)[t];
     const int cl[4] = {c4.x, c4.y, c4.z, c4.w};
-    double w = 0.0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const double fx = (double)fxp[4L * t + k], fy = (double)fyp[4L * t + k];
-      const int d = node - cl[k];
-      const double wx = d == 0 || d == ns ? 1 - fx : fx, wy = d == 0 || d == 1 ? 1 - fy : fy;
-      const double wk = wx * wy * 0.25;
-      w += cl[k] >= 0 && (d == 0 || d == 1 || d == ns || d == ns + 1) ? wk : 0.0;
-    }
-    return w;
+    return pair_weight4(node, ns, cl, fxp + 4L * t, fyp + 4L * t);
   }
   const double inv = 1.0 / n2;
   double w = 0.0;
@@ -669,21 +745,6 @@ __device__ __forceinline__ int len_bucket(int c) {
   const int msb = 31 - __clz(c);
   const int frac = msb >= 2 ? (c >> (msb - 2)) & 3 : (c << (2 - msb)) & 3;
   return 4 * msb + frac + 1;
-}
-
-// Lanes of this wave with the same 7-bit key.
-__device__ __forceinline__ unsigned long long match7(int key) {
-  unsigned long long mk = ~0ull;
-#pragma unroll
-  for (int b = 0; b < 7; ++b) {
-    const unsigned long long bal = __ballot((key >> b) & 1);
-    mk &= (key >> b) & 1 ? bal : ~bal;
-  }
-  return mk;
-}
-
-__device__ __forceinline__ int lanes_below(unsigned long long mask) {
-  return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
 }
 
 // Layout of L^T for one member (node-major form, sliced-ELL with rows sorted
@@ -778,7 +839,7 @@ __global__ void __launch_bounds__(1024) k_prep_layout(SolveArgs a) {
   for (int g = g0; g < g1; ++g) {
     const int i = 64 * g + lane, c = i < I ? cnt[i] : 0;
     const int b = i < I ? len_bucket(c) : 127;   // 127: no row length reaches it
-    const unsigned long long same = match7(b);
+    const unsigned long long same = match8(b);
     int* pos = &whist[wid * 128 + b];
     const int p = *pos + lanes_below(same);
     if (i < I) {
@@ -984,46 +1045,160 @@ __device__ __forceinline__ double add_product(double acc, double w, double v) {
 // padding entries, and the scale of the spectral preconditioner,
 // c = sum_i cov_i b_i^2 / sum_i b_i^2 with cov = L^T 1 (the weight each node
 // receives), a cheap stand-in for the Rayleigh quotient <b, L^T B^T B L b> / <b, b>.
-// Bound by the dependent reads entry -> record (48 bytes) -> v; four entries
-// of a row are in flight.
+// Bound by the dependent reads entry -> record (48 bytes) -> v, one cache line
+// each per lane.  One wave takes one slice, four slices a block (one block per
+// member left most of the chip idle for a single 128 x 128 member, 153 -> 51
+// us with rhs_row's batched reads, and ended with its slowest block for 256
+// of them, 417 -> 330 us).  Each block leaves its part of c's two sums for
+// k_split.
+constexpr int kRhsT = 256;
+__host__ __device__ __forceinline__ int rhs_blocks_of(int I) { return (I + kRhsT - 1) / kRhsT; }
+// Blocks per member in a launch: no more than keep the grid under 2^30 threads.
+static int rhs_grid(int I_max, int M) { return std::min(rhs_blocks_of(I_max), std::max(1, (1 << 22) / M)); }
+
+// What k_prep_rhs's rows read and write.
 template <typename T>
-__global__ void __launch_bounds__(1024) k_prep_rhs(SolveArgs a) {
-  __shared__ double red[32];
-  const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, n2 = a.n2;
+struct RhsView {
+  const int32_t* pix;
+  const int32_t* cellp;
+  const T* fxp;
+  const T* fyp;
+  const double* v;    // B^T d
+  const double* vh;   // B^T bhat, or NULL
+  LtEntry<T>* ent;
+  unsigned short* off16;   // the paired form's offsets and weights
+  float* w32;
+  int ns, n2, nx, off0, pitch;   // frame offset of image pixel (r, c): r pitch + c + off0
+  bool cubic;
+};
+
+// One row: its n entries from index e0, and the padding up to len.  FAST: 2 x 2
+// subpixels, bilinear or nearest, no Monte Carlo draws.  The reads of U
+// entries are issued together, level by level (code, then pixel and record,
+// then v), and the next codes ahead of their use: with the general form's
+// branches between them every entry waited for its own three reads.
+template <typename T, bool FAST, bool PAIRED>
+__device__ __forceinline__ void rhs_row(const RhsView<T>& o, int node, int n, int e0, int len, long step, double& acc,
+                                        double& acch, double& cov) {
+  constexpr int U = FAST ? (sizeof(T) == 4 ? 8 : 4) : 1;
+  int next[U];
+  auto codes = [&](int j0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + u;
+      next[u] = -1;
+      if (j < n) next[u] = PAIRED ? reinterpret_cast<const int*>(o.w32)[paired_index(e0, j)] : o.ent[e0 + step * j].off;
+    }
+  };
+  codes(0);
+  for (int j0 = 0; j0 < len; j0 += U) {
+    int code[U], rc[U];
+    double w[U], v[U], vh[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      code[u] = next[u];
+      rc[u] = o.pix[max(code[u], 0) >> 8];   // slot 0 stands in for no entry
+    }
+    if constexpr (FAST) {
+      int4 c4[U];
+      T f[U][4], g[U][4];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int t = max(code[u], 0) >> 8;
+        c4[u] = reinterpret_cast<const int4*>(o.cellp)[t];
+        if constexpr (sizeof(T) == 4) {
+          const float4 x = reinterpret_cast<const float4*>(o.fxp)[t], y = reinterpret_cast<const float4*>(o.fyp)[t];
+          f[u][0] = x.x; f[u][1] = x.y; f[u][2] = x.z; f[u][3] = x.w;
+          g[u][0] = y.x; g[u][1] = y.y; g[u][2] = y.z; g[u][3] = y.w;
+        } else {
+          const double2* x = reinterpret_cast<const double2*>(o.fxp) + 2L * t;
+          const double2* y = reinterpret_cast<const double2*>(o.fyp) + 2L * t;
+          const double2 x0 = x[0], x1 = x[1], y0 = y[0], y1 = y[1];
+          f[u][0] = x0.x; f[u][1] = x0.y; f[u][2] = x1.x; f[u][3] = x1.y;
+          g[u][0] = y0.x; g[u][1] = y0.y; g[u][2] = y1.x; g[u][3] = y1.y;
+        }
+      }
+      codes(j0 + U);
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = o.v[(rc[u] >> 16) * o.nx + (rc[u] & 0xFFFF)];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int cl[4] = {c4[u].x, c4[u].y, c4[u].z, c4[u].w};
+        w[u] = pair_weight4(node, o.ns, cl, f[u], g[u]);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int t = max(code[u], 0) >> 8, at = (rc[u] >> 16) * o.nx + (rc[u] & 0xFFFF);
+        w[u] = pair_weight(o.cubic, t, code[u] & 255, node, o.ns, o.n2, o.cellp, o.fxp, o.fyp);
+        v[u] = o.v[at];
+        vh[u] = o.vh ? o.vh[at] : 0.0;
+      }
+      codes(j0 + U);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + u;
+      if (j >= len) continue;
+      int off = 0;
+      T wt = (T)0;
+      if (code[u] >= 0) {
+        acc = add_product(acc, w[u], v[u]);
+        if (!FAST) acch = add_product(acch, w[u], vh[u]);
+        cov += w[u];
+        off = (rc[u] >> 16) * o.pitch + (rc[u] & 0xFFFF) + o.off0;
+        wt = (T)w[u];
+      }
+      if (PAIRED) {
+        const long e = paired_index(e0, j);
+        o.off16[e] = (unsigned short)off;
+        o.w32[e] = (float)wt;
+      } else {
+        LtEntry<T> y;
+        y.off = off;
+        y.w = wt;
+        o.ent[e0 + step * j] = y;
+      }
+    }
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kRhsT) k_prep_rhs(SolveArgs a) {
+  __shared__ double red[2 * kRhsT / 64];
+  // blocks go to the XCDs in turn: all of a member's blocks on one of them, whose L2 holds its records
+  const int idx = blockIdx.x >> 3, m = (idx / a.rhs_blocks) * 8 + (blockIdx.x & 7), part = idx % a.rhs_blocks;
+  if (m >= a.n_members) return;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, n2 = a.n2;
   const MemberInfo mi = a.minfo[m];
-  if (__builtin_amdgcn_readfirstlane(mi.status) != SL_ST_OK) return;
-  const int ns = mi.ns, I = mi.I, sell = __builtin_amdgcn_readfirstlane(mi.sell), nx = a.nx, J = a.nx * a.ny;
-  const int32_t* pix = a.pix_list + (long)m * a.slot_cap;
-  const int32_t* cellp = a.cell + (long)m * a.slot_cap * n2;
-  const T* fxp = reinterpret_cast<const T*>(a.fx) + (long)m * a.slot_cap * n2;
-  const T* fyp = reinterpret_cast<const T*>(a.fy) + (long)m * a.slot_cap * n2;
+  if (__builtin_amdgcn_readfirstlane((int)(mi.status != SL_ST_OK || part >= rhs_blocks_of(mi.I)))) return;
+  const int ns = mi.ns, I = mi.I, sell = __builtin_amdgcn_readfirstlane(mi.sell);
   const int32_t* rp = a.lt_ptr + (long)m * (a.I_max + 65);
   const int32_t* perm = a.lt_perm + (long)m * a.I_max;
   const int32_t* lcnt = a.lt_cnt + (long)m * a.I_max;
-  LtEntry<T>* ent = reinterpret_cast<LtEntry<T>*>(a.lt_ent) + (long)m * a.lt_cap;
   double* bm = a.b + (long)m * a.I_max;
   double* bhm = a.bh + (long)m * a.I_max;
-  const int halo = 2 * a.ckt;
-  const int pitch = (mi.c1 - mi.c0 + 1 + 2 * halo) | 1;
-  const bool cubic = a.interp == SL_INTERP_BICUBIC;
+  const int halo = 2 * a.ckt, pitch = (mi.c1 - mi.c0 + 1 + 2 * halo) | 1;
   const int ngroups = (I + 63) / 64, E = sell ? rp[ngroups] : 0;
-  unsigned short* off16 = reinterpret_cast<unsigned short*>(ent);
-  float* w32 = reinterpret_cast<float*>(off16 + E);
+  RhsView<T> o;
+  o.pix = a.pix_list + (long)m * a.slot_cap;
+  o.cellp = a.cell + (long)m * a.slot_cap * n2;
+  o.fxp = reinterpret_cast<const T*>(a.fx) + (long)m * a.slot_cap * n2;
+  o.fyp = reinterpret_cast<const T*>(a.fy) + (long)m * a.slot_cap * n2;
+  o.v = a.btd;
+  o.vh = a.mcn ? a.btd + a.nx * a.ny : nullptr;
+  o.ent = reinterpret_cast<LtEntry<T>*>(a.lt_ent) + (long)m * a.lt_cap;
+  o.off16 = reinterpret_cast<unsigned short*>(o.ent);
+  o.w32 = reinterpret_cast<float*>(o.off16 + E);
+  o.ns = ns;
+  o.n2 = n2;
+  o.nx = a.nx;
+  o.pitch = pitch;
+  o.off0 = (halo - mi.r0) * pitch + halo - mi.c0;
+  o.cubic = a.interp == SL_INTERP_BICUBIC;
+  const bool fast = n2 == 4 && !o.cubic && !o.vh;
   double num = 0.0, den = 0.0;
-  struct Term {
-    int off;
-    double w, v, vh;
-  };
-  auto term = [&](int code, int node) {
-    Term x;
-    const int t = code >> 8, rc = pix[t], r = rc >> 16, c = rc & 0xFFFF;
-    x.off = (r - mi.r0 + halo) * pitch + (c - mi.c0 + halo);
-    x.w = pair_weight(cubic, t, code & 255, node, ns, n2, cellp, fxp, fyp);
-    x.v = a.btd[r * nx + c];
-    x.vh = a.mcn ? a.btd[J + r * nx + c] : 0.0;
-    return x;
-  };
-  for (int g = wid; g < (sell ? ngroups : (I + 63) / 64); g += 16) {
+  for (int g = part * (kRhsT / 64) + wid; g < ngroups; g += a.rhs_blocks * (kRhsT / 64)) {
     const int p = 64 * g + lane;
     int node = -1, n = 0;
     if (p < I) {
@@ -1034,41 +1209,10 @@ __global__ void __launch_bounds__(1024) k_prep_rhs(SolveArgs a) {
     const int len = sell ? (rp[g + 1] - rp[g]) >> 6 : n;   // slice length (the row's own in CSR)
     const long step = sell ? 64L : 1L;
     double acc = 0.0, acch = 0.0, cov = 0.0;
-    for (int j0 = 0; j0 < len; j0 += 4) {
-      int code[4];
-      Term x[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = j0 + u;
-        code[u] = -1;
-        if (j < n) code[u] = sell == 2 ? reinterpret_cast<const int*>(w32)[paired_index(e0, j)] : ent[e0 + step * j].off;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (code[u] >= 0) x[u] = term(code[u], node);
-        else x[u] = Term{0, 0.0, 0.0, 0.0};
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = j0 + u;
-        if (j >= len) continue;
-        if (code[u] >= 0) {
-          acc = add_product(acc, x[u].w, x[u].v);
-          acch = add_product(acch, x[u].w, x[u].vh);
-          cov += x[u].w;
-        }
-        if (sell == 2) {
-          const long e = paired_index(e0, j);
-          off16[e] = (unsigned short)x[u].off;
-          w32[e] = (float)x[u].w;
-        } else {
-          LtEntry<T> y;
-          y.off = x[u].off;
-          y.w = (T)x[u].w;
-          ent[e0 + step * j] = y;
-        }
-      }
-    }
+    if (fast && sell == 2) rhs_row<T, true, true>(o, node, n, e0, len, step, acc, acch, cov);
+    else if (fast) rhs_row<T, true, false>(o, node, n, e0, len, step, acc, acch, cov);
+    else if (sell == 2) rhs_row<T, false, true>(o, node, n, e0, len, step, acc, acch, cov);
+    else rhs_row<T, false, false>(o, node, n, e0, len, step, acc, acch, cov);
     if (node >= 0) {
       bm[node] = acc;
       if (a.mcn) bhm[node] = acch;
@@ -1077,7 +1221,11 @@ __global__ void __launch_bounds__(1024) k_prep_rhs(SolveArgs a) {
     }
   }
   block_sum2(num, den, red);
-  if (tid == 0) a.minfo[m].pc_c = den > 0.0 ? (float)(num / den) : 0.0f;
+  if (tid == 0) {
+    double* pc = a.pcpart + 2L * ((long)m * a.rhs_blocks + part);
+    pc[0] = num;
+    pc[1] = den;
+  }
 }
 
 // ------------------------------------------------------------------ banded pass
@@ -2517,31 +2665,48 @@ static Chi2Kernel pick_chi2_kernel(int ckt) {
   return nullptr;
 }
 
-// Moves the items that take the spectral preconditioner into their own queues
-// (stable, per XCD queue): valid member, FP32, curvature H, frame in LDS with
-// room for the n x n scratch, and lambda >= pc_theta c.  One block.
+// Finishes the preconditioner's scale of every member (the sums of
+// k_prep_rhs's blocks, in block order) and moves the items that take the
+// spectral preconditioner into their own queues (stable, per XCD queue): valid
+// member, FP32, curvature H, frame in LDS with room for the n x n scratch, and
+// lambda >= pc_theta c.  One block, one wave per queue, 64 items per step (a
+// lane per queue took 190 us for 4096 items and 290 us for 6144).
 template <typename T>
-__global__ void __launch_bounds__(64) k_split(SolveArgs a) {
-  const int q = threadIdx.x;
-  if (q < 8) {
-    const int n = a.consts->qcount[q];
-    int keep = 0, moved = 0;
-    for (int k = 0; k < n; ++k) {   // in place: keep <= k, so no unread item is overwritten
-      const int item = a.queues[q * a.qcap + k];
+__global__ void __launch_bounds__(512) k_split(SolveArgs a) {
+  for (int m = threadIdx.x; m < a.n_members; m += 512) {
+    double num = 0.0, den = 0.0;
+    const double* pc = a.pcpart + 2L * m * a.rhs_blocks;
+    const int n = a.minfo[m].status == SL_ST_OK ? min(rhs_blocks_of(a.minfo[m].I), a.rhs_blocks) : 0;
+    for (int i = 0; i < n; ++i) {
+      num += pc[2 * i];
+      den += pc[2 * i + 1];
+    }
+    a.minfo[m].pc_c = den > 0.0 ? (float)(num / den) : 0.0f;
+  }
+  __syncthreads();
+  const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int n = a.consts->qcount[q];
+  int* Q = a.queues + q * a.qcap;
+  int* PQ = a.pqueues + q * a.qcap;
+  int keep = 0, moved = 0;
+  for (int k0 = 0; k0 < n; k0 += 64) {   // in place: what is written lies before the items still to be read
+    const int k = k0 + lane;
+    const int item = k < n ? Q[k] : -1;
+    bool pc = false;
+    if (item >= 0) {
       const MemberInfo mi = a.minfo[item / a.n_lambda];
       const double lam = a.lamv[item % a.n_lambda];
-      const bool fits = mi.lds_frame != 0;
-      const bool pc = sizeof(T) == 4 && a.reg == SL_H_CURVATURE && !a.plain_cg && mi.status == SL_ST_OK && fits &&
-                      mi.ns * mi.ns <= a.lds_frame_cap && lam >= (double)a.pc_theta * mi.pc_c;
-      // Both stores unconditionally, then bump one count: the store not
-      // taken lands at or past its queue's final count, where nothing reads.
-      // (The if/else form selected the base pointer per lane, and hipcc put
-      // the preconditioned base on lanes that only failed the lambda test.)
-      a.pqueues[q * a.qcap + moved] = item;
-      a.queues[q * a.qcap + keep] = item;
-      moved += pc ? 1 : 0;
-      keep += pc ? 0 : 1;
+      pc = sizeof(T) == 4 && a.reg == SL_H_CURVATURE && !a.plain_cg && mi.status == SL_ST_OK && mi.lds_frame != 0 &&
+           mi.ns * mi.ns <= a.lds_frame_cap && lam >= (double)a.pc_theta * mi.pc_c;
     }
+    const unsigned long long mp = __ballot(pc), mk = __ballot(item >= 0 && !pc);
+    const int jp = moved + lanes_below(mp), jk = keep + lanes_below(mk);
+    if (pc) PQ[jp] = item;
+    if (item >= 0 && !pc) Q[jk] = item;
+    moved += __popcll(mp);
+    keep += __popcll(mk);
+  }
+  if (lane == 0) {
     a.consts->qcount[q] = keep;
     a.consts->pqcount[q] = moved;
     a.consts->pqhead[q] = 0;
@@ -2662,6 +2827,7 @@ static Layout make_layout(const sl_problem* pb, int max_ns, int M, int NL, int n
   L.fy = take(sz * (size_t)M * L.slot_cap * L.n2);
   L.pmask = take(sizeof(unsigned long long) * (size_t)M * L.slot_cap);
   L.btd = take(sizeof(double) * 2 * (size_t)L.J);
+  L.pcpart = take(2 * sizeof(double) * (size_t)M * rhs_grid(L.I_max, M));
   L.b = take(sizeof(double) * (size_t)M * L.I_max);
   L.bh = take(sizeof(double) * (size_t)M * L.I_max);   // A^T bhat (Monte Carlo degrees of freedom)
   L.dofk = take(sizeof(double) * (size_t)M * NL);      // per-iterate estimate of the implicit solve
@@ -2948,7 +3114,7 @@ static int enqueue_prep(const SolveArgs& A, const LaunchCfg& c, hipStream_t st, 
   const int bands = (A.I_max + kFillBand - 1) / kFillBand;
   hipLaunchKernelGGL(k_prep_fill<T>, dim3(M * bands), dim3(64 * kFillW), c.fill_lds, st, A, bands);
   if (int e = check_launch("k_prep_fill")) return e;
-  hipLaunchKernelGGL(k_prep_rhs<T>, dim3(M), dim3(1024), 0, st, A);
+  hipLaunchKernelGGL(k_prep_rhs<T>, dim3((M + 7) / 8 * 8 * (unsigned)A.rhs_blocks), dim3(kRhsT), 0, st, A);
   return check_launch("k_prep_rhs");
 }
 
@@ -2980,7 +3146,7 @@ static int enqueue(const SolveArgs& A, const LamList& lams, const Layout& L, con
     hipLaunchKernelGGL(c.kim, dim3(L.n_wg), dim3(kNTof<T>), c.lds, st, A);
     if (int e = check_launch("k_implicit")) return e;
   } else if (c.kpc) {
-    hipLaunchKernelGGL(k_split<T>, dim3(1), dim3(64), 0, st, A);
+    hipLaunchKernelGGL(k_split<T>, dim3(1), dim3(512), 0, st, A);
     if (int e = check_launch("k_split")) return e;
     // The plain launch first on st, the preconditioned one on the side
     // stream: both are persistent, so its blocks take the CUs that the plain
@@ -3138,6 +3304,8 @@ static int prepare(const sl_problem* pb, const double* lens, const int32_t* ns, 
   A.dofk = (double*)(ws + L.dofk);
   A.pmask = (unsigned long long*)(ws + L.pmask);
   A.btd = (double*)(ws + L.btd);
+  A.pcpart = (double*)(ws + L.pcpart);
+  A.rhs_blocks = rhs_grid(L.I_max, n_members);
   A.lt_base = (int32_t*)(ws + L.lt_base);
   A.lt_cnt = (int32_t*)(ws + L.lt_cnt);
   A.mcbuf = ws + L.mcbuf;
