@@ -41,6 +41,8 @@ inline int check_launch(const char* what) {
   return SL_OK;
 }
 
+int device_cus();   // compute units of the current device (256 when unknown)
+
 constexpr int kWave = 64;
 
 // ---------------------------------------------------------------- reductions

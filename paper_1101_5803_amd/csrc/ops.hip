@@ -2,9 +2,11 @@
 //
 // These are the building blocks of the semilinear model (Rogers & Fiege 2011,
 // Sec. 2.1-2.2, Eq. 7) exposed one call per operator.  The batched solver in
-// solve.hip fuses the same operators into one persistent kernel; the kernels
-// here are straightforward one-thread-per-output launches over global memory,
-// except B/B^T which stage input tiles and the PSF in LDS.
+// solve.hip fuses the same operators into one persistent kernel.  Here one
+// launch covers up to kBatch members (blockIdx.y), whose grid sides and packed
+// offsets travel as a kernel argument: one launch per member left most of the
+// chip idle and cost 16 members of a 128 x 128 image 48 launches per operator
+// chain (trace 74, L 58, L^T 285 and H^T H 63 us in all).
 #include <algorithm>
 #include <cstdarg>
 #include <vector>
@@ -22,102 +24,214 @@ void set_error(const char* fmt, ...) {
   va_end(ap);
 }
 
+// Members of one launch: grid sides and starts in the packed source vectors.
+constexpr int kBatch = 64;
+struct Batch {
+  int ns[kBatch];
+  long off[kBatch];
+};
+
+// A subpixel's (u, v): 16 bytes in one access, 8-byte aligned as the caller's array.
+struct alignas(8) UV {
+  double u, v;
+};
+
 // ------------------------------------------------------------------ trace
-__global__ void k_trace(const double* __restrict__ genome, int nx, int ny, double pix, int nsub,
-                        int ns, double R, double* __restrict__ uv) {
+// Bound by the FP64 trace (atan, atanh, two square roots and the divisions of
+// one subpixel per thread); the lens's sines and cosines are taken once per
+// block.  16 members of a 128 x 128 image with 2 x 2 subpixels: 27 us (16
+// launches of 4.6 before).
+__global__ void __launch_bounds__(256) k_trace(const double* __restrict__ genome, int nx, int ny, double pix, int nsub,
+                                               Batch mb, double R, int rep, double* __restrict__ uv) {
+  __shared__ Lens Ls;
+  __shared__ int valid;
+  const int m = blockIdx.y, ns = mb.ns[m];
   const int n2 = nsub * nsub;
   const long total = (long)nx * ny * n2;
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= total) return;
-  double g[7];
-  for (int i = 0; i < 7; ++i) g[i] = genome[i];
-  double u = NAN, v = NAN;
-  if (lens_valid(g)) {
-    const Lens L = make_lens(g);
-    const int j = (int)(t / n2), k = (int)(t % n2);
-    const int r = j / nx, c = j % nx;
-    double x, y, bx, by;
-    subpixel_xy(r, c, k / nsub, k % nsub, nx, ny, pix, nsub, x, y);
-    lens_map(L, x, y, bx, by);
-    const double h = 2.0 * R / (ns - 1);
-    const double uu = (bx + R) / h, vv = (by + R) / h;
-    if (uu >= 0.0 && uu <= ns - 1 && vv >= 0.0 && vv <= ns - 1) {
-      u = uu;
-      v = vv;
-    }
+  if (threadIdx.x == 0) {
+    double g[7];
+    for (int i = 0; i < 7; ++i) g[i] = genome[7 * m + i];
+    valid = lens_valid(g);
+    Ls = make_lens(g);
   }
-  uv[2 * t] = u;
-  uv[2 * t + 1] = v;
+  __syncthreads();
+  const Lens L = Ls;
+  const double h = 2.0 * R / (ns - 1);
+  for (int i = 0; i < rep; ++i) {
+    const long t = ((long)blockIdx.x * rep + i) * 256 + threadIdx.x;
+    if (t >= total) return;
+    double u = NAN, v = NAN;
+    if (valid) {
+      const int j = (int)(t / n2), k = (int)(t % n2);
+      const int r = j / nx, c = j % nx;
+      double x, y, bx, by;
+      subpixel_xy(r, c, k / nsub, k % nsub, nx, ny, pix, nsub, x, y);
+      lens_map(L, x, y, bx, by);
+      const double uu = (bx + R) / h, vv = (by + R) / h;
+      if (uu >= 0.0 && uu <= ns - 1 && vv >= 0.0 && vv <= ns - 1) {
+        u = uu;
+        v = vv;
+      }
+    }
+    reinterpret_cast<UV*>(uv)[(long)m * total + t] = UV{u, v};
+  }
 }
 
 // ------------------------------------------------------------------ L, L^T
+// One thread per pixel; bound by the 16 n^2 bytes of positions it reads.
 template <typename T>
-__global__ void k_apply_L(const double* __restrict__ uv, int J, int nsub, int ns,
-                          const T* __restrict__ s, T* __restrict__ img) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) k_apply_L(const double* __restrict__ uv, int J, int nsub, Batch mb,
+                                                 const T* __restrict__ s_all, T* __restrict__ img) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x, m = blockIdx.y, ns = mb.ns[m];
   if (j >= J) return;
   const int n2 = nsub * nsub;
+  const T* s = s_all + mb.off[m];
+  const UV* p = reinterpret_cast<const UV*>(uv) + ((long)m * J + j) * n2;
   T acc = 0;
   for (int k = 0; k < n2; ++k) {
-    const long t = (long)j * n2 + k;
+    const UV q = p[k];
     int cell;
     double fx, fy;
-    if (!grid_cell(uv[2 * t], uv[2 * t + 1], ns, cell, fx, fy)) continue;
+    if (!grid_cell(q.u, q.v, ns, cell, fx, fy)) continue;
     const T tx = (T)fx, ty = (T)fy;
     acc += (1 - tx) * (1 - ty) * s[cell] + tx * (1 - ty) * s[cell + 1] + (1 - tx) * ty * s[cell + ns] +
            tx * ty * s[cell + ns + 1];
   }
-  img[j] = acc / (T)n2;
+  img[(long)m * J + j] = acc / (T)n2;
 }
 
-template <typename T>
-__global__ void k_apply_LT(const double* __restrict__ uv, int J, int nsub, int ns,
-                           const T* __restrict__ img, T* __restrict__ s) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= J) return;
-  const int n2 = nsub * nsub;
-  const T val = img[j] / (T)n2;
-  for (int k = 0; k < n2; ++k) {
-    const long t = (long)j * n2 + k;
-    int cell;
-    double fx, fy;
-    if (!grid_cell(uv[2 * t], uv[2 * t + 1], ns, cell, fx, fy)) continue;
-    const T tx = (T)fx, ty = (T)fy;
-    atomicAdd(&s[cell], (1 - tx) * (1 - ty) * val);
-    atomicAdd(&s[cell + 1], tx * (1 - ty) * val);
-    atomicAdd(&s[cell + ns], (1 - tx) * ty * val);
-    atomicAdd(&s[cell + ns + 1], tx * ty * val);
+// L^T of part of one member's pixels.  LDS = true: the terms are added in an
+// LDS copy of the member's source grid first and only its nonzero nodes go to
+// memory, where atomics across the XCDs run at about 36 G/s (every term there:
+// 285 us for 16 members of a 128 x 128 image, 4.2 M terms; LDS: 19 us).  The
+// lanes of a wave take pixels n/64 apart, so that a magnified region's
+// neighbouring pixels, which share nodes, do not meet in one LDS access.
+// LDS = false: grids whose source does not fit in LDS.
+constexpr int kLtT = 512;
+template <typename T, bool LDS>
+__global__ void __launch_bounds__(kLtT) k_apply_LT(const double* __restrict__ uv, int J, int nsub, Batch mb, int per,
+                                                   const T* __restrict__ img, T* __restrict__ s_all) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int m = blockIdx.y, ns = mb.ns[m], n2 = nsub * nsub, tid = threadIdx.x;
+  T* s = s_all + mb.off[m];
+  T* acc = LDS ? reinterpret_cast<T*>(smem) : s;
+  if (LDS) {
+    for (int i = tid; i < ns * ns; i += kLtT) acc[i] = (T)0;
+    __syncthreads();
+  }
+  const int lo = (int)blockIdx.x * per;   // per: a multiple of 64
+  for (int i = tid; i < per; i += kLtT) {
+    const int j = lo + (i & 63) * (per >> 6) + (i >> 6);
+    if (j >= J) continue;
+    const T val = img[(long)m * J + j] / (T)n2;
+    const UV* p = reinterpret_cast<const UV*>(uv) + ((long)m * J + j) * n2;
+    for (int k = 0; k < n2; ++k) {
+      const UV q = p[k];
+      int cell;
+      double fx, fy;
+      if (!grid_cell(q.u, q.v, ns, cell, fx, fy)) continue;
+      const T tx = (T)fx, ty = (T)fy;
+      atomicAdd(&acc[cell], (1 - tx) * (1 - ty) * val);
+      atomicAdd(&acc[cell + 1], tx * (1 - ty) * val);
+      atomicAdd(&acc[cell + ns], (1 - tx) * ty * val);
+      atomicAdd(&acc[cell + ns + 1], tx * ty * val);
+    }
+  }
+  if (LDS) {
+    __syncthreads();
+    for (int i = tid; i < ns * ns; i += kLtT) {
+      const T v = acc[i];
+      if (v != (T)0) atomicAdd(&s[i], v);   // (true for NaN)
+    }
   }
 }
 
 // Ordered L^T (fixed summation order).  A counting sort by node of the keys
 // key = 4 t + corner (t = subpixel index j n^2 + k, corner 0..3 for the
-// nodes cell, cell + 1, cell + ns, cell + ns + 1), then one thread per node
-// sums its terms in ascending key order, i.e. by pixel, subpixel, corner:
-// the order of a sequential scatter over the pixels.
-__global__ void k_lt_count(const double* __restrict__ uv, long nsubpix, int ns, int* __restrict__ cnt) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nsubpix) return;
-  int cell;
-  double fx, fy;
-  if (!grid_cell(uv[2 * t], uv[2 * t + 1], ns, cell, fx, fy)) return;
-  atomicAdd(&cnt[cell], 1);
-  atomicAdd(&cnt[cell + 1], 1);
-  atomicAdd(&cnt[cell + ns], 1);
-  atomicAdd(&cnt[cell + ns + 1], 1);
+// nodes cell, cell + 1, cell + ns, cell + ns + 1), then one wave per node puts
+// its keys in ascending order, i.e. by pixel, subpixel, corner (the order of a
+// sequential scatter over the pixels), and sums its terms in that order.
+
+// Members of one launch: as Batch, and the start of each one's workspace (ints).
+struct OrderedWs {
+  int *cnt, *ptr, *cur, *keys;
+};
+__host__ __device__ inline long ordered_ints(long I_max, long keys) { return 3 * I_max + 1 + keys; }
+__device__ __forceinline__ OrderedWs ordered_ws(int* ws, int m, long I_max, long keys) {
+  int* w = ws + m * ordered_ints(I_max, keys);
+  return {w, w + I_max, w + 2 * I_max + 1, w + 3 * I_max + 1};
 }
 
-// Exclusive scan of cnt[0..I) into ptr[0..I] and the fill cursors cur (one block).
-__global__ void __launch_bounds__(1024) k_lt_scan(const int* __restrict__ cnt, int I, int* __restrict__ ptr,
-                                                  int* __restrict__ cur) {
+// FILL = false: entries per node; true: the keys into their node's segment (in
+// any order).  With LDS, a block counts its subpixels per node there first and
+// takes each node's places with one atomic in memory.
+template <bool FILL, bool LDS>
+__global__ void __launch_bounds__(kLtT) k_lt_bin(const double* __restrict__ uv, long nsubpix, Batch mb, int per,
+                                                 int* __restrict__ ws, long I_max) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int m = blockIdx.y, ns = mb.ns[m], tid = threadIdx.x;
+  const OrderedWs w = ordered_ws(ws, m, I_max, 4 * nsubpix);
+  int* total = FILL ? w.cur : w.cnt;
+  int* h = LDS ? reinterpret_cast<int*>(smem) : total;
+  const UV* p = reinterpret_cast<const UV*>(uv) + m * nsubpix;
+  const long lo = (long)blockIdx.x * per, hi = lo + per < nsubpix ? lo + per : nsubpix;
+  if (LDS) {
+    for (int i = tid; i < ns * ns; i += kLtT) h[i] = 0;
+    __syncthreads();
+  }
+  if (LDS || !FILL) {
+    for (long t = lo + tid; t < hi; t += kLtT) {
+      const UV q = p[t];
+      int cell;
+      double fx, fy;
+      if (!grid_cell(q.u, q.v, ns, cell, fx, fy)) continue;
+      atomicAdd(&h[cell], 1);
+      atomicAdd(&h[cell + 1], 1);
+      atomicAdd(&h[cell + ns], 1);
+      atomicAdd(&h[cell + ns + 1], 1);
+    }
+  }
+  if (LDS) {
+    __syncthreads();
+    for (int i = tid; i < ns * ns; i += kLtT) {
+      const int c = h[i];
+      if (c) {
+        const int at = atomicAdd(&total[i], c);
+        if (FILL) h[i] = at;
+      }
+    }
+    __syncthreads();
+  }
+  if (FILL) {
+    for (long t = lo + tid; t < hi; t += kLtT) {
+      const UV q = p[t];
+      int cell;
+      double fx, fy;
+      if (!grid_cell(q.u, q.v, ns, cell, fx, fy)) continue;
+      const int nd[4] = {cell, cell + 1, cell + ns, cell + ns + 1};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) w.keys[atomicAdd(&h[nd[c]], 1)] = (int)(4 * t + c);
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256) k_lt_zero(Batch mb, int* __restrict__ ws, long I_max, long nkeys) {
+  const int i = blockIdx.x * 256 + threadIdx.x, ns = mb.ns[blockIdx.y];
+  if (i < ns * ns) ordered_ws(ws, blockIdx.y, I_max, nkeys).cnt[i] = 0;
+}
+
+// Exclusive scan of cnt[0..I) into ptr[0..I] and the fill cursors cur (one block per member).
+__global__ void __launch_bounds__(1024) k_lt_scan(Batch mb, int* __restrict__ ws, long I_max, long nkeys) {
   __shared__ int wsum[16];
   __shared__ int carry;
+  const OrderedWs w = ordered_ws(ws, blockIdx.x, I_max, nkeys);
+  const int I = mb.ns[blockIdx.x] * mb.ns[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   if (tid == 0) carry = 0;
   __syncthreads();
   for (int i0 = 0; i0 < I; i0 += 1024) {
     const int i = i0 + tid;
-    const int v = i < I ? cnt[i] : 0;
+    const int v = i < I ? w.cnt[i] : 0;
     int incl = v;
     for (int o = 1; o < 64; o <<= 1) {
       const int u = __shfl_up(incl, o, 64);
@@ -126,60 +240,87 @@ __global__ void __launch_bounds__(1024) k_lt_scan(const int* __restrict__ cnt, i
     if (lane == 63) wsum[wid] = incl;
     __syncthreads();
     int before = carry;
-    for (int w = 0; w < wid; ++w) before += wsum[w];
+    for (int x = 0; x < wid; ++x) before += wsum[x];
     if (i < I) {
-      ptr[i] = before + incl - v;
-      cur[i] = before + incl - v;
+      w.ptr[i] = before + incl - v;
+      w.cur[i] = before + incl - v;
     }
     __syncthreads();
     if (tid == 1023) carry = before + incl;
     __syncthreads();
   }
-  if (tid == 0) ptr[I] = carry;
+  if (tid == 0) w.ptr[I] = carry;
 }
 
-__global__ void k_lt_fill(const double* __restrict__ uv, long nsubpix, int ns, int* __restrict__ cur,
-                          int* __restrict__ keys) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nsubpix) return;
-  int cell;
-  double fx, fy;
-  if (!grid_cell(uv[2 * t], uv[2 * t + 1], ns, cell, fx, fy)) return;
-  const int nd[4] = {cell, cell + 1, cell + ns, cell + ns + 1};
-#pragma unroll
-  for (int q = 0; q < 4; ++q) keys[atomicAdd(&cur[nd[q]], 1)] = (int)(4 * t + q);
-}
-
+// One wave per node.  Its keys are distinct, so a key's rank is the count of
+// smaller ones: up to kSortCap of them at a time in LDS.  A longer row is taken
+// in ascending ranges of keys that hold no more than that.  (With one thread
+// per node sorting its segment in memory by insertion, and five launches per
+// member, a chain of operators with the ordered L^T took 81 ms for 16 members
+// of a 128 x 128 image; 0.36 ms so.)
+constexpr int kSortCap = 512, kGatherW = 4;
 template <typename T>
-__global__ void k_lt_gather(const double* __restrict__ uv, int n2, int ns, const int* __restrict__ ptr,
-                            int* __restrict__ keys, const T* __restrict__ img, T* __restrict__ s) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(64 * kGatherW) k_lt_gather(const double* __restrict__ uv, int n2, long nsubpix,
+                                                             Batch mb, int* __restrict__ ws, long I_max,
+                                                             const T* __restrict__ img, T* __restrict__ s) {
+  __shared__ int ks_[kGatherW][kSortCap];
+  __shared__ T tw_[kGatherW][kSortCap], tv_[kGatherW][kSortCap];
+  const int m = blockIdx.y, ns = mb.ns[m], lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kGatherW + wid));
   if (i >= ns * ns) return;
-  const int e0 = ptr[i], e1 = ptr[i + 1];
-  // insertion sort of this node's keys (the segment belongs to this thread)
-  for (int e = e0 + 1; e < e1; ++e) {
-    const int k = keys[e];
-    int f = e - 1;
-    while (f >= e0 && keys[f] > k) {
-      keys[f + 1] = keys[f];
-      --f;
-    }
-    keys[f + 1] = k;
-  }
+  int* ks = ks_[wid];
+  T *tw = tw_[wid], *tv = tv_[wid];
+  const OrderedWs w = ordered_ws(ws, m, I_max, 4 * nsubpix);
+  const int* keys = w.keys + w.ptr[i];
+  const int n = w.ptr[i + 1] - w.ptr[i];
+  const UV* p = reinterpret_cast<const UV*>(uv) + m * nsubpix;
+  img += (long)m * (nsubpix / n2);
+  const auto wave_sync = [] {   // this wave's LDS accesses complete in order; keep the compiler's order too
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
   T acc = 0;
-  for (int e = e0; e < e1; ++e) {
-    const int key = keys[e];
-    const long t = key >> 2;
-    const int q = key & 3;
-    int cell;
-    double fx, fy;
-    grid_cell(uv[2 * t], uv[2 * t + 1], ns, cell, fx, fy);
-    const T tx = (T)fx, ty = (T)fy;
-    const T val = img[t / n2] / (T)n2;
-    const T w = q == 0 ? (1 - tx) * (1 - ty) : q == 1 ? tx * (1 - ty) : q == 2 ? (1 - tx) * ty : tx * ty;
-    acc += w * val;
+  const long all = 4 * nsubpix;
+  long width = n <= kSortCap ? all : all / ((n + kSortCap - 1) / kSortCap);
+  for (long lo = 0; lo < all && n > 0;) {
+    if (width < kSortCap) width = kSortCap;   // never more than that many distinct keys
+    const long hi = lo + width < all ? lo + width : all;
+    int c = 0;
+    for (int e = 0; e < n && c <= kSortCap; e += 64) {
+      const int k = e + lane < n ? keys[e + lane] : -1;
+      const bool in = k >= lo && k < hi;
+      const unsigned long long bal = __ballot(in);
+      const int at = c + __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+      if (in && at < kSortCap) ks[at] = k;
+      c += __popcll(bal);
+    }
+    c = __builtin_amdgcn_readfirstlane(c);
+    wave_sync();
+    if (c > kSortCap) {
+      width >>= 1;
+      continue;
+    }
+    for (int e = lane; e < c; e += 64) {
+      const int key = ks[e];
+      int rank = 0;
+      for (int x = 0; x < c; ++x) rank += ks[x] < key;
+      const long t = key >> 2;
+      const UV q = p[t];
+      int cell;
+      double fx, fy;
+      grid_cell(q.u, q.v, ns, cell, fx, fy);
+      const T tx = (T)fx, ty = (T)fy;
+      const int corner = key & 3;
+      tw[rank] = (corner & 1 ? tx : 1 - tx) * (corner & 2 ? ty : 1 - ty);
+      tv[rank] = img[t / n2] / (T)n2;
+    }
+    wave_sync();
+    for (int x = 0; x < c; ++x) acc += tw[x] * tv[x];
+    wave_sync();
+    lo = hi;
   }
-  s[i] = acc;
+  if (lane == 0) s[mb.off[m] + i] = acc;
 }
 
 template <typename T>
@@ -189,12 +330,107 @@ __global__ void k_fill(T* __restrict__ p, long n, T v) {
 }
 
 // ------------------------------------------------------------------ B, B^T
-// One 16x16 output tile per block; the (16+K-1)^2 input tile and the PSF are
-// staged in LDS.  TRANSPOSE=false: convolution, true: correlation.
+// TRANSPOSE=false: convolution, out(r, c) = sum P[a][b] x(r-a+ck, c-b+ck);
+// true: correlation, x(r+a-ck, c+b-ck).  A block takes 32 rows x 8 N columns of
+// one image, its input tile with the halo and the PSF in LDS.  A thread forms N
+// consecutive outputs of one row from a register window, so that eight tap
+// values from LDS (the same for every lane) and N + 7 input values serve 8 N
+// products (two LDS reads per product in k_blur_small); a half-wave's lanes take consecutive rows,
+// which the odd pitch puts in distinct banks.  Every output adds its taps in
+// row-major order.  N = 8 reads less per product, N = 4 gives twice the waves:
+// the host takes 8 where that leaves at least two blocks per CU.
+constexpr int kBlurT = 256, kBlurR = 32;
+template <typename T, bool TRANSPOSE, int N>
+__global__ void __launch_bounds__(kBlurT) k_blur(int nx, int ny, const double* __restrict__ psf, int K,
+                                                 const T* __restrict__ in, T* __restrict__ out) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int W = 8 * N;   // columns of a block
+  const int ck = (K - 1) / 2, KP = (K + 7) & ~7;
+  const int tw = W + 2 * ck, pitch = tw | 1, th = kBlurR + 2 * ck;
+  T* P = reinterpret_cast<T*>(smem);   // [K][KP], the pad zero
+  T* tile = P + K * KP;
+  const int bx = (nx + W - 1) / W, by = (ny + kBlurR - 1) / kBlurR;
+  const int img = blockIdx.x / (bx * by), b = blockIdx.x % (bx * by);
+  const int R0 = (b / bx) * kBlurR, C0 = (b % bx) * W;
+  const T* src = in + (long)img * nx * ny;
+  const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
+  for (int a = ty; a < K; a += 8)
+    for (int i = tx; i < KP; i += 32) P[a * KP + i] = i < K ? (T)psf[a * K + i] : (T)0;
+  for (int j = tx; j < tw; j += 32) {
+    const int cc = C0 - ck + j;
+    const bool on = cc >= 0 && cc < nx;
+    for (int i0 = ty; i0 < th; i0 += 64) {   // eight rows' loads in flight
+      T v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int rr = R0 - ck + i0 + 8 * u;
+        v[u] = on && i0 + 8 * u < th && rr >= 0 && rr < ny ? src[(long)rr * nx + cc] : (T)0;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (i0 + 8 * u < th) tile[(i0 + 8 * u) * pitch + j] = v[u];
+    }
+  }
+  __syncthreads();
+  const int r = R0 + tx, c0 = C0 + N * ty;
+  if (r >= ny || c0 >= nx) return;
+  T acc[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = 0;
+  // taps b0..b0+7 of PSF row a and the window x[i] they meet: the input b0 + i
+  // after the thread's first (TRANSPOSE), or b0 + i before its last
+  auto load = [&](int a, int b0, T (&x)[N + 7], T (&t)[8]) {
+    const T* row = tile + (TRANSPOSE ? tx + a : tx + 2 * ck - a) * pitch + N * ty + (TRANSPOSE ? b0 : 2 * ck + N - 1 - b0);
+    // the last chunk also reads up to seven values past the row, inside the LDS array, that no tap uses
+#pragma unroll
+    for (int i = 0; i < N + 7; ++i) x[i] = TRANSPOSE ? row[i] : row[-i];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = P[a * KP + b0 + u];
+  };
+  T x[N + 7], t[8];
+  load(0, 0, x, t);
+  for (int a = 0, b0 = 0; a < K;) {
+    const int nb = K - b0;
+    int a2 = a, b2 = b0 + 8;
+    if (b2 >= K) {
+      b2 = 0;
+      ++a2;
+    }
+    T xn[N + 7], tn[8];
+    load(min(a2, K - 1), b2, xn, tn);   // the next chunk, ahead of this one's products
+    if (nb >= 8) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] += t[u] * x[TRANSPOSE ? u + i : u + N - 1 - i];
+    } else {
+#pragma unroll
+      for (int u = 0; u < 7; ++u)
+        if (u < nb) {   // uniform; a pad tap (zero) must not meet an infinite value
+#pragma unroll
+          for (int i = 0; i < N; ++i) acc[i] += t[u] * x[TRANSPOSE ? u + i : u + N - 1 - i];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < N + 7; ++i) x[i] = xn[i];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = tn[u];
+    a = a2;
+    b0 = b2;
+  }
+  T* o = out + (long)img * nx * ny + (long)r * nx + c0;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (c0 + i < nx) o[i] = acc[i];
+}
+
+// The same for few outputs: one output per thread in 16 x 16 tiles, 256 threads
+// a block, so that a single 200 x 200 image (K = 21) is 676 waves instead of
+// the 196 of k_blur<4>: 12 against 22 us.
 constexpr int kTile = 16;
 
 template <typename T, bool TRANSPOSE>
-__global__ void k_blur(int nx, int ny, const double* __restrict__ psf, int K,
+__global__ void k_blur_small(int nx, int ny, const double* __restrict__ psf, int K,
                        const T* __restrict__ in, T* __restrict__ out) {
   extern __shared__ __align__(16) unsigned char smem[];
   T* P = reinterpret_cast<T*>(smem);
@@ -240,9 +476,12 @@ __device__ __forceinline__ T d2y_at(const T* s, int ns, int r, int c) {
 }
 
 template <typename T>
-__global__ void k_apply_HtH(int reg, int ns, const T* __restrict__ s, T* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) k_apply_HtH(int reg, Batch mb, const T* __restrict__ s_all,
+                                                   T* __restrict__ out_all) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x, ns = mb.ns[blockIdx.y];
   if (i >= ns * ns) return;
+  const T* s = s_all + mb.off[blockIdx.y];
+  T* out = out_all + mb.off[blockIdx.y];
   if (reg == SL_H_IDENTITY) {
     out[i] = s[i];
     return;
@@ -273,19 +512,44 @@ static int check_ns(const int32_t* ns, int n_members) {
 
 static inline unsigned nblocks(long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
+// Calls launch(first member, batch, members of the batch, largest side) for
+// batches of at most kBatch members and 2^31 threads (threads(ns) of one member).
+template <typename Threads, typename Launch>
+static void for_batches(const int32_t* ns, int n_members, Threads threads, Launch launch) {
+  long off = 0;
+  for (int m0 = 0; m0 < n_members;) {
+    Batch mb;
+    int n = 0, big = 0;
+    long most = 0;
+    while (n < kBatch && m0 + n < n_members) {
+      const int side = ns[m0 + n];
+      const long t = std::max(most, (long)threads(side));
+      if (n > 0 && t * (n + 1) > (1L << 31)) break;
+      most = t;
+      big = std::max(big, side);
+      mb.ns[n] = side;
+      mb.off[n] = off;
+      off += (long)side * side;
+      ++n;
+    }
+    launch(m0, mb, n, big);
+    m0 += n;
+  }
+}
+
 template <typename T>
 static int apply_L_impl(const double* uv, int n_members, const sl_image_grid* img, const int32_t* ns,
                         const void* s, void* out, hipStream_t st) {
   const int J = img->nx * img->ny, n2 = img->nsub * img->nsub;
-  long soff = 0;
-  for (int m = 0; m < n_members; ++m) {
-    hipLaunchKernelGGL(k_apply_L<T>, dim3(nblocks(J, 256)), dim3(256), 0, st,
-                       uv + (long)m * J * n2 * 2, J, img->nsub, ns[m], (const T*)s + soff,
-                       (T*)out + (long)m * J);
-    soff += (long)ns[m] * ns[m];
-  }
+  for_batches(ns, n_members, [&](int) { return (long)J + 256; }, [&](int m0, const Batch& mb, int n, int) {
+    hipLaunchKernelGGL(k_apply_L<T>, dim3(nblocks(J, 256), n), dim3(256), 0, st, uv + (long)m0 * J * n2 * 2, J,
+                       img->nsub, mb, (const T*)s, (T*)out + (long)m0 * J);
+  });
   return check_launch("k_apply_L");
 }
+
+// Largest LDS copy of a source grid (two blocks of 512 threads still fit on a CU).
+constexpr size_t kLtLds = 78 * 1024;
 
 template <typename T>
 static int apply_LT_impl(const double* uv, int n_members, const sl_image_grid* img, const int32_t* ns,
@@ -294,24 +558,52 @@ static int apply_LT_impl(const double* uv, int n_members, const sl_image_grid* i
   long total = 0;
   for (int m = 0; m < n_members; ++m) total += (long)ns[m] * ns[m];
   hipLaunchKernelGGL(k_fill<T>, dim3(nblocks(total, 256)), dim3(256), 0, st, (T*)s, total, (T)0);
-  long soff = 0;
-  for (int m = 0; m < n_members; ++m) {
-    hipLaunchKernelGGL(k_apply_LT<T>, dim3(nblocks(J, 256)), dim3(256), 0, st,
-                       uv + (long)m * J * n2 * 2, J, img->nsub, ns[m], (const T*)in + (long)m * J,
-                       (T*)s + soff);
-    soff += (long)ns[m] * ns[m];
-  }
+  SL_HIP(hipFuncSetAttribute((const void*)k_apply_LT<T, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)kLtLds));
+  for_batches(ns, n_members, [&](int) { return (long)J + kLtT; }, [&](int m0, const Batch& mb, int n, int big) {
+    const size_t lds = sizeof(T) * (size_t)big * big;
+    // about 256 blocks over the batch, each with at least two pixels a thread: every block adds its nodes to
+    // memory, so more of them cost more atomics than they save
+    const int want = std::max(1, std::min((256 + n - 1) / n, (J + 2 * kLtT - 1) / (2 * kLtT)));
+    const int per = ((J + want - 1) / want + 63) / 64 * 64;
+    const dim3 grid(nblocks(J, per), n);
+    const double* uvm = uv + (long)m0 * J * n2 * 2;
+    if (lds <= kLtLds)
+      hipLaunchKernelGGL((k_apply_LT<T, true>), grid, dim3(kLtT), lds, st, uvm, J, img->nsub, mb, per,
+                         (const T*)in + (long)m0 * J, (T*)s);
+    else
+      hipLaunchKernelGGL((k_apply_LT<T, false>), grid, dim3(kLtT), 0, st, uvm, J, img->nsub, mb, per,
+                         (const T*)in + (long)m0 * J, (T*)s);
+  });
   return check_launch("k_apply_LT");
 }
 
-// Workspace of the ordered L^T: per member (I + 1) + I ints of row starts and
-// cursors and 4 J n^2 keys; members are processed one after another, so
-// the largest member sets the size.
-static size_t lt_ordered_ws(const sl_image_grid* img, const int32_t* ns, int n_members) {
+// Workspace of the ordered L^T: per member (I + 1) + 2 I ints of counts, row
+// starts and cursors and 4 J n^2 keys, all sized for the largest grid, for as
+// many members at a time as fit in 256 MB (at least one).
+static long ordered_group(const sl_image_grid* img, const int32_t* ns, int n_members, long* I_max) {
   long I = 0;
   for (int m = 0; m < n_members; ++m) I = std::max(I, (long)ns[m] * ns[m]);
-  const long keys = 4L * img->nx * img->ny * img->nsub * img->nsub;
-  return sizeof(int) * (size_t)(2 * I + 1 + I + keys);
+  *I_max = I;
+  const long bytes = 4 * ordered_ints(I, 4L * img->nx * img->ny * img->nsub * img->nsub);
+  return std::max(1L, std::min({(long)n_members, (long)kBatch, (256L << 20) / bytes}));
+}
+
+static size_t lt_ordered_ws(const sl_image_grid* img, const int32_t* ns, int n_members) {
+  long I = 0;
+  const long g = ordered_group(img, ns, n_members, &I);
+  return sizeof(int) * (size_t)(g * ordered_ints(I, 4L * img->nx * img->ny * img->nsub * img->nsub));
+}
+
+template <bool LDS>
+static void launch_bins(const double* uv, long nsp, const Batch& mb, int n, size_t lds, int* ws, long I_max,
+                        hipStream_t st) {
+  const int want = (int)std::max(1L, std::min((256L + n - 1) / n, (nsp + 8L * kLtT - 1) / (8L * kLtT)));
+  const int per = (int)((nsp + want - 1) / want);
+  const dim3 grid(nblocks(nsp, per), n);
+  hipLaunchKernelGGL((k_lt_bin<false, LDS>), grid, dim3(kLtT), lds, st, uv, nsp, mb, per, ws, I_max);
+  hipLaunchKernelGGL(k_lt_scan, dim3(n), dim3(1024), 0, st, mb, ws, I_max, 4 * nsp);
+  hipLaunchKernelGGL((k_lt_bin<true, LDS>), grid, dim3(kLtT), lds, st, uv, nsp, mb, per, ws, I_max);
 }
 
 template <typename T>
@@ -320,33 +612,61 @@ static int apply_LT_ordered_impl(const double* uv, int n_members, const sl_image
   const int J = img->nx * img->ny, n2 = img->nsub * img->nsub;
   const long nsp = (long)J * n2;
   long I_max = 0;
-  for (int m = 0; m < n_members; ++m) I_max = std::max(I_max, (long)ns[m] * ns[m]);
-  int* cnt = (int*)ws;
-  int* ptr = cnt + I_max;
-  int* cur = ptr + I_max + 1;
-  int* keys = cur + I_max;
-  long soff = 0;
-  for (int m = 0; m < n_members; ++m) {
-    const int I = ns[m] * ns[m];
-    const double* uvm = uv + (long)m * nsp * 2;
-    hipLaunchKernelGGL(k_fill<int>, dim3(nblocks(I, 256)), dim3(256), 0, st, cnt, (long)I, 0);
-    hipLaunchKernelGGL(k_lt_count, dim3(nblocks(nsp, 256)), dim3(256), 0, st, uvm, nsp, ns[m], cnt);
-    hipLaunchKernelGGL(k_lt_scan, dim3(1), dim3(1024), 0, st, cnt, I, ptr, cur);
-    hipLaunchKernelGGL(k_lt_fill, dim3(nblocks(nsp, 256)), dim3(256), 0, st, uvm, nsp, ns[m], cur, keys);
-    hipLaunchKernelGGL(k_lt_gather<T>, dim3(nblocks(I, 256)), dim3(256), 0, st, uvm, n2, ns[m], ptr, keys,
-                       (const T*)in + (long)m * J, (T*)s + soff);
+  const int group = (int)ordered_group(img, ns, n_members, &I_max);
+  SL_HIP(hipFuncSetAttribute((const void*)k_lt_bin<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)kLtLds));
+  SL_HIP(hipFuncSetAttribute((const void*)k_lt_bin<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)kLtLds));
+  long off = 0;
+  for (int m0 = 0; m0 < n_members; m0 += group) {
+    const int n = std::min(group, n_members - m0);
+    Batch mb;
+    int big = 0;
+    for (int i = 0; i < n; ++i) {
+      mb.ns[i] = ns[m0 + i];
+      mb.off[i] = off;
+      off += (long)ns[m0 + i] * ns[m0 + i];
+      big = std::max(big, ns[m0 + i]);
+    }
+    const double* uvm = uv + (long)m0 * nsp * 2;
+    int* w = (int*)ws;
+    hipLaunchKernelGGL(k_lt_zero, dim3(nblocks((long)big * big, 256), n), dim3(256), 0, st, mb, w, I_max, 4 * nsp);
+    const size_t lds = sizeof(int) * (size_t)big * big;
+    if (lds <= kLtLds) launch_bins<true>(uvm, nsp, mb, n, lds, w, I_max, st);
+    else launch_bins<false>(uvm, nsp, mb, n, 0, w, I_max, st);
+    hipLaunchKernelGGL(k_lt_gather<T>, dim3(nblocks((long)big * big, kGatherW), n), dim3(64 * kGatherW), 0, st, uvm,
+                       n2, nsp, mb, w, I_max, (const T*)in + (long)m0 * J, (T*)s);
     if (int e = check_launch("ordered L^T")) return e;
-    soff += I;
   }
   return SL_OK;
 }
 
+template <typename T, bool TR, int N>
+static int blur_launch(int nx, int ny, int n_images, const double* psf, int k, const void* in, void* out,
+                       hipStream_t st) {
+  const size_t lds =
+      sizeof(T) * ((size_t)k * ((k + 7) & ~7) + (size_t)(kBlurR + k - 1) * ((8 * N + k - 1) | 1) + 8);
+  if (lds > 64 * 1024)
+    SL_HIP(hipFuncSetAttribute((const void*)k_blur<T, TR, N>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  const unsigned blocks = nblocks(nx, 8 * N) * nblocks(ny, kBlurR) * (unsigned)n_images;
+  hipLaunchKernelGGL((k_blur<T, TR, N>), dim3(blocks), dim3(kBlurT), lds, st, nx, ny, psf, k, (const T*)in, (T*)out);
+  return check_launch("k_blur");
+}
+
+// The register-tiled forms need a block per CU to win (K = 15, 16 images of
+// 128 x 128, 256 blocks of 32 x 32: 15.0 against 14.7 us; K = 21, 64 images of
+// 200 x 200: 72 against 199 us; K = 63, 640 x 640, 400 blocks: 143 against 301 us).
 template <typename T, bool TR>
 static int blur_impl(int nx, int ny, int n_images, const double* psf, int k, const void* in, void* out,
                      hipStream_t st) {
+  const long rows = (long)nblocks(ny, kBlurR) * n_images;
+  if (nblocks(nx, 64) * rows >= 2L * device_cus()) return blur_launch<T, TR, 8>(nx, ny, n_images, psf, k, in, out, st);
+  if (nblocks(nx, 32) * rows > device_cus()) return blur_launch<T, TR, 4>(nx, ny, n_images, psf, k, in, out, st);
   const int tw = kTile + k - 1;
   const size_t lds = sizeof(T) * ((size_t)k * k + (size_t)tw * tw);
-  hipLaunchKernelGGL((k_blur<T, TR>), dim3(nblocks(nx, kTile), nblocks(ny, kTile), n_images),
+  if (lds > 64 * 1024)
+    SL_HIP(hipFuncSetAttribute((const void*)k_blur_small<T, TR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL((k_blur_small<T, TR>), dim3(nblocks(nx, kTile), nblocks(ny, kTile), n_images),
                      dim3(kTile, kTile), lds, st, nx, ny, psf, k, (const T*)in, (T*)out);
   return check_launch("k_blur");
 }
@@ -369,9 +689,12 @@ int sl_lens_trace(const double* lens, int n_members, const sl_image_grid* img, c
   SL_REQUIRE(std::isfinite(half_width) && half_width > 0.0, "half_width must be positive");
   hipStream_t st = (hipStream_t)stream;
   const long per = (long)img->nx * img->ny * img->nsub * img->nsub;
-  for (int m = 0; m < n_members; ++m)
-    hipLaunchKernelGGL(k_trace, dim3(nblocks(per, 256)), dim3(256), 0, st, lens + 7L * m, img->nx,
-                       img->ny, img->pix, img->nsub, ns[m], half_width, uv + 2 * per * m);
+  for_batches(ns, n_members, [&](int) { return per + 256; }, [&](int m0, const Batch& mb, int n, int) {
+    // four subpixels a thread once that leaves four blocks per CU: the block's lens constants are one thread's work
+    const int rep = nblocks(per, 1024) * (long)n >= 4L * device_cus() ? 4 : 1;
+    hipLaunchKernelGGL(k_trace, dim3(nblocks(per, 256 * rep), n), dim3(256), 0, st, lens + 7L * m0, img->nx, img->ny,
+                       img->pix, img->nsub, mb, half_width, rep, uv + 2 * per * m0);
+  });
   return check_launch("k_trace");
 }
 
@@ -448,19 +771,15 @@ int sl_apply_HtH(int dtype, int reg, int n_members, const int32_t* ns, const voi
   SL_REQUIRE(reg == SL_H_IDENTITY || reg == SL_H_CURVATURE, "unknown reg %d", reg);
   SL_REQUIRE(s && out && s != out, "bad device pointers");
   hipStream_t st = (hipStream_t)stream;
-  long off = 0;
-  for (int m = 0; m < n_members; ++m) {
-    const int I = ns[m] * ns[m];
+  SL_REQUIRE(dtype == SL_F32 || dtype == SL_F64, "unknown dtype %d", dtype);
+  for_batches(ns, n_members, [](int side) { return (long)side * side + 256; },
+              [&](int, const Batch& mb, int n, int big) {
+    const dim3 grid(nblocks((long)big * big, 256), n);
     if (dtype == SL_F32)
-      hipLaunchKernelGGL(k_apply_HtH<float>, dim3(nblocks(I, 256)), dim3(256), 0, st, reg, ns[m],
-                         (const float*)s + off, (float*)out + off);
-    else if (dtype == SL_F64)
-      hipLaunchKernelGGL(k_apply_HtH<double>, dim3(nblocks(I, 256)), dim3(256), 0, st, reg, ns[m],
-                         (const double*)s + off, (double*)out + off);
+      hipLaunchKernelGGL(k_apply_HtH<float>, grid, dim3(256), 0, st, reg, mb, (const float*)s, (float*)out);
     else
-      SL_REQUIRE(false, "unknown dtype %d", dtype);
-    off += I;
-  }
+      hipLaunchKernelGGL(k_apply_HtH<double>, grid, dim3(256), 0, st, reg, mb, (const double*)s, (double*)out);
+  });
   return check_launch("k_apply_HtH");
 }
 

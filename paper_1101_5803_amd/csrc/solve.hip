@@ -2784,7 +2784,7 @@ __global__ void k_put_int(int32_t* p, int v) {
   if (threadIdx.x == 0) *p = v;
 }
 
-static int device_cus() {
+int device_cus() {
   static int cus[64] = {0};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 256;
