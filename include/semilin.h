@@ -460,9 +460,9 @@ int sl_lcurve_corner(const double* reg, const double* chi2, int n, int32_t* k_st
 #define SL_MLP_MAX_BATCH (1 << 20)
 
 /*
- * Bytes of device workspace that a call with this batch size needs (BF16
- * and FP32 transposed copies of W1, activations, GELU derivatives and partial
- * sums of the training step).  Returns 0, with sl_last_error set, for a
+ * Bytes of device workspace that a call with this batch size needs (the
+ * activations, gradient signals and partial sums of the training step; the
+ * forward pass leaves it untouched).  Returns 0, with sl_last_error set, for a
  * batch outside [0, SL_MLP_MAX_BATCH].  The caller allocates it; calls that
  * share a workspace must not overlap in time.
  */
@@ -478,15 +478,11 @@ int sl_mlp_forward(const float* params, const float* x, int batch, float* y, voi
                    void* stream);
 
 /*
- * sl_mlp_forward without a workspace, for callers that cannot allocate
- * device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid allocation).  Same results as sl_mlp_forward, bit
- * for bit.  Its scratch (the BF16 and FP32 transposed copies of W1,
- * 384 KiB, whatever the batch) is a static device array of the library,
- * one per GPU, held until the process ends; the call allocates nothing.
- * Every call on a GPU shares that GPU's array, so calls that overlap in
- * time on one GPU (two streams, two threads) race and must be serialised by
- * the caller.  batch in [1, SL_MLP_MAX_BATCH], else SL_EINVAL.
+ * sl_mlp_forward without a workspace argument, for callers that cannot
+ * allocate device memory (code under HIP graph capture, tight serving loops,
+ * harnesses that forbid allocation).  Same results as sl_mlp_forward, bit for
+ * bit.  It uses no device memory but its arguments, so calls may overlap.
+ * batch in [1, SL_MLP_MAX_BATCH], else SL_EINVAL.
  */
 int sl_mlp_forward_noalloc(const float* params, const float* x, int batch, float* y, void* stream);
 

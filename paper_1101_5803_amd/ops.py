@@ -462,8 +462,7 @@ def mlp_forward(params: torch.Tensor, x: torch.Tensor, out: torch.Tensor | None 
 
 
 def mlp_forward_noalloc(params: torch.Tensor, x: torch.Tensor, out: torch.Tensor) -> torch.Tensor:
-    """mlp_forward through sl_mlp_forward_noalloc: the library allocates nothing (its scratch is a static
-    device array); the caller passes the output buffer.  Overlapping calls on one GPU race."""
+    """mlp_forward through sl_mlp_forward_noalloc: no workspace; the caller passes the output buffer."""
     _mlp_check(params, x)
     _dev_check(out)
     x = x.contiguous()
