@@ -36,6 +36,7 @@
 // rank-1 takes the direct K x K path with an image-space buffer in global memory.
 #include <algorithm>
 #include <array>
+#include <type_traits>
 #include <map>
 #include <climits>
 #include <cstdio>
@@ -1311,6 +1312,18 @@ __device__ __forceinline__ void banded_pass(T* __restrict__ F0, int pitch, int n
   }
 }
 
+// An out-of-line function sees its pointer arguments without their address
+// space, and every access through them becomes a flat one, which waits on both
+// the vector memory and the LDS counters; such functions take these pointer
+// types inside.  (A cast to one of them and back is folded away.)
+template <typename T>
+using Lds = __attribute__((address_space(3))) T*;
+template <typename T>
+using Global = __attribute__((address_space(1))) T*;
+__device__ __forceinline__ float uniform(float x) {
+  return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x)));
+}
+
 // ------------------------------------------------------------------ k_solve
 template <typename T>
 __device__ __forceinline__ T lds_node(const T* P, int ns, int r, int c) {
@@ -1342,11 +1355,11 @@ __device__ __forceinline__ double reg_node(const T* P, int ns, int r, int c, int
 
 // Block-wide FP64 sum with one barrier; consecutive calls must alternate `buf`
 // (0/1) and be separated by at least one other barrier before a buffer is reused.
-template <int NW = kWaves>
-__device__ __forceinline__ double block_sum1(double v, double* scratch, int buf) {
+template <int NW = kWaves, typename SP>
+__device__ __forceinline__ double block_sum1(double v, SP scratch, int buf) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   v = wave_sum(v);
-  double* sc = scratch + 16 * buf;
+  const SP sc = scratch + 16 * buf;
   if (lane == 0) sc[wid] = v;
   __syncthreads();
   double t = 0.0;
@@ -1365,92 +1378,176 @@ __device__ __forceinline__ double block_sum1(double v, double* scratch, int buf)
 // division.  With x an n x n array X, (S (x) S) x = S X S.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// C = S B (n x n, row-major B in LDS) on the FP32 matrix cores, stored
-// row-major (trans = 0) or transposed (trans = 1); with `scale`, element
-// (j, k) is divided by c + lambda (mu_j + mu_k).  S comes from the table
-// tab[m] = sqrt(2/(n+1)) sin(pi m / (n+1)), m = (j+1)(k+1) mod 2(n+1).
-// Each wave takes 16 x 48 output strips (three 16 x 16 tiles sharing the S
-// operand, three independent accumulator chains); the operands of the next
-// k-step are loaded before the current step's MFMAs.
+// C = S D (SA) or D S on the FP32 matrix cores, D and C n x n arrays in LDS
+// with rows `pitch` apart; with `scale`, element (j, k) is divided by c +
+// lambda (mu_j + mu_k).  S comes from the table tab[m] = sqrt(2/(n+1))
+// sin(pi m / (n+1)), m = (j+1)(k+1) mod 2(n+1).  A wave takes 16 x 16 output
+// tiles of one 16-row (SA) or 16-column block of S, NTL of them at a time
+// sharing its values; the next four inner steps' operands are read before the
+// current four's MFMAs, and only the last steps test the inner index: a step
+// is NTL MFMAs, NTL + 1 LDS reads and as many address updates.
 // v_mfma_f32_16x16x4f32: lane l supplies A[l%16][l/16] and B[l/16][l%16];
 // accumulator element r is C[4 (l/16) + r][l%16].
-__device__ __forceinline__ void sine_mul(const float* tab, const float* mu, int n, const float* B, float* C, int trans, int scale,
-                         float c, float lam) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int lc = lane & 15, lq = lane >> 4;
-  const int nt = (n + 15) >> 4, ng = (nt + 2) / 3, nn2 = 2 * (n + 1);
-  for (int strip = wv; strip < nt * ng; strip += kWaves) {
-    const int i0 = (strip / ng) << 4, jg = (strip % ng) * 48;
-    const int i = i0 + lc;
-    const int j0 = jg + lc, j1 = j0 + 16, j2 = j0 + 32;
-    f32x4 acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = acc0, acc2 = acc0;
-    int mi = ((i + 1) * (lq + 1)) % nn2;          // table index of S[i][t], t = t0 + lq
-    const int step = (4 * (i + 1)) % nn2;
-    float av = (i < n && lq < n) ? tab[mi] : 0.0f;
-    float b0 = (lq < n && j0 < n) ? B[lq * n + j0] : 0.0f;
-    float b1 = (lq < n && j1 < n) ? B[lq * n + j1] : 0.0f;
-    float b2 = (lq < n && j2 < n) ? B[lq * n + j2] : 0.0f;
-    for (int t0 = 0; t0 < n; t0 += 4) {
-      mi += step;
-      if (mi >= nn2) mi -= nn2;
-      const int tn = t0 + 4 + lq;
-      const float avn = (i < n && tn < n) ? tab[mi] : 0.0f;
-      const float b0n = (tn < n && j0 < n) ? B[tn * n + j0] : 0.0f;
-      const float b1n = (tn < n && j1 < n) ? B[tn * n + j1] : 0.0f;
-      const float b2n = (tn < n && j2 < n) ? B[tn * n + j2] : 0.0f;
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b0, acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b1, acc1, 0, 0, 0);
-      acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b2, acc2, 0, 0, 0);
-      av = avn;
-      b0 = b0n;
-      b1 = b1n;
-      b2 = b2n;
-    }
+template <bool SA, int NTL>
+__device__ __forceinline__ void sine_tiles(Lds<const float> tab, Lds<const float> mu, int n, int pitch,
+                                           Lds<const float> D, Lds<float> C, int blk, int o0, int ostep, bool scale, float c, float lam) {
+  constexpr int G = 4;
+  const int lane = threadIdx.x & 63, lc = lane & 15, lq = lane >> 4;
+  const unsigned nn2 = 2 * (n + 1);
+  const int si = 16 * blk + lc;                       // this lane's row (column) of S; past n it feeds no stored result
+  const unsigned step = (4u * (si + 1)) % nn2;
+  unsigned mi = ((si + 1u) * (lq + 1)) % nn2;
+  // data operand of tile q, inner index t = 4 u + lq: SA: D[t][j], else D[i][t]; a lane past the edge repeats the last
+  const int dstep = SA ? 4 * pitch : 4;
+  Lds<const float> dp[NTL];
 #pragma unroll
-    for (int g = 0; g < 3; ++g) {
-      const f32x4 acc = g == 0 ? acc0 : (g == 1 ? acc1 : acc2);
+  for (int q = 0; q < NTL; ++q) {
+    const int f = min(16 * (o0 + q * ostep) + lc, n - 1);
+    dp[q] = D + (SA ? lq * pitch + f : f * pitch + lq);
+  }
+  f32x4 acc[NTL];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = i0 + 4 * lq + r, col = jg + 16 * g + lc;
-        if (row < n && col < n) {
-          float v = acc[r];
-          if (scale) v = v / (c + lam * (mu[row] + mu[col]));
-          if (trans)
-            C[col * n + row] = v;
-          else
-            C[row * n + col] = v;
+  for (int q = 0; q < NTL; ++q) acc[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  float sv[G], dv[NTL][G];
+  int t0 = 0;   // inner index of the next read
+  auto load = [&](float (&s)[G], float (&d)[NTL][G]) {
+    if (t0 + 4 * G <= n) {   // uniform
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        s[g] = tab[mi];
+        mi += step;
+        mi = min(mi, mi - nn2);   // mod nn2
+#pragma unroll
+        for (int q = 0; q < NTL; ++q) {
+          d[q][g] = *dp[q];
+          dp[q] += dstep;
         }
+      }
+    } else {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const bool in = t0 + 4 * g + lq < n;   // inner indices past n enter as zeros
+        s[g] = in ? tab[mi] : 0.0f;
+        mi += step;
+        mi = min(mi, mi - nn2);
+#pragma unroll
+        for (int q = 0; q < NTL; ++q) {
+          d[q][g] = in ? *dp[q] : 0.0f;
+          dp[q] += dstep;
+        }
+      }
+    }
+    t0 += 4 * G;
+  };
+  load(sv, dv);
+  for (int k = 0; k < n; k += 4 * G) {
+    float sn[G], dn[NTL][G];
+    load(sn, dn);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int q = 0; q < NTL; ++q)
+        acc[q] = SA ? __builtin_amdgcn_mfma_f32_16x16x4f32(sv[g], dv[q][g], acc[q], 0, 0, 0)
+                    : __builtin_amdgcn_mfma_f32_16x16x4f32(dv[q][g], sv[g], acc[q], 0, 0, 0);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      sv[g] = sn[g];
+#pragma unroll
+      for (int q = 0; q < NTL; ++q) dv[q][g] = dn[q][g];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NTL; ++q) {
+    const int o = o0 + q * ostep;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * (SA ? blk : o) + 4 * lq + r, col = 16 * (SA ? o : blk) + lc;
+      if (row < n && col < n) {
+        float v = acc[q][r];
+        if (scale) v = v / (c + lam * (mu[row] + mu[col]));
+        C[row * pitch + col] = v;
       }
     }
   }
 }
 
+// The n x n product by the block's 16 waves: nt = ceil(n/16) blocks of S, each
+// taken by floor(16/nt) waves that share its nt tiles out (n <= 128: at most
+// four tiles a wave).
+template <bool SA>
+__device__ __forceinline__ void sine_mul(Lds<const float> tab, Lds<const float> mu, int n, int pitch, Lds<const float> D,
+                                         Lds<float> C, bool scale, float c, float lam) {
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nt = (n + 15) >> 4, per = 16 / nt, blk = wv / per, o0 = wv % per;
+  if (blk >= nt || o0 >= nt) return;
+  switch ((nt - o0 + per - 1) / per) {
+    case 1: sine_tiles<SA, 1>(tab, mu, n, pitch, D, C, blk, o0, per, scale, c, lam); break;
+    case 2: sine_tiles<SA, 2>(tab, mu, n, pitch, D, C, blk, o0, per, scale, c, lam); break;
+    case 3: sine_tiles<SA, 3>(tab, mu, n, pitch, D, C, blk, o0, per, scale, c, lam); break;
+    default: sine_tiles<SA, 4>(tab, mu, n, pitch, D, C, blk, o0, per, scale, c, lam); break;
+  }
+}
+
 // One preconditioned-CG direction update, all threads of the block:
-// z = M^-1 r (r from r_g, the n x n scratch T in the frame, X = the Q region),
+// z = M^-1 r (r from r_g, the scratch in the Q region and the frame F),
 // rz_new = <r, z>, p = z + beta p with beta = rz_new / rz_old (0 when
-// `restart`), and the scratch zeroed again.  Returns rz_new.  Kept out of
-// line so that its registers do not add to the CG loop's pressure.
-__device__ __attribute__((noinline)) double pc_apply(float* P, float* X, float* Tb, const float* tab,
-                                                     const float* mu, int n, const float* r_g, float c, float lam,
-                                                     double rz_old, int restart, double* red) {
+// `restart`), and the frame zeroed again.  Returns rz_new.  Kept out of line so
+// that its registers do not add to the CG loop's pressure.
+//
+// Bound by the matrix cores' FP32 rate (four products of n^3) and the LDS reads
+// that feed them.  With S on either side of the data no product needs a
+// transposed copy.  Rows n apart put the sixteen rows of an operand in 1, 2 or
+// 4 of the 32 banks when 8 divides n; there they are n + 2 apart where both
+// arrays have the room (qcap, fcap floats).  (58k cycles at n = 64 and 168k at n
+// = 100 when 16 x 48 strips left half the waves or two thirds of their tiles
+// empty, the transposed stores met in one bank and every access was a flat
+// one; 38k and 117k so.)
+__device__ __attribute__((noinline)) double pc_apply(float* P_, float* Q_, float* F_, int qcap_, int fcap_,
+                                                     const float* tab_, const float* mu_, int n_, const float* r_,
+                                                     float c_, float lam_, double rz_old, int restart,
+                                                     double* red_) {
+  const Lds<float> P = (Lds<float>)P_, Q = (Lds<float>)Q_, F = (Lds<float>)F_;
+  const Lds<const float> tab = (Lds<const float>)tab_, mu = (Lds<const float>)mu_;
+  const Global<const float> r_g = (Global<const float>)r_;
+  const Lds<double> red = (Lds<double>)red_;
+  const int n = __builtin_amdgcn_readfirstlane(n_), qcap = __builtin_amdgcn_readfirstlane(qcap_),
+            fcap = __builtin_amdgcn_readfirstlane(fcap_);
+  const float c = uniform(c_), lam = uniform(lam_);
   const int tid = threadIdx.x, nn = n * n;
-  for (int i = tid; i < nn; i += kNT) X[(i % n) * n + i / n] = r_g[i];   // X^T
+  int pitch = n & 7 ? n : n + 2;
+  Lds<float> X = Q;
+  const Lds<float> Tb = F;
+  int used = n * pitch;   // floats of the frame
+  if (pitch != n) {
+    if (used > qcap && 2 * used <= fcap) {
+      X = F + used;
+      used *= 2;
+    } else if (used > qcap || used > fcap) {
+      pitch = n;
+      used = nn;
+    }
+  }
+  const float inv_n = 1.0f / n;
+  const int pad = pitch - n;
+  // node i at i + row(i) pad; (i + 1/2) / n in FP32 is exact enough for i < 2^14
+  auto at = [&](int i) { return i + (int)((i + 0.5f) * inv_n) * pad; };
+  for (int i = tid; i < nn; i += kNT) X[at(i)] = r_g[i];
   __syncthreads();
-  // every product is S B; the stored transposes make the next B row-major
-  sine_mul(tab, mu, n, X, Tb, 1, 0, 0.0f, 0.0f);     // (S X^T)^T = X S
+  sine_mul<false>(tab, mu, n, pitch, X, Tb, false, 0.0f, 0.0f);   // X S
   __syncthreads();
-  sine_mul(tab, mu, n, Tb, X, 0, 1, c, lam);         // Y = S X S over the eigenvalues of M
+  sine_mul<true>(tab, mu, n, pitch, Tb, X, true, c, lam);         // Y = S X S over the eigenvalues of M
   __syncthreads();
-  sine_mul(tab, mu, n, X, Tb, 1, 0, 0.0f, 0.0f);     // (S Y)^T
+  sine_mul<true>(tab, mu, n, pitch, X, Tb, false, 0.0f, 0.0f);    // S Y
   __syncthreads();
-  sine_mul(tab, mu, n, Tb, X, 1, 0, 0.0f, 0.0f);     // (S (S Y)^T)^T = S Y S = z, node order
+  sine_mul<false>(tab, mu, n, pitch, Tb, X, false, 0.0f, 0.0f);   // z = S Y S
   __syncthreads();
   double rzn = 0.0;
-  for (int i = tid; i < nn; i += kNT) rzn += (double)r_g[i] * (double)X[i];
+  for (int i = tid; i < nn; i += kNT) rzn += (double)r_g[i] * (double)X[at(i)];
   rzn = block_sum1(rzn, red, 2);
   const float beta = restart ? 0.0f : (float)(rzn / rz_old);
-  for (int i = tid; i < nn; i += kNT) P[i] = X[i] + beta * P[i];
-  for (int e = tid; e < nn; e += kNT) Tb[e] = 0.0f;   // the scratch lies in the frame
+  for (int i = tid; i < nn; i += kNT) P[i] = X[at(i)] + beta * P[i];
+  if (X != Q) __syncthreads();   // z lies in the frame too
+  for (int e = tid; e < used; e += kNT) F[e] = 0.0f;
   return rzn;
 }
 
@@ -1609,10 +1706,9 @@ __device__ __forceinline__ void gather_L(const OpView<T>& o, const T* __restrict
 // z = B y over the dilated box (Dh x Dw, row-major) from the frame, whose
 // entries off the mapped pixels are zero.  Returns this thread's part of
 // ||z||^2.
-template <typename T, int CKT, int NT>
-__device__ __forceinline__ double blur_box(const OpView<T>& o, T* __restrict__ Z) {
-  const T* const F0 = o.F0;
-  const T* taps = o.taps;
+// F0, taps and Z are o.F0, o.taps and the output (of any pointer type).
+template <typename T, int CKT, int NT, typename FP, typename TP, typename ZP>
+__device__ __forceinline__ double blur_box(const OpView<T>& o, FP F0, TP taps, ZP __restrict__ Z) {
   const TapIdx ti(o.K);
   const int K = o.K, ck = o.ck, r0 = o.r0, c0 = o.c0, h = o.h, w = o.w, pitch = o.pitch;
   const int Dr0 = o.Dr0, Dc0 = o.Dc0, Dh = o.Dh, Dw = o.Dw;
@@ -1623,10 +1719,10 @@ __device__ __forceinline__ double blur_box(const OpView<T>& o, T* __restrict__ Z
     if (ck <= CKT) {
       // every tap of an output in the dilated region lands in the bounding
       // box or its zero halo (2 CKT >= 2 ck on each side): no bounds tests
-      const T* yrow = F0 + (rr_ + ck - r0) * pitch + (cc_ + ck - c0);
-      const T* tp = taps + ti.psf;
+      const auto yrow = F0 + (rr_ + ck - r0) * pitch + (cc_ + ck - c0);
+      const auto tp = taps + ti.psf;
       for (int aa = 0; aa < K; ++aa) {
-        const T* y = yrow - aa * pitch;
+        const auto y = yrow - aa * pitch;
         for (int bb = 0; bb < K; ++bb) acc += tp[aa * K + bb] * y[-bb];
       }
     } else {   // PSFs wider than the widest compiled window: the halo is narrower than ck
@@ -1793,13 +1889,13 @@ __device__ __forceinline__ bool tiled_ok(const OpView<T>& o) {
 // z = B y over the dilated box into Z (Dh x Dw, row-major), y in the frame
 // with its zero halo.  Returns this thread's part of ||z||^2 (each output
 // counted once).
-template <typename T, int CKT, int NT>
-__device__ __forceinline__ double blur_box_t8(const OpView<T>& o, T* __restrict__ Z) {
+template <typename T, int CKT, int NT, typename FP, typename TP, typename ZP>
+__device__ __forceinline__ double blur_box_t8(const OpView<T>& o, FP F0, TP taps, ZP __restrict__ Z) {
   constexpr int KT = 2 * CKT + 1, NV = KT + 7;
   const int Dh = o.Dh, Dw = o.Dw, pitch = o.pitch;
-  const T* tp = o.taps + TapIdx(KT).psf;
+  const auto tp = taps + TapIdx(KT).psf;
   // output (r, c) of the dilated box reads base[(r - aa) * pitch + (c - bb)]
-  const T* base = o.F0 + (o.Dr0 + CKT - o.r0) * pitch + (o.Dc0 + CKT - o.c0);
+  const auto base = F0 + (o.Dr0 + CKT - o.r0) * pitch + (o.Dc0 + CKT - o.c0);
   const int nct = (Dw + 7) >> 3;
   double zz = 0.0;
   for (int t = threadIdx.x; t < Dh * nct; t += NT) {
@@ -1810,11 +1906,11 @@ __device__ __forceinline__ double blur_box_t8(const OpView<T>& o, T* __restrict_
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0;
     for (int aa = 0; aa < KT; ++aa) {
-      const T* row = base + (r - aa) * pitch + c - (KT - 1);
+      const auto row = base + (r - aa) * pitch + c - (KT - 1);
       T v[NV];
 #pragma unroll
       for (int j = 0; j < NV; ++j) v[j] = row[j];
-      const T* ta = tp + aa * KT;
+      const auto ta = tp + aa * KT;
 #pragma unroll
       for (int bb = 0; bb < KT; ++bb) {
         const T tv = ta[bb];
@@ -1822,7 +1918,7 @@ __device__ __forceinline__ double blur_box_t8(const OpView<T>& o, T* __restrict_
         for (int i = 0; i < 8; ++i) acc[i] += tv * v[i - bb + KT - 1];
       }
     }
-    T* zo = Z + r * Dw + c;
+    const auto zo = Z + r * Dw + c;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       zo[i] = acc[i];
@@ -1904,8 +2000,35 @@ __device__ __forceinline__ void adjoint_blur(const OpView<T>& o, const T* __rest
 // z = B y over the dilated box into Z; returns this thread's part of ||z||^2.
 template <typename T, int CKT, int NT>
 __device__ __forceinline__ double forward_blur(const OpView<T>& o, T* __restrict__ Z) {
-  if (tiled_ok<T, CKT>(o)) return blur_box_t8<T, CKT, NT>(o, Z);
-  return blur_box<T, CKT, NT>(o, Z);
+  if (tiled_ok<T, CKT>(o)) return blur_box_t8<T, CKT, NT>(o, (const T*)o.F0, o.taps, Z);
+  return blur_box<T, CKT, NT>(o, (const T*)o.F0, o.taps, Z);
+}
+
+// The same, out of line, for the end of an item: its registers stay out of the
+// CG loop's budget.  (A loop over the taps of one output at a time, each with
+// its own bounds tests, took 420k cycles per c3 item, 6.5 CG iterations; the
+// tiled form and the rest of the tail 65k.)
+template <typename T, int CKT, int NT, bool LDSF>
+__device__ __attribute__((noinline)) void model_image(const T* F0_, const T* taps_, T* Z_, int K, int r0, int c0, int h,
+                                                      int w, int pitch, int Dr0, int Dc0, int Dh, int Dw) {
+  using FP = std::conditional_t<LDSF, Lds<const T>, Global<const T>>;
+  const FP F0 = (FP)F0_;
+  const Global<const T> taps = (Global<const T>)taps_;
+  const Global<T> Z = (Global<T>)Z_;
+  OpView<T> o{};
+  o.K = __builtin_amdgcn_readfirstlane(K);
+  o.ck = (o.K - 1) / 2;
+  o.r0 = __builtin_amdgcn_readfirstlane(r0);
+  o.c0 = __builtin_amdgcn_readfirstlane(c0);
+  o.h = __builtin_amdgcn_readfirstlane(h);
+  o.w = __builtin_amdgcn_readfirstlane(w);
+  o.pitch = __builtin_amdgcn_readfirstlane(pitch);
+  o.Dr0 = __builtin_amdgcn_readfirstlane(Dr0);
+  o.Dc0 = __builtin_amdgcn_readfirstlane(Dc0);
+  o.Dh = __builtin_amdgcn_readfirstlane(Dh);
+  o.Dw = __builtin_amdgcn_readfirstlane(Dw);
+  if (tiled_ok<T, CKT>(o)) (void)blur_box_t8<T, CKT, NT>(o, F0, taps, Z);
+  else (void)blur_box<T, CKT, NT>(o, F0, taps, Z);
 }
 
 // Zero the frame rows that an operator application wrote, after every
@@ -2027,7 +2150,8 @@ __device__ __forceinline__ void run_item(const SolveArgs& a, const MemberInfo& m
       const double sn = sin(pi * (e + 1) / (2.0 * (ns + 1)));
       mu[e] = (float)(16.0 * sn * sn * sn * sn);
     }
-    rz = pc_apply(reinterpret_cast<float*>(P), reinterpret_cast<float*>(Q), reinterpret_cast<float*>(F), tab, mu, ns,
+    rz = pc_apply(reinterpret_cast<float*>(P), reinterpret_cast<float*>(Q), reinterpret_cast<float*>(F),
+                  (a.red_off - a.q_off) / 4, a.lds_frame_cap, tab, mu, ns,
                   reinterpret_cast<const float*>(r_g), mi.pc_c, (float)a.lamv[kl], 0.0, 1, red);
     __syncthreads();
   }
@@ -2078,8 +2202,8 @@ __device__ __forceinline__ void run_item(const SolveArgs& a, const MemberInfo& m
     rn = block_sum1<NT / kWave>(rn, red, 1);
     if constexpr (PC && sizeof(T) == 4) {
       float* tab = reinterpret_cast<float*>(smem + a.pc_off);
-      rz = pc_apply(reinterpret_cast<float*>(P), reinterpret_cast<float*>(Q), reinterpret_cast<float*>(F), tab,
-                    tab + 2 * (ns + 1), ns, reinterpret_cast<const float*>(r_g), mi.pc_c, (float)a.lamv[kl], rz, 0,
+      rz = pc_apply(reinterpret_cast<float*>(P), reinterpret_cast<float*>(Q), reinterpret_cast<float*>(F),
+                    (a.red_off - a.q_off) / 4, a.lds_frame_cap, tab, tab + 2 * (ns + 1), ns, reinterpret_cast<const float*>(r_g), mi.pc_c, (float)a.lamv[kl], rz, 0,
                     red);
     } else {
       const T beta = (T)(rn / rr);
@@ -2122,21 +2246,12 @@ __device__ __forceinline__ void run_item(const SolveArgs& a, const MemberInfo& m
   double regacc = 0.0;
   for (int i = tid; i < I; i += NT) regacc += reg_node(P, ns, i / ns, i % ns, a.reg);
   __syncthreads();
+  model_image<T, CKT, NT, LDSF>(F0, taps, Z, K, r0, c0, h, w, pitch, Dr0, Dc0, Dh, Dw);
+  __syncthreads();
   double cacc = 0.0;
   for (int e = tid; e < Dh * Dw; e += NT) {
-    const int rr_ = Dr0 + e / Dw, cc_ = Dc0 + e % Dw;
-    T z = 0;
-    for (int aa = 0; aa < K; ++aa) {
-      const int yr = rr_ - aa + ck - r0;
-      if (yr < 0 || yr >= h) continue;
-      for (int bb = 0; bb < K; ++bb) {
-        const int yc = cc_ - bb + ck - c0;
-        if (yc < 0 || yc >= w) continue;
-        z += taps[ti.psf + aa * K + bb] * F0[yr * pitch + yc];
-      }
-    }
-    const double zd = (double)z;
-    cacc += zd * zd - 2.0 * zd * a.d[rr_ * nx + cc_];
+    const double zd = (double)Z[e];
+    cacc += zd * zd - 2.0 * zd * a.d[(Dr0 + e / Dw) * nx + Dc0 + e % Dw];
   }
   block_sum2(cacc, regacc, red);
   if (tid == 0) {
