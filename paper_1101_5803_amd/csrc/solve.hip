@@ -62,6 +62,7 @@ constexpr int kUpd = 4;        // CG vector-update chunk (nodes per thread)
 constexpr int kPcThetaPct = 15;   // default theta = 0.15 (sl_tuning.pc_theta_pct = 0)
 constexpr int kFillW = 16;     // waves that fill the transposed operator in parallel in k_prep_fill
 constexpr int kHeavy = 4;      // default count of smallest lambdas of each member queued ahead of the rest
+constexpr int kCoefCap = 1024; // CG iterations per item whose step lengths are kept for the Monte Carlo pass
 constexpr int kMaxCK = 31;
 
 struct alignas(16) MemberInfo {
@@ -89,7 +90,7 @@ struct alignas(16) Consts {
 };
 
 struct Layout {
-  size_t consts, lam, taps_d, taps_f, minfo, queues, pqueues, pix, cell, fx, fy, pmask, btd, pcpart, b, bh, dofk, s_all, gframe, gz, rbuf, mcbuf, ibuf,
+  size_t consts, lam, taps_d, taps_f, minfo, queues, pqueues, pix, cell, fx, fy, pmask, btd, pcpart, b, bh, dofk, coef, s_all, gframe, gz, rbuf, mcbuf, ibuf,
       lt_ptr, lt_perm, lt_base, lt_cnt,
       lt_ent,
       total;
@@ -184,6 +185,7 @@ struct SolveArgs {
   double* btd;       // [2][J] B^T d and B^T bhat (FP64)
   double* pcpart;    // [member][rhs_blocks][2] parts of the preconditioner scale's two sums
   int rhs_blocks;    // blocks of k_prep_rhs per member
+  double2* coef;     // [member][n_lambda][kCoefCap] FP64 CG's step lengths (alpha, beta), for k_mcdof
   int32_t* lt_base;  // [member][I_max] index of each node's first entry of the transposed operator
   int32_t* lt_cnt;   // [member][I_max] entries of each node
   void* mcbuf;       // [n_wg][5][I_max] r, xhat, rhat, phat, saved p of the pass
@@ -2207,6 +2209,10 @@ __device__ __forceinline__ void run_item(const SolveArgs& a, const MemberInfo& m
                     red);
     } else {
       const T beta = (T)(rn / rr);
+      if constexpr (sizeof(T) == 8) {
+        if (a.mcn && it < kCoefCap)   // the same value from every thread
+          a.coef[out_idx * kCoefCap + it] = make_double2((double)alT, (double)beta);
+      }
       if (I <= kUpd * NT) {
 #pragma unroll
         for (int k = 0; k < kUpd; ++k) {
@@ -2402,6 +2408,33 @@ __device__ __forceinline__ void run_mc_item(const SolveArgs& a, const MemberInfo
       const T beta = (T)(rn / rr);
       for (int i = tid; i < I; i += NT) P[i] = rh_g[i] + beta * P[i];
       rr = rn;
+      __syncthreads();
+    }
+  } else if (__builtin_amdgcn_readfirstlane((int)(a.iters[(long)m * a.n_lambda + kl] <= kCoefCap))) {
+    // The data system's step lengths as k_solve left them: only the second
+    // system is advanced (solving the data system again in lockstep, as below,
+    // took twice the operator applications: 170 ms for 64 c3 members, 83 ms so).
+    const int n_it = __builtin_amdgcn_readfirstlane(a.iters[(long)m * a.n_lambda + kl]);
+    const double2* cf = a.coef + ((long)m * a.n_lambda + kl) * kCoefCap;
+    for (int i = tid; i < I; i += NT) {
+      const T nv = (T)bhm[i];
+      P[i] = nv;
+      rh_g[i] = nv;
+      xh_g[i] = (T)0;
+    }
+    __syncthreads();
+    for (int it = 0; it < n_it; ++it) {
+      (void)apply_normal<T, CKT, NT, DIR>(ov, P, Q);
+      __syncthreads();   // every gather has read P and the frame
+      clear_rows<T, CKT, NT, DIR>(ov);
+      const T alT = (T)cf[it].x, beta = (T)cf[it].y;
+      for (int i = tid; i < I; i += NT) {
+        const T ph = P[i];
+        xh_g[i] += alT * ph;
+        const T rk = rh_g[i] - alT * Q[i];
+        rh_g[i] = rk;
+        P[i] = rk + beta * ph;
+      }
       __syncthreads();
     }
   } else {
@@ -2945,6 +2978,7 @@ static Layout make_layout(const sl_problem* pb, int max_ns, int M, int NL, int n
   L.pcpart = take(2 * sizeof(double) * (size_t)M * rhs_grid(L.I_max, M));
   L.b = take(sizeof(double) * (size_t)M * L.I_max);
   L.bh = take(sizeof(double) * (size_t)M * L.I_max);   // A^T bhat (Monte Carlo degrees of freedom)
+  if (pb->dtype == SL_F64) L.coef = take(sizeof(double2) * (size_t)M * NL * kCoefCap);
   L.dofk = take(sizeof(double) * (size_t)M * NL);      // per-iterate estimate of the implicit solve
   L.s_all = take(sz * (size_t)M * NL * L.I_max);
   L.gframe_elems = (pb->img.ny + 4 * 16 + kSegR) * ((pb->img.nx + 4 * 16) | 1);   // widest window's halo
@@ -3417,6 +3451,7 @@ static int prepare(const sl_problem* pb, const double* lens, const int32_t* ns, 
   A.b = (double*)(ws + L.b);
   A.bh = (double*)(ws + L.bh);
   A.dofk = (double*)(ws + L.dofk);
+  A.coef = pb->dtype == SL_F64 ? (double2*)(ws + L.coef) : nullptr;
   A.pmask = (unsigned long long*)(ws + L.pmask);
   A.btd = (double*)(ws + L.btd);
   A.pcpart = (double*)(ws + L.pcpart);
