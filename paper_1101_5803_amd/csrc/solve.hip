@@ -71,9 +71,17 @@ struct alignas(16) MemberInfo {
   int Mtrue;       // pixels with at least one subpixel on the grid
   int sell;        // transposed operator: CSR (0), sliced-ELL (1), sliced-ELL with paired 16-bit offsets (2)
   float pc_c;      // scale c of the spectral preconditioner (see k_prep_rhs)
-  int lds_frame;   // 1: the member's image frame fits in LDS beside p and q; 0: global frame
+  int lds_frame;   // where the solve keeps the member's image frame: Mem
   int pad_[2];
 };
+
+// Where a member's image frame and q live.  FP32: p, q and the frame in LDS
+// at offsets for the largest grid, or the frame in global memory.  FP64, whose
+// arrays are twice the size, places them by the member's own grid (LdsPlan),
+// and q, which each iteration writes once and reads once by its owners, gives
+// its place to the frame, which the gathers and the banded passes work in,
+// where not both fit.
+enum Mem { kMemGlobal = 0, kMemLds = 1, kMemLdsQGlobal = 2 };
 
 // Device constants written by k_setup (one copy per workspace).
 struct alignas(16) Consts {
@@ -125,10 +133,17 @@ struct alignas(2 * sizeof(T) > 8 ? 16 : 8) LtEntry {
   T w;
 };
 
+// Weights of the paired form's entries 2k and 2k + 1 of a row.
+template <typename T>
+struct alignas(2 * sizeof(T)) EntryPair {
+  T x, y;
+};
+
 // ------------------------------------------------------------------ parameters
 struct SolveArgs {
   int nx, ny, nsub, n2, K, ck, ckt, reg, n_members, n_lambda, max_ns, maxit, lds_frame_cap;
   int q_off, red_off, pc_off, frame_off;   // byte offsets in dynamic LDS
+  int lds_bytes;                   // dynamic LDS of the solve kernels
   int gframe_elems;                // per-block global frame size (elements)
   int slot_cap;                    // trace-table slots per member (J + 64)
   double pix, R, sigma, tol;
@@ -423,6 +438,26 @@ __global__ void __launch_bounds__(1024) k_setup(SolveArgs a, LamList lams) {
   }
 }
 
+// Byte offsets of a member's arrays in dynamic LDS.
+struct LdsPlan {
+  int p, q, red, frame;
+};
+template <typename T>
+__device__ __forceinline__ LdsPlan lds_plan(const SolveArgs& a, int I, int mem) {
+  if (sizeof(T) == 4) return {0, a.q_off, a.red_off, a.frame_off};
+  const int red = 64 * (int)sizeof(double), v = ((int)sizeof(T) * I + 255) & ~255;
+  return {red, red + v, 0, red + (mem == kMemLdsQGlobal ? v : 2 * v)};
+}
+
+// Mem of a member whose frame has `elems` elements.
+template <typename T>
+__device__ __forceinline__ int mem_of(const SolveArgs& a, int I, long elems) {
+  if (sizeof(T) == 4) return elems <= a.lds_frame_cap ? kMemLds : kMemGlobal;
+  for (int mem : {(int)kMemLds, (int)kMemLdsQGlobal})
+    if (lds_plan<T>(a, I, mem).frame + elems * (long)sizeof(T) <= a.lds_bytes) return mem;
+  return kMemGlobal;
+}
+
 // ------------------------------------------------------------------ member set-up (k_prep_*)
 // The tables of every member, by five grid-wide kernels (one block per member
 // did all of it before: 2.9 ms for a single 128 x 128 lens, 4.0 ms for 256 of
@@ -637,7 +672,7 @@ __global__ void __launch_bounds__(kPrepT) k_prep_place(SolveArgs a) {
         mi.r1 = mi.c1 = -1;
       }
       const int fh = mi.r1 - mi.r0 + 1, fw = mi.c1 - mi.c0 + 1;
-      mi.lds_frame = (long)(fh + 4 * a.ckt + kSegR) * ((fw + 4 * a.ckt) | 1) <= a.lds_frame_cap;
+      mi.lds_frame = mem_of<T>(a, mi.I, (long)(fh + 4 * a.ckt + kSegR) * ((fw + 4 * a.ckt) | 1));
       mi.sell = 0;
       mi.pc_c = 0.0f;
       a.minfo[m] = mi;
@@ -757,10 +792,10 @@ __device__ __forceinline__ int len_bucket(int c) {
 // + p%64, every slice padded to its longest row with entries (offset 0, weight
 // 0) -- offset 0 is a frame halo element, always zero.  Falls back to plain CSR
 // in node order (ptr = row starts) when the padded form exceeds the capacity.
-// FP32 members whose frame fits in LDS (frame offsets below 2^16) store the
+// Members whose frame fits in LDS (frame offsets below 2^16) store the
 // sliced-ELL entries in pairs: slices of even length, one dword holding the
-// 16-bit offsets of entries 2k and 2k + 1 of a lane and one float2 their
-// weights (6 bytes per entry instead of 8).
+// 16-bit offsets of entries 2k and 2k + 1 of a lane and one EntryPair their
+// weights (6 bytes per entry instead of 8 in FP32, 10 instead of 16 in FP64).
 //
 // One block per member: the row lengths are counted with LDS atomics, which a
 // grid-wide count would have to do in memory, and the sixteen waves place
@@ -861,8 +896,7 @@ __global__ void __launch_bounds__(1024) k_prep_layout(SolveArgs a) {
   }
   __syncthreads();
   const int fh = mi.r1 - mi.r0 + 1, fw = mi.c1 - mi.c0 + 1;
-  const bool pair_ok = sizeof(T) == 4 && (long)(fh + 4 * a.ckt + kSegR) * ((fw + 4 * a.ckt) | 1) <= a.lds_frame_cap &&
-                       a.lds_frame_cap <= 65536;
+  const bool pair_ok = mi.lds_frame != kMemGlobal && (long)(fh + 4 * a.ckt + kSegR) * ((fw + 4 * a.ckt) | 1) <= 65536;
   for (int g = wid; g < ngroups; g += 16) {
     int mx = pcnt[64 * g + lane];
 #pragma unroll
@@ -943,7 +977,7 @@ __global__ void __launch_bounds__(1024) k_prep_fill(SolveArgs a, int bands) {
   const int32_t* lbase = a.lt_base + (long)m * a.I_max;
   LtEntry<T>* ent = reinterpret_cast<LtEntry<T>*>(a.lt_ent) + (long)m * a.lt_cap;
   const int E = a.lt_ptr[(long)m * (a.I_max + 65) + (mi.I + 63) / 64];   // sliced-ELL entries
-  int* code2 = reinterpret_cast<int*>(reinterpret_cast<unsigned short*>(ent) + E);   // the paired form's weights
+  T* w2 = reinterpret_cast<T*>(reinterpret_cast<unsigned short*>(ent) + E);   // the paired form's weights
   const bool cubic = a.interp == SL_INTERP_BICUBIC;
   for (int i = tid; i < kFillW * cap; i += 1024) all[i] = 0;
   for (int i = tid; i < nb; i += 1024) base[i] = lbase[n0 + i];
@@ -997,7 +1031,7 @@ __global__ void __launch_bounds__(1024) k_prep_fill(SolveArgs a, int bands) {
       clash &= ~same;
     }
     if (nd >= 0) {
-      if (sell == 2) code2[paired_index(base[nd], j)] = code;
+      if (sell == 2) *reinterpret_cast<int*>(&w2[paired_index(base[nd], j)]) = code;
       else ent[(long)base[nd] + (sell ? 64L : 1L) * j].off = code;
     }
     __builtin_amdgcn_wave_barrier();
@@ -1070,7 +1104,7 @@ struct RhsView {
   const double* vh;   // B^T bhat, or NULL
   LtEntry<T>* ent;
   unsigned short* off16;   // the paired form's offsets and weights
-  float* w32;
+  T* w2;
   int ns, n2, nx, off0, pitch;   // frame offset of image pixel (r, c): r pitch + c + off0
   bool cubic;
 };
@@ -1090,7 +1124,7 @@ __device__ __forceinline__ void rhs_row(const RhsView<T>& o, int node, int n, in
     for (int u = 0; u < U; ++u) {
       const int j = j0 + u;
       next[u] = -1;
-      if (j < n) next[u] = PAIRED ? reinterpret_cast<const int*>(o.w32)[paired_index(e0, j)] : o.ent[e0 + step * j].off;
+      if (j < n) next[u] = PAIRED ? *reinterpret_cast<const int*>(&o.w2[paired_index(e0, j)]) : o.ent[e0 + step * j].off;
     }
   };
   codes(0);
@@ -1155,7 +1189,7 @@ __device__ __forceinline__ void rhs_row(const RhsView<T>& o, int node, int n, in
       if (PAIRED) {
         const long e = paired_index(e0, j);
         o.off16[e] = (unsigned short)off;
-        o.w32[e] = (float)wt;
+        o.w2[e] = wt;
       } else {
         LtEntry<T> y;
         y.off = off;
@@ -1192,7 +1226,7 @@ __global__ void __launch_bounds__(kRhsT) k_prep_rhs(SolveArgs a) {
   o.vh = a.mcn ? a.btd + a.nx * a.ny : nullptr;
   o.ent = reinterpret_cast<LtEntry<T>*>(a.lt_ent) + (long)m * a.lt_cap;
   o.off16 = reinterpret_cast<unsigned short*>(o.ent);
-  o.w32 = reinterpret_cast<float*>(o.off16 + E);
+  o.w2 = reinterpret_cast<T*>(o.off16 + E);
   o.ns = ns;
   o.n2 = n2;
   o.nx = a.nx;
@@ -1798,32 +1832,33 @@ __device__ __forceinline__ double gather_LT(const OpView<T>& o, const T* __restr
       const int len = (lt_rp[sl + 1] - b0) >> 6;
       const int pk = idx < I ? perm[idx] : 0;
       T acc = 0;
-      if (sizeof(T) == 4 && sell == 2) {
+      if (sell == 2) {
         // paired entries (even `len`, entries summed in the same order)
         const unsigned* op = reinterpret_cast<const unsigned*>(lt_e) + (b0 >> 1) + lane;
-        const float2* wq = reinterpret_cast<const float2*>(reinterpret_cast<const unsigned*>(lt_e) + (lt_E >> 1)) +
-                           (b0 >> 1) + lane;
+        const EntryPair<T>* wq = reinterpret_cast<const EntryPair<T>*>(reinterpret_cast<const unsigned*>(lt_e) + (lt_E >> 1)) +
+                                 (b0 >> 1) + lane;
         const int npair = len >> 1;
+        constexpr int U = 8;
         int j = 0;
-        for (; j + 7 < npair; j += 8) {   // sixteen entries in flight
-          unsigned ov[8];
-          float2 wv[8];
+        for (; j + U <= npair; j += U) {   // 2 U entries in flight
+          unsigned ov[U];
+          EntryPair<T> wv[U];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
+          for (int u = 0; u < U; ++u) {
             ov[u] = op[64L * (j + u)];
             wv[u] = wq[64L * (j + u)];
           }
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            acc += (T)wv[u].x * F[ov[u] & 0xFFFFu];
-            acc += (T)wv[u].y * F[ov[u] >> 16];
+          for (int u = 0; u < U; ++u) {
+            acc += wv[u].x * F[ov[u] & 0xFFFFu];
+            acc += wv[u].y * F[ov[u] >> 16];
           }
         }
         for (; j < npair; ++j) {
           const unsigned o0 = op[64L * j];
-          const float2 w0 = wq[64L * j];
-          acc += (T)w0.x * F[o0 & 0xFFFFu];
-          acc += (T)w0.y * F[o0 >> 16];
+          const EntryPair<T> w0 = wq[64L * j];
+          acc += w0.x * F[o0 & 0xFFFFu];
+          acc += w0.y * F[o0 >> 16];
         }
       } else {
         const LtEntry<T>* ep = lt_e + b0 + lane;
@@ -2079,7 +2114,7 @@ __device__ __forceinline__ double apply_normal(const OpView<T>& o, const T* __re
   return gather_LT<T, NT, false>(o, P, Q);
 }
 
-template <typename T, int CKT, bool LDSF, bool PC, bool DIR>
+template <typename T, int CKT, int MEM, bool PC, bool DIR>
 __device__ __forceinline__ void run_item(const SolveArgs& a, const MemberInfo& mi, int m, int kl, unsigned char* smem) {
   constexpr int NT = kNTof<T>;   // threads of this block
   const int tid = threadIdx.x;
@@ -2098,12 +2133,18 @@ __device__ __forceinline__ void run_item(const SolveArgs& a, const MemberInfo& m
   const int J = a.nx * a.ny, n2 = a.n2, nx = a.nx, ny = a.ny, K = a.K, ck = a.ck;
   const T lamT = (T)a.lamv[kl];
   const bool ident = a.reg == SL_H_IDENTITY;
-  T* P = reinterpret_cast<T*>(smem);
-  T* Q = reinterpret_cast<T*>(smem + a.q_off);
-  double* red = reinterpret_cast<double*>(smem + a.red_off);
+  constexpr bool LDSF = MEM != kMemGlobal;
+  const LdsPlan lp = lds_plan<T>(a, I, MEM);
+  T* P = reinterpret_cast<T*>(smem + lp.p);
+  T* Q;   // (the second half of rbuf is the preconditioned launch's, which FP64 has not)
+  if (MEM == kMemLdsQGlobal)
+    Q = reinterpret_cast<T*>(a.rbuf) + (slot + (long)gridDim.x) * a.I_max;
+  else
+    Q = reinterpret_cast<T*>(smem + lp.q);
+  double* red = reinterpret_cast<double*>(smem + lp.red);
   T* F;
   if (LDSF)
-    F = reinterpret_cast<T*>(smem + a.frame_off);
+    F = reinterpret_cast<T*>(smem + lp.frame);
   else
     F = reinterpret_cast<T*>(a.gframe) + (long)blockIdx.x * a.gframe_elems;
   T* const F0 = F + HALO * pitch + HALO;        // interior (0, 0) = image (r0, c0)
@@ -2304,16 +2345,18 @@ __global__ void __launch_bounds__(kNTof<T>) k_solve(SolveArgs a) {
     const int m = item / a.n_lambda, kl = item % a.n_lambda;   // scalar
     const MemberInfo mi = a.minfo[m];                          // uniform address: scalar loads
     if constexpr (PC) {
-      run_item<T, CKT, true, true, DIR>(a, mi, m, kl, smem);
+      run_item<T, CKT, kMemLds, true, DIR>(a, mi, m, kl, smem);
     } else {
       const int status = __builtin_amdgcn_readfirstlane(mi.status);
       const int fits = __builtin_amdgcn_readfirstlane(mi.lds_frame);
       if (status != SL_ST_OK)
         trivial_item<T>(a, mi, m, kl);
-      else if (fits)
-        run_item<T, CKT, true, false, DIR>(a, mi, m, kl, smem);
-      else
-        run_item<T, CKT, false, false, DIR>(a, mi, m, kl, smem);
+      else if (fits == kMemLds)
+        run_item<T, CKT, kMemLds, false, DIR>(a, mi, m, kl, smem);
+      else if (fits == kMemGlobal)
+        run_item<T, CKT, kMemGlobal, false, DIR>(a, mi, m, kl, smem);
+      else if constexpr (sizeof(T) == 8)
+        run_item<T, CKT, kMemLdsQGlobal, false, DIR>(a, mi, m, kl, smem);
     }
   }
 }
@@ -2337,7 +2380,7 @@ __device__ __forceinline__ int fetch_counter(int* counter, int* sh_m) {
 // the second system by its own CG (see below).  Then gamma = <A^T bhat, xhat>
 // = bhat^T A xhat and dof = bhat^T bhat - gamma.  Per-block scratch (global):
 // r, xhat, rhat, phat and the saved p.
-template <typename T, int CKT, bool LDSF, bool DIR>
+template <typename T, int CKT, int MEM, bool DIR>
 __device__ __forceinline__ void run_mc_item(const SolveArgs& a, const MemberInfo& mi, int m, int kl,
                                             unsigned char* smem) {
   constexpr int NT = kNTof<T>;
@@ -2354,10 +2397,12 @@ __device__ __forceinline__ void run_mc_item(const SolveArgs& a, const MemberInfo
   const int pitch = (w + 2 * HALO) | 1;
   const int frame_elems = (h + 2 * HALO + kSegR) * pitch;
   const int J = a.nx * a.ny, n2 = a.n2, nx = a.nx, ny = a.ny, K = a.K, ck = a.ck;
-  T* P = reinterpret_cast<T*>(smem);
-  T* Q = reinterpret_cast<T*>(smem + a.q_off);
-  double* red = reinterpret_cast<double*>(smem + a.red_off);
-  T* F = LDSF ? reinterpret_cast<T*>(smem + a.frame_off) : reinterpret_cast<T*>(a.gframe) + slot * a.gframe_elems;
+  const LdsPlan lp = lds_plan<T>(a, I, MEM);
+  T* P = reinterpret_cast<T*>(smem + lp.p);
+  T* Q = MEM == kMemLdsQGlobal ? reinterpret_cast<T*>(a.rbuf) + slot * a.I_max : reinterpret_cast<T*>(smem + lp.q);
+  double* red = reinterpret_cast<double*>(smem + lp.red);
+  T* F = MEM != kMemGlobal ? reinterpret_cast<T*>(smem + lp.frame)
+                           : reinterpret_cast<T*>(a.gframe) + slot * a.gframe_elems;
   T* const F0 = F + HALO * pitch + HALO;
   const int Dr0 = max(mi.r0 - ck, 0), Dr1 = min(mi.r1 + ck, ny - 1);
   const int Dc0 = max(mi.c0 - ck, 0), Dc1 = min(mi.c1 + ck, nx - 1);
@@ -2515,10 +2560,13 @@ __global__ void __launch_bounds__(kNTof<T>) k_mcdof(SolveArgs a) {
       a.dofv[m] = NAN;   // the same value from every thread
     } else {
       const int kl = __builtin_amdgcn_readfirstlane(a.k_star[m]);
-      if (__builtin_amdgcn_readfirstlane(mi.lds_frame))
-        run_mc_item<T, CKT, true, DIR>(a, mi, m, kl, smem);
-      else
-        run_mc_item<T, CKT, false, DIR>(a, mi, m, kl, smem);
+      const int mem = __builtin_amdgcn_readfirstlane(mi.lds_frame);
+      if (mem == kMemLds)
+        run_mc_item<T, CKT, kMemLds, DIR>(a, mi, m, kl, smem);
+      else if (mem == kMemGlobal)
+        run_mc_item<T, CKT, kMemGlobal, DIR>(a, mi, m, kl, smem);
+      else if constexpr (sizeof(T) == 8)
+        run_mc_item<T, CKT, kMemLdsQGlobal, DIR>(a, mi, m, kl, smem);
     }
   }
 }
@@ -2546,7 +2594,7 @@ __global__ void __launch_bounds__(kNTof<T>) k_mcdof(SolveArgs a) {
 // goes to dofk, and k_corner takes the value at the corner.  Its vectors
 // live in the block's global scratch: xhat, phat and A^T ehat in mcbuf, ehat
 // on the dilated box in the second half of gz.
-template <typename T, int CKT, bool LDSF>
+template <typename T, int CKT, int MEM>
 __device__ __forceinline__ void run_implicit_item(const SolveArgs& a, const MemberInfo& mi, int m,
                                                   unsigned char* smem) {
   constexpr int NT = kNTof<T>;
@@ -2559,10 +2607,13 @@ __device__ __forceinline__ void run_implicit_item(const SolveArgs& a, const Memb
   const int pitch = (w + 2 * HALO) | 1;
   const int frame_elems = (h + 2 * HALO + kSegR) * pitch;
   const int J = a.nx * a.ny, n2 = a.n2, nx = a.nx, ny = a.ny, K = a.K, ck = a.ck;
-  T* P = reinterpret_cast<T*>(smem);                      // search direction p
-  T* G = reinterpret_cast<T*>(smem + a.q_off);            // gradient g = A^T e
-  double* red = reinterpret_cast<double*>(smem + a.red_off);
-  T* F = LDSF ? reinterpret_cast<T*>(smem + a.frame_off) : reinterpret_cast<T*>(a.gframe) + slot * a.gframe_elems;
+  const LdsPlan lp = lds_plan<T>(a, I, MEM);
+  T* P = reinterpret_cast<T*>(smem + lp.p);               // search direction p
+  T* G = MEM == kMemLdsQGlobal ? reinterpret_cast<T*>(a.rbuf) + slot * a.I_max   // gradient g = A^T e
+                               : reinterpret_cast<T*>(smem + lp.q);
+  double* red = reinterpret_cast<double*>(smem + lp.red);
+  T* F = MEM != kMemGlobal ? reinterpret_cast<T*>(smem + lp.frame)
+                           : reinterpret_cast<T*>(a.gframe) + slot * a.gframe_elems;
   T* const F0 = F + HALO * pitch + HALO;
   const int Dr0 = max(mi.r0 - ck, 0), Dr1 = min(mi.r1 + ck, ny - 1);
   const int Dc0 = max(mi.c0 - ck, 0), Dc1 = min(mi.c1 + ck, nx - 1);
@@ -2709,10 +2760,14 @@ __global__ void __launch_bounds__(kNTof<T>) k_implicit(SolveArgs a) {
         a.iters[o] = 0;
         a.status[o] = status;
       }
-    } else if (__builtin_amdgcn_readfirstlane(mi.lds_frame)) {
-      run_implicit_item<T, CKT, true>(a, mi, m, smem);
     } else {
-      run_implicit_item<T, CKT, false>(a, mi, m, smem);
+      const int mem = __builtin_amdgcn_readfirstlane(mi.lds_frame);
+      if (mem == kMemLds)
+        run_implicit_item<T, CKT, kMemLds>(a, mi, m, smem);
+      else if (mem == kMemGlobal)
+        run_implicit_item<T, CKT, kMemGlobal>(a, mi, m, smem);
+      else if constexpr (sizeof(T) == 8)
+        run_implicit_item<T, CKT, kMemLdsQGlobal>(a, mi, m, smem);
     }
     __syncthreads();
   }
@@ -2729,19 +2784,12 @@ __global__ void __launch_bounds__(kNTof<T>) k_implicit(SolveArgs a) {
 // it into the frame, B runs over the dilated box into Z, and the residual
 // sum is FP64.  The frame holds values at the mapped pixels only, each of
 // which every gather overwrites, so it is zeroed once.
-template <typename T, int CKT>
-__global__ void __launch_bounds__(kNTof<T>) k_chi2_src(SolveArgs a, const double* src, int n_src, double* chi2) {
-  extern __shared__ __align__(16) unsigned char smem[];
+template <typename T, int CKT, bool LDSF>
+__device__ __forceinline__ void run_chi2_src(const SolveArgs& a, const MemberInfo& mi, const double* src, int n_src,
+                                             double* chi2, unsigned char* smem) {
   constexpr int NT = kNTof<T>;
   const int tid = threadIdx.x;
-  const MemberInfo mi = a.minfo[0];
-  const int status = __builtin_amdgcn_readfirstlane(mi.status);
   const double inv_s2 = 1.0 / (a.sigma * a.sigma);
-  if (status != SL_ST_OK) {   // no mapped pixel (chi^2 of s = 0) or invalid lens (NaN)
-    const double c2 = status == SL_ST_INVALID ? NAN : a.consts->sum_d2 * inv_s2;
-    for (int p = blockIdx.x; p < n_src; p += gridDim.x) chi2[p] = c2;   // the same value from every thread
-    return;
-  }
   const int ns = mi.ns, I = mi.I, M = mi.M, r0 = mi.r0, c0 = mi.c0;
   const int h = mi.r1 - mi.r0 + 1, w = mi.c1 - mi.c0 + 1;
   constexpr int HALO = 2 * CKT;
@@ -2749,10 +2797,10 @@ __global__ void __launch_bounds__(kNTof<T>) k_chi2_src(SolveArgs a, const double
   const int frame_elems = (h + 2 * HALO + kSegR) * pitch;
   const int J = a.nx * a.ny, n2 = a.n2, nx = a.nx, ny = a.ny, K = a.K, ck = a.ck;
   const long slot = (long)blockIdx.x;
-  T* S = reinterpret_cast<T*>(smem);
-  double* red = reinterpret_cast<double*>(smem + a.red_off);
-  T* F = __builtin_amdgcn_readfirstlane(mi.lds_frame) ? reinterpret_cast<T*>(smem + a.frame_off)
-                                                       : reinterpret_cast<T*>(a.gframe) + slot * a.gframe_elems;
+  const LdsPlan lp = lds_plan<T>(a, I, kMemLdsQGlobal);   // no second vector
+  T* S = reinterpret_cast<T*>(smem + lp.p);
+  double* red = reinterpret_cast<double*>(smem + lp.red);
+  T* F = LDSF ? reinterpret_cast<T*>(smem + lp.frame) : reinterpret_cast<T*>(a.gframe) + slot * a.gframe_elems;
   T* const F0 = F + HALO * pitch + HALO;
   const int Dr0 = max(mi.r0 - ck, 0), Dr1 = min(mi.r1 + ck, ny - 1);
   const int Dc0 = max(mi.c0 - ck, 0), Dc1 = min(mi.c1 + ck, nx - 1);
@@ -2787,6 +2835,23 @@ __global__ void __launch_bounds__(kNTof<T>) k_chi2_src(SolveArgs a, const double
     acc = block_sum1<NT / kWave>(acc, red, 1);   // its barrier: every read of S, the frame and Z is done
     chi2[p] = (acc + d_out) * inv_s2;            // the same value from every thread
     __syncthreads();
+  }
+}
+
+// The frame's place is a template argument: through a pointer that may be to
+// either memory every access to the frame is a flat one.
+template <typename T, int CKT>
+__global__ void __launch_bounds__(kNTof<T>) k_chi2_src(SolveArgs a, const double* src, int n_src, double* chi2) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const MemberInfo mi = a.minfo[0];
+  const int status = __builtin_amdgcn_readfirstlane(mi.status);
+  if (status != SL_ST_OK) {   // no mapped pixel (chi^2 of s = 0) or invalid lens (NaN)
+    const double c2 = status == SL_ST_INVALID ? NAN : a.consts->sum_d2 * (1.0 / (a.sigma * a.sigma));
+    for (int p = blockIdx.x; p < n_src; p += gridDim.x) chi2[p] = c2;   // the same value from every thread
+  } else if (__builtin_amdgcn_readfirstlane(mi.lds_frame) != kMemGlobal) {
+    run_chi2_src<T, CKT, true>(a, mi, src, n_src, chi2, smem);
+  } else {
+    run_chi2_src<T, CKT, false>(a, mi, src, n_src, chi2, smem);
   }
 }
 
@@ -3187,6 +3252,7 @@ static int configure(SolveArgs& A, const Layout& L, const sl_tuning& v, LaunchCf
   if (lds > lds_max) lds = lds_max;
   SL_REQUIRE(lds > fixed + 64 * sz, "source grid too large for LDS");
   A.lds_frame_cap = (int)((lds - fixed) / sz);
+  A.lds_bytes = (int)lds;
   c->ks = ks;
   c->ksd = ksd;
   if (sizeof(T) == 4 && A.reg == SL_H_CURVATURE && !A.plain_cg && !A.implicit) {
@@ -3788,7 +3854,7 @@ int sl_solve_member_info(const sl_problem* pb, int max_ns, int n_members, int n_
     o[6] = mi[m].c1;
     o[7] = mi[m].status;
     o[8] = mi[m].status == SL_ST_OK ? mi[m].sell : -1;
-    o[9] = mi[m].status == SL_ST_OK ? mi[m].lds_frame : -1;
+    o[9] = mi[m].status == SL_ST_OK ? mi[m].lds_frame != kMemGlobal : -1;
   }
   return SL_OK;
 }
