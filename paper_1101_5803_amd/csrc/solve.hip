@@ -1808,7 +1808,14 @@ __device__ __forceinline__ void blur_T_mapped(const OpView<T>& o, const T* __res
 // (no atomics, fixed order), stored in Q.  Returns this thread's part of
 // <p, q>.  With GRAD, q = L^T w alone (no P term) and the return value is
 // this thread's part of ||q||^2.
-template <typename T, int NT, bool GRAD>
+//
+// Bound by the entries' way from L2 and the Infinity Cache and by the bank
+// conflicts of the frame reads.  With PIPE the paired entries are read a batch
+// ahead of their use: 31.0k -> 28.3k cycles per c3 iteration of 65k.  The CKT =
+// 10 kernel has no registers left for it (88.0k -> 88.7k per c4 iteration) and
+// FP64's wide entries gain nothing (9.6k -> 14.2k at 16 x 16 nodes): there,
+// batches of eight pairs.
+template <typename T, int NT, bool GRAD, bool PIPE = false>
 __device__ __forceinline__ double gather_LT(const OpView<T>& o, const T* __restrict__ P, T* __restrict__ Q) {
   const int tid = threadIdx.x;
   const T* const F = o.F;
@@ -1838,27 +1845,67 @@ __device__ __forceinline__ double gather_LT(const OpView<T>& o, const T* __restr
         const EntryPair<T>* wq = reinterpret_cast<const EntryPair<T>*>(reinterpret_cast<const unsigned*>(lt_e) + (lt_E >> 1)) +
                                  (b0 >> 1) + lane;
         const int npair = len >> 1;
-        constexpr int U = 8;
-        int j = 0;
-        for (; j + U <= npair; j += U) {   // 2 U entries in flight
-          unsigned ov[U];
-          EntryPair<T> wv[U];
+        if constexpr (PIPE) {
+          // the next U pairs are read while these U are added; past the row's
+          // end the last pair again, unused.  (One path for the reads: with a
+          // second, unclamped one the values met at the join and every read was
+          // waited for there, 55k cycles instead of 28k.)
+          constexpr int U = 4;
+          unsigned on[U];
+          EntryPair<T> wn[U];
+          const int last = npair - 1;
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            ov[u] = op[64L * (j + u)];
-            wv[u] = wq[64L * (j + u)];
+            const int jj = min(u, max(last, 0));
+            on[u] = npair ? op[64L * jj] : 0u;
+            if (npair) wn[u] = wq[64L * jj];
           }
+          for (int j = 0; j < npair; j += U) {
+            unsigned ov[U];
+            EntryPair<T> wv[U];
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            acc += wv[u].x * F[ov[u] & 0xFFFFu];
-            acc += wv[u].y * F[ov[u] >> 16];
+            for (int u = 0; u < U; ++u) {
+              ov[u] = on[u];
+              wv[u] = wn[u];
+            }
+            if (j + U < npair) {
+#pragma unroll
+              for (int u = 0; u < U; ++u) {
+                const int jj = min(j + U + u, last);
+                on[u] = op[64L * jj];
+                wn[u] = wq[64L * jj];
+              }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              if (j + u < npair) {   // uniform
+                acc += wv[u].x * F[ov[u] & 0xFFFFu];
+                acc += wv[u].y * F[ov[u] >> 16];
+              }
           }
-        }
-        for (; j < npair; ++j) {
-          const unsigned o0 = op[64L * j];
-          const EntryPair<T> w0 = wq[64L * j];
-          acc += w0.x * F[o0 & 0xFFFFu];
-          acc += w0.y * F[o0 >> 16];
+        } else {
+          constexpr int U = 8;
+          int j = 0;
+          for (; j + U <= npair; j += U) {   // 2 U entries in flight
+            unsigned ov[U];
+            EntryPair<T> wv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              ov[u] = op[64L * (j + u)];
+              wv[u] = wq[64L * (j + u)];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              acc += wv[u].x * F[ov[u] & 0xFFFFu];
+              acc += wv[u].y * F[ov[u] >> 16];
+            }
+          }
+          for (; j < npair; ++j) {
+            const unsigned o0 = op[64L * j];
+            const EntryPair<T> w0 = wq[64L * j];
+            acc += w0.x * F[o0 & 0xFFFFu];
+            acc += w0.y * F[o0 >> 16];
+          }
         }
       } else {
         const LtEntry<T>* ep = lt_e + b0 + lane;
@@ -2111,7 +2158,7 @@ __device__ __forceinline__ double apply_normal(const OpView<T>& o, const T* __re
     __syncthreads();
     adjoint_blur<T, CKT, NT>(o, o.Z);  // w = B^T z (at least) at the mapped pixels, in the frame
   }
-  return gather_LT<T, NT, false>(o, P, Q);
+  return gather_LT<T, NT, false, sizeof(T) == 4 && CKT <= 7>(o, P, Q);
 }
 
 template <typename T, int CKT, int MEM, bool PC, bool DIR>
