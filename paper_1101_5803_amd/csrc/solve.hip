@@ -449,13 +449,22 @@ __device__ __forceinline__ LdsPlan lds_plan(const SolveArgs& a, int I, int mem) 
   return {red, red + v, 0, red + (mem == kMemLdsQGlobal ? v : 2 * v)};
 }
 
+// Where q of a member with its frame in LDS lives: in LDS, but in global memory
+// for FP64 with the wider windows, whose frames leave it no room more often
+// than not.  (One place per kernel: an FP64 kernel with all three forms grew
+// past what the compiler takes apart, its arguments stayed in scratch memory
+// and every access through their pointers became a flat one.)
+template <typename T>
+__host__ __device__ constexpr int lds_mem(int ckt) {
+  return sizeof(T) == 8 && ckt > 2 ? kMemLdsQGlobal : kMemLds;
+}
+
 // Mem of a member whose frame has `elems` elements.
 template <typename T>
 __device__ __forceinline__ int mem_of(const SolveArgs& a, int I, long elems) {
   if (sizeof(T) == 4) return elems <= a.lds_frame_cap ? kMemLds : kMemGlobal;
-  for (int mem : {(int)kMemLds, (int)kMemLdsQGlobal})
-    if (lds_plan<T>(a, I, mem).frame + elems * (long)sizeof(T) <= a.lds_bytes) return mem;
-  return kMemGlobal;
+  const int mem = lds_mem<T>(a.ckt);
+  return lds_plan<T>(a, I, mem).frame + elems * (long)sizeof(T) <= a.lds_bytes ? mem : (int)kMemGlobal;
 }
 
 // ------------------------------------------------------------------ member set-up (k_prep_*)
@@ -1845,7 +1854,8 @@ __device__ __forceinline__ double gather_LT(const OpView<T>& o, const T* __restr
         const EntryPair<T>* wq = reinterpret_cast<const EntryPair<T>*>(reinterpret_cast<const unsigned*>(lt_e) + (lt_E >> 1)) +
                                  (b0 >> 1) + lane;
         const int npair = len >> 1;
-        if constexpr (PIPE) {
+        if (PIPE && npair >= 4) {
+          // (rows shorter than a batch: one by one below)
           // the next U pairs are read while these U are added; past the row's
           // end the last pair again, unused.  (One path for the reads: with a
           // second, unclamped one the values met at the join and every read was
@@ -1884,8 +1894,9 @@ __device__ __forceinline__ double gather_LT(const OpView<T>& o, const T* __restr
               }
           }
         } else {
-          constexpr int U = 8;
           int j = 0;
+          if constexpr (!PIPE) {
+          constexpr int U = 8;
           for (; j + U <= npair; j += U) {   // 2 U entries in flight
             unsigned ov[U];
             EntryPair<T> wv[U];
@@ -1899,6 +1910,7 @@ __device__ __forceinline__ double gather_LT(const OpView<T>& o, const T* __restr
               acc += wv[u].x * F[ov[u] & 0xFFFFu];
               acc += wv[u].y * F[ov[u] >> 16];
             }
+          }
           }
           for (; j < npair; ++j) {
             const unsigned o0 = op[64L * j];
@@ -2398,12 +2410,10 @@ __global__ void __launch_bounds__(kNTof<T>) k_solve(SolveArgs a) {
       const int fits = __builtin_amdgcn_readfirstlane(mi.lds_frame);
       if (status != SL_ST_OK)
         trivial_item<T>(a, mi, m, kl);
-      else if (fits == kMemLds)
-        run_item<T, CKT, kMemLds, false, DIR>(a, mi, m, kl, smem);
       else if (fits == kMemGlobal)
         run_item<T, CKT, kMemGlobal, false, DIR>(a, mi, m, kl, smem);
-      else if constexpr (sizeof(T) == 8)
-        run_item<T, CKT, kMemLdsQGlobal, false, DIR>(a, mi, m, kl, smem);
+      else
+        run_item<T, CKT, lds_mem<T>(CKT), false, DIR>(a, mi, m, kl, smem);
     }
   }
 }
@@ -2608,12 +2618,10 @@ __global__ void __launch_bounds__(kNTof<T>) k_mcdof(SolveArgs a) {
     } else {
       const int kl = __builtin_amdgcn_readfirstlane(a.k_star[m]);
       const int mem = __builtin_amdgcn_readfirstlane(mi.lds_frame);
-      if (mem == kMemLds)
-        run_mc_item<T, CKT, kMemLds, DIR>(a, mi, m, kl, smem);
-      else if (mem == kMemGlobal)
+      if (mem == kMemGlobal)
         run_mc_item<T, CKT, kMemGlobal, DIR>(a, mi, m, kl, smem);
-      else if constexpr (sizeof(T) == 8)
-        run_mc_item<T, CKT, kMemLdsQGlobal, DIR>(a, mi, m, kl, smem);
+      else
+        run_mc_item<T, CKT, lds_mem<T>(CKT), DIR>(a, mi, m, kl, smem);
     }
   }
 }
@@ -2809,12 +2817,10 @@ __global__ void __launch_bounds__(kNTof<T>) k_implicit(SolveArgs a) {
       }
     } else {
       const int mem = __builtin_amdgcn_readfirstlane(mi.lds_frame);
-      if (mem == kMemLds)
-        run_implicit_item<T, CKT, kMemLds>(a, mi, m, smem);
-      else if (mem == kMemGlobal)
+      if (mem == kMemGlobal)
         run_implicit_item<T, CKT, kMemGlobal>(a, mi, m, smem);
-      else if constexpr (sizeof(T) == 8)
-        run_implicit_item<T, CKT, kMemLdsQGlobal>(a, mi, m, smem);
+      else
+        run_implicit_item<T, CKT, lds_mem<T>(CKT)>(a, mi, m, smem);
     }
     __syncthreads();
   }
