@@ -459,10 +459,19 @@ __host__ __device__ constexpr int lds_mem(int ckt) {
   return sizeof(T) == 8 && ckt > 2 ? kMemLdsQGlobal : kMemLds;
 }
 
+// FP64 members with more nodes keep a global frame.  p alone takes 72 KB or
+// more of theirs, so a 128 x 128 lens's frame fits beside it for some members
+// and not for others, and the others' items, the longest of their launch, set
+// its time either way (64 members of 32..96 nodes per side with Monte Carlo
+// degrees of freedom, against one earlier build: 1.67x with the limit, 1.64x
+// without).
+constexpr int kLdsNodesF64 = 9000;
+
 // Mem of a member whose frame has `elems` elements.
 template <typename T>
 __device__ __forceinline__ int mem_of(const SolveArgs& a, int I, long elems) {
   if (sizeof(T) == 4) return elems <= a.lds_frame_cap ? kMemLds : kMemGlobal;
+  if (I > kLdsNodesF64) return kMemGlobal;
   const int mem = lds_mem<T>(a.ckt);
   return lds_plan<T>(a, I, mem).frame + elems * (long)sizeof(T) <= a.lds_bytes ? mem : (int)kMemGlobal;
 }
