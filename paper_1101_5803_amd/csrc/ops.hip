@@ -656,10 +656,11 @@ static int blur_launch(int nx, int ny, int n_images, const double* psf, int k, c
 // The register-tiled forms need a block per CU to win (K = 15, 16 images of
 // 128 x 128, 256 blocks of 32 x 32: 15.0 against 14.7 us; K = 21, 64 images of
 // 200 x 200: 72 against 199 us; K = 63, 640 x 640, 400 blocks: 143 against 301 us).
+// More images than a grid is deep stay with the form whose launch refuses them.
 template <typename T, bool TR>
 static int blur_impl(int nx, int ny, int n_images, const double* psf, int k, const void* in, void* out,
                      hipStream_t st) {
-  const long rows = (long)nblocks(ny, kBlurR) * n_images;
+  const long rows = n_images <= 65535 ? (long)nblocks(ny, kBlurR) * n_images : 0;
   if (nblocks(nx, 64) * rows >= 2L * device_cus()) return blur_launch<T, TR, 8>(nx, ny, n_images, psf, k, in, out, st);
   if (nblocks(nx, 32) * rows > device_cus()) return blur_launch<T, TR, 4>(nx, ny, n_images, psf, k, in, out, st);
   const int tw = kTile + k - 1;
