@@ -1976,31 +1976,42 @@ __device__ __forceinline__ double gather_LT(const OpView<T>& o, const T* __restr
   return pq;
 }
 
-// Register-tiled direct K x K forms, for a PSF of exactly KT = 2 CKT + 1
-// taps per side.  Each thread computes eight consecutive outputs of one row
+// Register-tiled direct K x K forms.  Each thread computes eight consecutive outputs of one row
 // from a window of KT + 7 values per input row, so that one load serves up
 // to eight products; consecutive lanes take consecutive rows, so with the
 // odd frame pitch their LDS reads fall in distinct banks.  The last tile of a
 // row starts at width - 8: tiles overlap there and write the same values
 // twice.  Each output sums its taps in the order of the per-output forms
 // (row of the PSF outer, column inner), so the results are the same.
-// Usable when ck == CKT and both the box and the dilated box are at least 8
-// wide (tiled_ok).
+// Usable when the window is the PSF's own (not one size up) and both the box
+// and the dilated box are at least 8 wide (tiled_ok).  FULL: the PSF has
+// exactly KT = 2 CKT + 1 taps per side; otherwise the taps past the window's
+// narrowest PSF are guarded in pairs by uniform branches, and the values they
+// would have met are read from the frame's zero halo (2 CKT wide).
+// (They took the per-output forms before, each tap a load: 24 members of a
+// 96 x 90 image at four lambdas, K = 7, 11, 19 in FP32 42.4, 83.5, 245 ms,
+// now 11.9, 13.9, 23.6; K = 9, 13, 19 in FP64 111, 216, 474 ms, now 24.5,
+// 32.1, 45.3; the widest sides' 15 and 21 take 16.4 and 25.3 ms in FP32.)
+template <typename T>
+__device__ constexpr int narrowest_ck(int ckt) {   // of the PSFs that take window ckt
+  return ckt == 2 ? 0 : ckt == 10 ? 8 : ckt == 16 ? 11 : sizeof(T) == 8 || ckt == 4 ? 3 : 5;
+}
 template <typename T, int CKT>
 __device__ __forceinline__ bool tiled_ok(const OpView<T>& o) {
-  return o.ck == CKT && o.w >= 8 && o.Dw >= 8;
+  return o.ck <= CKT && o.ck >= narrowest_ck<T>(CKT) && o.w >= 8 && o.Dw >= 8;
 }
 
 // z = B y over the dilated box into Z (Dh x Dw, row-major), y in the frame
 // with its zero halo.  Returns this thread's part of ||z||^2 (each output
 // counted once).
-template <typename T, int CKT, int NT, typename FP, typename TP, typename ZP>
+template <typename T, int CKT, int NT, bool FULL, typename FP, typename TP, typename ZP>
 __device__ __forceinline__ double blur_box_t8(const OpView<T>& o, FP F0, TP taps, ZP __restrict__ Z) {
-  constexpr int KT = 2 * CKT + 1, NV = KT + 7;
+  constexpr int KT = 2 * CKT + 1, NV = KT + 7, KMIN = FULL ? KT : 2 * narrowest_ck<T>(CKT) + 1;
+  const int K = FULL ? KT : o.K, ck = FULL ? CKT : o.ck;
   const int Dh = o.Dh, Dw = o.Dw, pitch = o.pitch;
-  const auto tp = taps + TapIdx(KT).psf;
+  const auto tp = taps + TapIdx(K).psf;
   // output (r, c) of the dilated box reads base[(r - aa) * pitch + (c - bb)]
-  const auto base = F0 + (o.Dr0 + CKT - o.r0) * pitch + (o.Dc0 + CKT - o.c0);
+  const auto base = F0 + (o.Dr0 + ck - o.r0) * pitch + (o.Dc0 + ck - o.c0);
   const int nct = (Dw + 7) >> 3;
   double zz = 0.0;
   for (int t = threadIdx.x; t < Dh * nct; t += NT) {
@@ -2010,18 +2021,28 @@ __device__ __forceinline__ double blur_box_t8(const OpView<T>& o, FP F0, TP taps
     T acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0;
-    for (int aa = 0; aa < KT; ++aa) {
+    for (int aa = 0; aa < K; ++aa) {
       const auto row = base + (r - aa) * pitch + c - (KT - 1);
       T v[NV];
 #pragma unroll
       for (int j = 0; j < NV; ++j) v[j] = row[j];
-      const auto ta = tp + aa * KT;
+      const auto ta = tp + aa * K;
 #pragma unroll
-      for (int bb = 0; bb < KT; ++bb) {
+      for (int bb = 0; bb < KMIN; ++bb) {
         const T tv = ta[bb];
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] += tv * v[i - bb + KT - 1];
       }
+#pragma unroll
+      for (int b2 = KMIN; b2 < KT; b2 += 2)
+        if (b2 < K) {
+#pragma unroll
+          for (int bb = b2; bb < b2 + 2; ++bb) {
+            const T tv = ta[bb];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] += tv * v[i - bb + KT - 1];
+          }
+        }
     }
     const auto zo = Z + r * Dw + c;
 #pragma unroll
@@ -2035,13 +2056,14 @@ __device__ __forceinline__ double blur_box_t8(const OpView<T>& o, FP F0, TP taps
 
 // w = B^T z over the bounding box (h x w) into W (row-major, pitch w), z
 // staged in the frame over the dilated box with zeros beyond it.
-template <typename T, int CKT, int NT>
+template <typename T, int CKT, int NT, bool FULL>
 __device__ __forceinline__ void blurT_box_t8(const OpView<T>& o, T* __restrict__ W) {
-  constexpr int KT = 2 * CKT + 1, NV = KT + 7;
+  constexpr int KT = 2 * CKT + 1, NV = KT + 7, KMIN = FULL ? KT : 2 * narrowest_ck<T>(CKT) + 1;
+  const int K = FULL ? KT : o.K, ck = FULL ? CKT : o.ck;
   const int h = o.h, w = o.w, pitch = o.pitch;
-  const T* tp = o.taps + TapIdx(KT).psf;
+  const T* tp = o.taps + TapIdx(K).psf;
   // output (r, c) of the box reads base[(r + aa) * pitch + (c + bb)]
-  const T* base = o.F0 - CKT * pitch - CKT;
+  const T* base = o.F0 - ck * pitch - ck;
   const int nct = (w + 7) >> 3;
   for (int t = threadIdx.x; t < h * nct; t += NT) {
     const int r = t % h;
@@ -2049,18 +2071,28 @@ __device__ __forceinline__ void blurT_box_t8(const OpView<T>& o, T* __restrict__
     T acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0;
-    for (int aa = 0; aa < KT; ++aa) {
+    for (int aa = 0; aa < K; ++aa) {
       const T* row = base + (r + aa) * pitch + c;
       T v[NV];
 #pragma unroll
       for (int j = 0; j < NV; ++j) v[j] = row[j];
-      const T* ta = tp + aa * KT;
+      const T* ta = tp + aa * K;
 #pragma unroll
-      for (int bb = 0; bb < KT; ++bb) {
+      for (int bb = 0; bb < KMIN; ++bb) {
         const T tv = ta[bb];
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] += tv * v[i + bb];
       }
+#pragma unroll
+      for (int b2 = KMIN; b2 < KT; b2 += 2)
+        if (b2 < K) {
+#pragma unroll
+          for (int bb = b2; bb < b2 + 2; ++bb) {
+            const T tv = ta[bb];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] += tv * v[i + bb];
+          }
+        }
     }
     T* wo = W + r * w + c;
 #pragma unroll
@@ -2093,7 +2125,8 @@ __device__ __forceinline__ void adjoint_blur(const OpView<T>& o, const T* __rest
   if (tiled_ok<T, CKT>(o)) {   // uniform: scalar member values
     stage_dilated<T, NT>(o, Zs);
     __syncthreads();
-    blurT_box_t8<T, CKT, NT>(o, o.W);
+    if (o.ck == CKT) blurT_box_t8<T, CKT, NT, true>(o, o.W);
+    else blurT_box_t8<T, CKT, NT, false>(o, o.W);
     __syncthreads();
     stage_box<T, NT>(o, o.W);
   } else {
@@ -2102,11 +2135,20 @@ __device__ __forceinline__ void adjoint_blur(const OpView<T>& o, const T* __rest
   __syncthreads();
 }
 
-// z = B y over the dilated box into Z; returns this thread's part of ||z||^2.
-template <typename T, int CKT, int NT>
+// z = B y over the dilated box into Z; with SUM returns this thread's part of
+// ||z||^2.  Narrower PSFs than the window's widest add it up in the order of
+// the per-output form, which they took before.
+template <typename T, int CKT, int NT, bool SUM>
 __device__ __forceinline__ double forward_blur(const OpView<T>& o, T* __restrict__ Z) {
-  if (tiled_ok<T, CKT>(o)) return blur_box_t8<T, CKT, NT>(o, (const T*)o.F0, o.taps, Z);
-  return blur_box<T, CKT, NT>(o, (const T*)o.F0, o.taps, Z);
+  if (!tiled_ok<T, CKT>(o)) return blur_box<T, CKT, NT>(o, (const T*)o.F0, o.taps, Z);
+  if (o.ck == CKT) return blur_box_t8<T, CKT, NT, true>(o, (const T*)o.F0, o.taps, Z);
+  (void)blur_box_t8<T, CKT, NT, false>(o, (const T*)o.F0, o.taps, Z);
+  double zz = 0.0;
+  if (SUM) {
+    __syncthreads();
+    for (int e = threadIdx.x; e < o.Dh * o.Dw; e += NT) zz += (double)Z[e] * (double)Z[e];
+  }
+  return zz;
 }
 
 // The same, out of line, for the end of an item: its registers stay out of the
@@ -2132,15 +2174,16 @@ __device__ __attribute__((noinline)) void model_image(const T* F0_, const T* tap
   o.Dc0 = __builtin_amdgcn_readfirstlane(Dc0);
   o.Dh = __builtin_amdgcn_readfirstlane(Dh);
   o.Dw = __builtin_amdgcn_readfirstlane(Dw);
-  if (tiled_ok<T, CKT>(o)) (void)blur_box_t8<T, CKT, NT>(o, F0, taps, Z);
-  else (void)blur_box<T, CKT, NT>(o, F0, taps, Z);
+  if (!tiled_ok<T, CKT>(o)) (void)blur_box<T, CKT, NT>(o, F0, taps, Z);
+  else if (o.ck == CKT) (void)blur_box_t8<T, CKT, NT, true>(o, F0, taps, Z);
+  else (void)blur_box_t8<T, CKT, NT, false>(o, F0, taps, Z);
 }
 
 // Zero the frame rows that an operator application wrote, after every
 // gather has read the frame: the bounding box's rows (full pitch), and after
 // the tiled direct blur (DIR: the direct forms ran; the tiled one stages z
 // there) also the ck rows above and below them.  The tiled form needs
-// ck == CKT, so those rows lie inside the frame's 2 CKT halo; the other forms
+// ck <= CKT, so those rows lie inside the frame's 2 CKT halo; the other forms
 // write inside the box only.
 template <typename T, int CKT, int NT, bool DIR>
 __device__ __forceinline__ void clear_rows(const OpView<T>& o) {
@@ -2175,7 +2218,7 @@ __device__ __forceinline__ double apply_normal(const OpView<T>& o, const T* __re
                                o.taps + ti.ery);
     __syncthreads();
   } else {
-    forward_blur<T, CKT, NT>(o, o.Z);  // z = B y over the dilated region into global Z
+    forward_blur<T, CKT, NT, false>(o, o.Z);  // z = B y over the dilated region into global Z
     __syncthreads();
     adjoint_blur<T, CKT, NT>(o, o.Z);  // w = B^T z (at least) at the mapped pixels, in the frame
   }
@@ -2729,7 +2772,7 @@ __device__ __forceinline__ void run_implicit_item(const SolveArgs& a, const Memb
     if (__builtin_amdgcn_readfirstlane((int)(gg <= 0.0))) break;
     gather_L<T, NT>(ov, P);                               // frame = L p
     __syncthreads();
-    double qq = forward_blur<T, CKT, NT>(ov, Zq);         // q = B L p
+    double qq = forward_blur<T, CKT, NT, true>(ov, Zq);         // q = B L p
     qq = block_sum1<NT / kWave>(qq, red, 0);
     if (__builtin_amdgcn_readfirstlane((int)!(qq > 0.0))) {
       st = SL_ST_BREAKDOWN;
@@ -2770,7 +2813,7 @@ __device__ __forceinline__ void run_implicit_item(const SolveArgs& a, const Memb
       __syncthreads();                                    // the frame is clear again
       gather_L<T, NT>(ov, ph);
       __syncthreads();
-      forward_blur<T, CKT, NT>(ov, Zq);                   // A phat
+      forward_blur<T, CKT, NT, false>(ov, Zq);                   // A phat
       __syncthreads();
       double gam = 0.0;
       for (int i = tid; i < I; i += NT) {
@@ -2887,7 +2930,7 @@ __device__ __forceinline__ void run_chi2_src(const SolveArgs& a, const MemberInf
     __syncthreads();
     gather_L<T, NT>(ov, S);                      // frame = L s_p at the mapped pixels
     __syncthreads();
-    forward_blur<T, CKT, NT>(ov, Z);             // Z = B L s_p over the dilated box
+    forward_blur<T, CKT, NT, false>(ov, Z);             // Z = B L s_p over the dilated box
     __syncthreads();
     double acc = 0.0;
     for (int e = tid; e < Dh * Dw; e += NT) {
