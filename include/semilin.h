@@ -462,8 +462,9 @@ int sl_lcurve_corner(const double* reg, const double* chi2, int n, int32_t* k_st
 /*
  * Bytes of device workspace that a call with this batch size needs (the
  * activations, gradient signals and partial sums of the training step; the
- * forward pass leaves it untouched).  Returns 0, with sl_last_error set, for a
- * batch outside [0, SL_MLP_MAX_BATCH].  The caller allocates it; calls that
+ * forward pass leaves it untouched).  It never falls as the batch grows, so a
+ * workspace for a program's largest batch serves every smaller one.  Returns 0,
+ * with sl_last_error set, for a batch outside [0, SL_MLP_MAX_BATCH].  The caller allocates it; calls that
  * share a workspace must not overlap in time.
  */
 size_t sl_mlp_workspace_size(int batch);

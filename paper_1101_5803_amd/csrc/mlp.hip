@@ -74,6 +74,11 @@ __device__ __forceinline__ float gelu_grad(float z) {
 // independent, and every sum over a row's columns has the same order).
 int rows_per_block(int batch) { return batch <= 2048 ? 8 : batch <= 4096 ? 16 : 32; }
 int row_tiles(int batch) { return (batch + rows_per_block(batch) - 1) / rows_per_block(batch); }
+// Tiles that a workspace of this batch has room for: the most of any batch up to
+// it.  A caller may size one workspace for its largest batch and train smaller
+// ones in it (the calls take no size), and 2048 rows have more tiles than 2049.
+int tile_room(int batch) { return batch <= 2048 ? row_tiles(batch) : std::max(row_tiles(2048), row_tiles(batch)); }
+static_assert(4096 / 16 <= 2048 / 8, "16-row tiles never outnumber the 8-row tiles of 2048 rows");
 // Row ranges of gW1: 128 rows or more each (64: 31.4 against 29.9 us for a step on 1024 rows).
 int row_splits(int batch) { return std::min(kMaxSplit, std::max(1, batch / 128)); }
 
@@ -92,7 +97,7 @@ size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 size_t carve(int batch, unsigned char* base, Ws* w) {
   const size_t B = (size_t)(batch > 0 ? batch : 0);
-  const size_t tiles = (size_t)row_tiles(batch);
+  const size_t tiles = (size_t)tile_room(batch);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
