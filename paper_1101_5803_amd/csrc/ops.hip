@@ -337,8 +337,8 @@ __global__ void k_fill(T* __restrict__ p, long n, T v) {
 // values from LDS (the same for every lane) and N + 7 input values serve 8 N
 // products (two LDS reads per product in k_blur_small); a half-wave's lanes take consecutive rows,
 // which the odd pitch puts in distinct banks.  Every output adds its taps in
-// row-major order.  N = 8 reads less per product, N = 4 gives twice the waves:
-// the host takes 8 where that leaves at least two blocks per CU.
+// row-major order.  N = 8 reads less per product, N = 4 gives twice the waves;
+// blur_cost estimates which is faster.
 constexpr int kBlurT = 256, kBlurR = 32;
 template <typename T, bool TRANSPOSE, int N>
 __global__ void __launch_bounds__(kBlurT) k_blur(int nx, int ny, const double* __restrict__ psf, int K,
@@ -424,9 +424,9 @@ __global__ void __launch_bounds__(kBlurT) k_blur(int nx, int ny, const double* _
     if (c0 + i < nx) o[i] = acc[i];
 }
 
-// The same for few outputs: one output per thread in 16 x 16 tiles, 256 threads
-// a block, so that a single 200 x 200 image (K = 21) is 676 waves instead of
-// the 196 of k_blur<4>: 12 against 22 us.
+// The same for few outputs and small or thin images: one output per thread in
+// 16 x 16 tiles, 256 threads a block, so that a single 200 x 200 image (K = 21) is
+// 676 waves instead of the 196 of k_blur<4>: 12 against 22 us.
 constexpr int kTile = 16;
 
 template <typename T, bool TRANSPOSE>
@@ -641,11 +641,17 @@ static int apply_LT_ordered_impl(const double* uv, int n_members, const sl_image
   return SL_OK;
 }
 
+// LDS of a blur block with N consecutive outputs a thread (1: k_blur_small).
+template <typename T>
+static size_t blur_lds(int N, int k) {
+  if (N == 1) return sizeof(T) * ((size_t)k * k + (size_t)(kTile + k - 1) * (kTile + k - 1));
+  return sizeof(T) * ((size_t)k * ((k + 7) & ~7) + (size_t)(kBlurR + k - 1) * ((8 * N + k - 1) | 1) + 8);
+}
+
 template <typename T, bool TR, int N>
 static int blur_launch(int nx, int ny, int n_images, const double* psf, int k, const void* in, void* out,
                        hipStream_t st) {
-  const size_t lds =
-      sizeof(T) * ((size_t)k * ((k + 7) & ~7) + (size_t)(kBlurR + k - 1) * ((8 * N + k - 1) | 1) + 8);
+  const size_t lds = blur_lds<T>(N, k);
   if (lds > 64 * 1024)
     SL_HIP(hipFuncSetAttribute((const void*)k_blur<T, TR, N>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   const unsigned blocks = nblocks(nx, 8 * N) * nblocks(ny, kBlurR) * (unsigned)n_images;
@@ -653,18 +659,64 @@ static int blur_launch(int nx, int ny, int n_images, const double* psf, int k, c
   return check_launch("k_blur");
 }
 
-// The register-tiled forms need a block per CU to win (K = 15, 16 images of
-// 128 x 128, 256 blocks of 32 x 32: 15.0 against 14.7 us; K = 21, 64 images of
-// 200 x 200: 72 against 199 us; K = 63, 640 x 640, 400 blocks: 143 against 301 us).
-// More images than a grid is deep stay with the form whose launch refuses them.
+// Estimated microseconds of one form, launch aside: rounds of blocks, each of a
+// fixed part and one output's chain of products, and the products of the waves
+// that hold outputs (on images narrower or flatter than a tile most of a
+// register-tiled block's waves hold none; k_blur_small's tile fits closer).
+// The constants are fits to 2010 measured launches of each form: 33 image
+// shapes from 4 x 4 and 1 x 200 to 512 x 512, 2^17 to 2^21 outputs, K = 1 to 63,
+// both types.  *bare: few blocks or few waves with outputs on a CU, which leave
+// nothing to hide a block's staging and its chains behind.
+template <typename T>
+static double blur_cost(int N, int nx, int ny, int n_images, int k, double* bare) {
+  struct Cost {
+    double block, chain, wave;
+  };
+  static const Cost kCost[2][3] = {{{0.30, 0.0038, 0.0022}, {1.20, 0.020, 0.0021}, {0.54, 0.022, 0.0019}},
+                                   {{0.10, 0.0105, 0.0028}, {3.20, 0.019, 0.0055}, {0.96, 0.021, 0.0043}}};
+  const Cost& c = kCost[sizeof(T) == 8][N / 4];
+  const int cus = device_cus(), fit = std::max(1, std::min(8, (int)(160 * 1024 / blur_lds<T>(N, k))));
+  double blocks, waves, work;
+  if (N == 1) {
+    blocks = (double)nblocks(nx, kTile) * nblocks(ny, kTile);
+    waves = (double)nblocks(nx, kTile) * nblocks(ny, 4);   // four rows of a tile per wave
+    work = (double)k * k;
+  } else {   // two column groups of N per wave
+    blocks = (double)nblocks(nx, 8 * N) * nblocks(ny, kBlurR);
+    waves = (nx / (8 * N) * 4 + (double)nblocks(nblocks(nx % (8 * N), N), 2)) * nblocks(ny, kBlurR);
+    work = (double)k * ((k + 7) / 8) * 4 * (N / 4 + 1);
+  }
+  *bare = fit * waves <= 3 * blocks ? 1.6 : fit <= 2 ? 1.2 : 1.0;
+  const double rounds = std::max(1.0, blocks * n_images / ((double)cus * fit));
+  return rounds * (c.block + c.chain * work) + c.wave * waves * n_images * work / cus;
+}
+
+// A register-tiled form has to be estimated a fifth faster than k_blur_small (more
+// with few waves on a CU), so that the error of an estimate does not lose time.
+// So chosen, 6 of the 2010 launches are more than 5 % slower than with
+// k_blur_small, by 11 % at most, and the choice is within 3.5 % of the best of
+// the three on average.  (The rule before counted full tiles only and took a
+// register-tiled form from one or two blocks per CU up: 8192 images of 8 x 8, K =
+// 63, 592 -> 3358 us; one 2000 x 2000 image in FP64, K = 3, 35 -> 44 us.)  Below K =
+// 5 (FP64: 9) a tile's staging and the stores of N outputs per lane, a row apart
+// from lane to lane, cost what the register window saves; at K = 5 only rows of
+// whole groups of N win.  Where they win: K = 21, 64 images of 200 x 200, 72
+// against 199 us; K = 63, 640 x 640, 143 against 301 us.
 template <typename T, bool TR>
 static int blur_impl(int nx, int ny, int n_images, const double* psf, int k, const void* in, void* out,
                      hipStream_t st) {
-  const long rows = n_images <= 65535 ? (long)nblocks(ny, kBlurR) * n_images : 0;
-  if (nblocks(nx, 64) * rows >= 2L * device_cus()) return blur_launch<T, TR, 8>(nx, ny, n_images, psf, k, in, out, st);
-  if (nblocks(nx, 32) * rows > device_cus()) return blur_launch<T, TR, 4>(nx, ny, n_images, psf, k, in, out, st);
-  const int tw = kTile + k - 1;
-  const size_t lds = sizeof(T) * ((size_t)k * k + (size_t)tw * tw);
+  if (k >= (sizeof(T) == 4 ? 5 : 9)) {
+    double bare, bare4, bare8;
+    const double small = 0.8 * blur_cost<T>(1, nx, ny, n_images, k, &bare);
+    const double c4 = blur_cost<T>(4, nx, ny, n_images, k, &bare4), c8 = blur_cost<T>(8, nx, ny, n_images, k, &bare8);
+    const bool ok4 = k > 5 || nx % 4 == 0, ok8 = k > 5 || nx % 8 == 0;
+    if (ok4 && (c4 <= c8 || !ok8)) {
+      if (bare4 * c4 < small) return blur_launch<T, TR, 4>(nx, ny, n_images, psf, k, in, out, st);
+    } else if (ok8 && bare8 * c8 < small) {
+      return blur_launch<T, TR, 8>(nx, ny, n_images, psf, k, in, out, st);
+    }
+  }
+  const size_t lds = blur_lds<T>(1, k);
   if (lds > 64 * 1024)
     SL_HIP(hipFuncSetAttribute((const void*)k_blur_small<T, TR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   hipLaunchKernelGGL((k_blur_small<T, TR>), dim3(nblocks(nx, kTile), nblocks(ny, kTile), n_images),
