@@ -100,50 +100,62 @@ __global__ void __launch_bounds__(256) k_apply_L(const double* __restrict__ uv, 
   img[(long)m * J + j] = acc / (T)n2;
 }
 
-// L^T of part of one member's pixels.  LDS = true: the terms are added in an
-// LDS copy of the member's source grid first and only its nonzero nodes go to
-// memory, where atomics across the XCDs run at about 36 G/s (every term there:
-// 285 us for 16 members of a 128 x 128 image, 4.2 M terms; LDS: 19 us).  The
-// lanes of a wave take pixels n/64 apart, so that a magnified region's
-// neighbouring pixels, which share nodes, do not meet in one LDS access.
-// LDS = false: grids whose source does not fit in LDS.
+// Adds the four terms of each of a pixel's subpixels to acc.
+template <typename T>
+__device__ __forceinline__ void add_pixel(const UV* __restrict__ p, int n2, int ns, T val, T* acc) {
+  for (int k = 0; k < n2; ++k) {
+    const UV q = p[k];
+    int cell;
+    double fx, fy;
+    if (!grid_cell(q.u, q.v, ns, cell, fx, fy)) continue;
+    const T tx = (T)fx, ty = (T)fy;
+    atomicAdd(&acc[cell], (1 - tx) * (1 - ty) * val);
+    atomicAdd(&acc[cell + 1], tx * (1 - ty) * val);
+    atomicAdd(&acc[cell + ns], (1 - tx) * ty * val);
+    atomicAdd(&acc[cell + ns + 1], tx * ty * val);
+  }
+}
+
+// L^T of part of one member's pixels: the terms are added in an LDS copy of the
+// member's source grid first and only its nonzero nodes go to memory, where
+// atomics across the XCDs run at about 36 G/s (every term there: 285 us for 16
+// members of a 128 x 128 image, 4.2 M terms; LDS: 19 us).  The lanes of a wave
+// take pixels n/64 apart, so that a magnified region's neighbouring pixels, which
+// share nodes, do not meet in one LDS access.
 constexpr int kLtT = 512;
-template <typename T, bool LDS>
+template <typename T>
 __global__ void __launch_bounds__(kLtT) k_apply_LT(const double* __restrict__ uv, int J, int nsub, Batch mb, int per,
                                                    const T* __restrict__ img, T* __restrict__ s_all) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int m = blockIdx.y, ns = mb.ns[m], n2 = nsub * nsub, tid = threadIdx.x;
   T* s = s_all + mb.off[m];
-  T* acc = LDS ? reinterpret_cast<T*>(smem) : s;
-  if (LDS) {
-    for (int i = tid; i < ns * ns; i += kLtT) acc[i] = (T)0;
-    __syncthreads();
-  }
+  T* acc = reinterpret_cast<T*>(smem);
+  for (int i = tid; i < ns * ns; i += kLtT) acc[i] = (T)0;
+  __syncthreads();
   const int lo = (int)blockIdx.x * per;   // per: a multiple of 64
   for (int i = tid; i < per; i += kLtT) {
     const int j = lo + (i & 63) * (per >> 6) + (i >> 6);
     if (j >= J) continue;
-    const T val = img[(long)m * J + j] / (T)n2;
-    const UV* p = reinterpret_cast<const UV*>(uv) + ((long)m * J + j) * n2;
-    for (int k = 0; k < n2; ++k) {
-      const UV q = p[k];
-      int cell;
-      double fx, fy;
-      if (!grid_cell(q.u, q.v, ns, cell, fx, fy)) continue;
-      const T tx = (T)fx, ty = (T)fy;
-      atomicAdd(&acc[cell], (1 - tx) * (1 - ty) * val);
-      atomicAdd(&acc[cell + 1], tx * (1 - ty) * val);
-      atomicAdd(&acc[cell + ns], (1 - tx) * ty * val);
-      atomicAdd(&acc[cell + ns + 1], tx * ty * val);
-    }
+    add_pixel(reinterpret_cast<const UV*>(uv) + ((long)m * J + j) * n2, n2, ns, img[(long)m * J + j] / (T)n2, acc);
   }
-  if (LDS) {
-    __syncthreads();
-    for (int i = tid; i < ns * ns; i += kLtT) {
-      const T v = acc[i];
-      if (v != (T)0) atomicAdd(&s[i], v);   // (true for NaN)
-    }
+  __syncthreads();
+  for (int i = tid; i < ns * ns; i += kLtT) {
+    const T v = acc[i];
+    if (v != (T)0) atomicAdd(&s[i], v);   // (true for NaN)
   }
+}
+
+// The same for grids whose copy does not fit in LDS: a thread per pixel, every
+// term to memory.  (About 256 blocks whose lanes took pixels far apart, as the
+// LDS form's do, were slower than this: a 1024 x 1024 image with 512 x 512 nodes 867
+// against 541 us.)
+template <typename T>
+__global__ void __launch_bounds__(256) k_apply_LT_mem(const double* __restrict__ uv, int J, int nsub, Batch mb,
+                                                      const T* __restrict__ img, T* __restrict__ s_all) {
+  const int j = blockIdx.x * 256 + threadIdx.x, m = blockIdx.y, n2 = nsub * nsub;
+  if (j >= J) return;
+  add_pixel(reinterpret_cast<const UV*>(uv) + ((long)m * J + j) * n2, n2, mb.ns[m], img[(long)m * J + j] / (T)n2,
+            s_all + mb.off[m]);
 }
 
 // Ordered L^T (fixed summation order).  A counting sort by node of the keys
@@ -558,8 +570,7 @@ static int apply_LT_impl(const double* uv, int n_members, const sl_image_grid* i
   long total = 0;
   for (int m = 0; m < n_members; ++m) total += (long)ns[m] * ns[m];
   hipLaunchKernelGGL(k_fill<T>, dim3(nblocks(total, 256)), dim3(256), 0, st, (T*)s, total, (T)0);
-  SL_HIP(hipFuncSetAttribute((const void*)k_apply_LT<T, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)kLtLds));
+  SL_HIP(hipFuncSetAttribute((const void*)k_apply_LT<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLtLds));
   for_batches(ns, n_members, [&](int) { return (long)J + kLtT; }, [&](int m0, const Batch& mb, int n, int big) {
     const size_t lds = sizeof(T) * (size_t)big * big;
     // about 256 blocks over the batch, each with at least two pixels a thread: every block adds its nodes to
@@ -569,10 +580,10 @@ static int apply_LT_impl(const double* uv, int n_members, const sl_image_grid* i
     const dim3 grid(nblocks(J, per), n);
     const double* uvm = uv + (long)m0 * J * n2 * 2;
     if (lds <= kLtLds)
-      hipLaunchKernelGGL((k_apply_LT<T, true>), grid, dim3(kLtT), lds, st, uvm, J, img->nsub, mb, per,
+      hipLaunchKernelGGL(k_apply_LT<T>, grid, dim3(kLtT), lds, st, uvm, J, img->nsub, mb, per,
                          (const T*)in + (long)m0 * J, (T*)s);
     else
-      hipLaunchKernelGGL((k_apply_LT<T, false>), grid, dim3(kLtT), 0, st, uvm, J, img->nsub, mb, per,
+      hipLaunchKernelGGL(k_apply_LT_mem<T>, dim3(nblocks(J, 256), n), dim3(256), 0, st, uvm, J, img->nsub, mb,
                          (const T*)in + (long)m0 * J, (T*)s);
   });
   return check_launch("k_apply_LT");

@@ -1,0 +1,49 @@
+"""Which form of L^T a call takes (its launches, read from a captured graph), and its values there.
+
+sl_apply_LT adds a member's terms in an LDS copy of its source grid where that
+fits, else by a thread per pixel straight to memory.  Values against the FP64
+oracle within 2 (terms + 4) u of the sum of absolute terms, as in the
+operators' test (which explains the bound).
+"""
+import numpy as np
+import pytest
+import torch
+
+import synthgen
+from captured import kernel_launches
+from oracle import lens as olens
+from oracle import operators as oops
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+U = {torch.float32: 2.0 ** -24, torch.float64: 2.0 ** -53}
+
+
+def _call(nx, nsub, ns, dtype, ordered=False, check=()):
+    import paper_1101_5803_amd as sl
+    grid = sl.Grid(nx, nx, 4.0 / nx, nsub)
+    G = synthgen.population(11, len(ns))
+    img = np.random.default_rng(nx).standard_normal((len(ns), grid.J)).astype(np.float32).astype(np.float64)
+    uv = sl.lens_trace(torch.tensor(G, device=DEV), grid, ns, 1.0)
+    it = torch.tensor(img, dtype=dtype, device=DEV)
+    call = lambda: (sl.apply_LT_ordered if ordered else sl.apply_LT)(uv, grid, ns, it)
+    got = call().double().cpu().numpy()
+    off = np.concatenate([[0], np.cumsum(np.square(ns))])
+    for m in check:
+        idx, w, inside = oops.bilinear_table(*olens.trace_image(G[m], nx, nx, grid.pix, nsub), ns[m], 1.0)
+        if dtype == torch.float32:   # the fractions that the FP32 operator holds
+            fx, fy = ((w[..., a] + w[..., 3]).astype(np.float32).astype(np.float64) for a in (1, 2))
+            w = np.where(inside[..., None], np.stack([(1 - fx) * (1 - fy), fx * (1 - fy), (1 - fx) * fy, fx * fy], -1), 0.0)
+        tab = (idx, w, inside)
+        ref, ones = (oops.apply_LT(tab, v, ns[m] ** 2, nsub) for v in (img[m], np.abs(img[m])))
+        cnt = np.bincount(np.asarray(idx).reshape(-1), minlength=ns[m] ** 2)
+        bound = 2 * (cnt + 4) * U[dtype] * ones + 64 * ns[m] * U[torch.float64] * cnt * np.abs(img[m]).max()
+        assert np.all(np.abs(got[off[m]:off[m + 1]] - ref) <= bound), m
+    return kernel_launches(call)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_large_grid_has_a_thread_per_pixel(dtype):
+    """A grid that LDS cannot hold: as many threads as pixels, not a few blocks that walk them."""
+    (grid, block, lds) = _call(512, 1, [200], dtype, check=(0,))[-1]
+    assert lds == 0 and grid[0] * block[0] >= 512 * 512
