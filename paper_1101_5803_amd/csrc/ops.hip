@@ -101,27 +101,29 @@ __global__ void __launch_bounds__(256) k_apply_L(const double* __restrict__ uv, 
 }
 
 // Adds the four terms of each of a pixel's subpixels to acc.
-template <typename T>
-__device__ __forceinline__ void add_pixel(const UV* __restrict__ p, int n2, int ns, T val, T* acc) {
+template <typename T, typename A>
+__device__ __forceinline__ void add_pixel(const UV* __restrict__ p, int n2, int ns, T val, A* acc) {
   for (int k = 0; k < n2; ++k) {
     const UV q = p[k];
     int cell;
     double fx, fy;
     if (!grid_cell(q.u, q.v, ns, cell, fx, fy)) continue;
     const T tx = (T)fx, ty = (T)fy;
-    atomicAdd(&acc[cell], (1 - tx) * (1 - ty) * val);
-    atomicAdd(&acc[cell + 1], tx * (1 - ty) * val);
-    atomicAdd(&acc[cell + ns], (1 - tx) * ty * val);
-    atomicAdd(&acc[cell + ns + 1], tx * ty * val);
+    atomicAdd(&acc[cell], (A)((1 - tx) * (1 - ty) * val));
+    atomicAdd(&acc[cell + 1], (A)(tx * (1 - ty) * val));
+    atomicAdd(&acc[cell + ns], (A)((1 - tx) * ty * val));
+    atomicAdd(&acc[cell + ns + 1], (A)(tx * ty * val));
   }
 }
 
 // L^T of part of one member's pixels: the terms are added in an LDS copy of the
 // member's source grid first and only its nonzero nodes go to memory, where
 // atomics across the XCDs run at about 36 G/s (every term there: 285 us for 16
-// members of a 128 x 128 image, 4.2 M terms; LDS: 19 us).  The lanes of a wave
-// take pixels n/64 apart, so that a magnified region's neighbouring pixels, which
-// share nodes, do not meet in one LDS access.
+// members of a 128 x 128 image, 4.2 M terms; so 13 us).  The copy is FP64 for both
+// types: ds_add_f32 takes two cycles a lane where ds_add_f64 takes a fraction of
+// one (19 us for those 16 members with an FP32 copy, and one 64 x 64 image 22
+// against 6 us).  The lanes of a wave take pixels n/64 apart, so that a magnified
+// region's neighbouring pixels, which share nodes, do not meet in one LDS access.
 constexpr int kLtT = 512;
 template <typename T>
 __global__ void __launch_bounds__(kLtT) k_apply_LT(const double* __restrict__ uv, int J, int nsub, Batch mb, int per,
@@ -129,8 +131,8 @@ __global__ void __launch_bounds__(kLtT) k_apply_LT(const double* __restrict__ uv
   extern __shared__ __align__(16) unsigned char smem[];
   const int m = blockIdx.y, ns = mb.ns[m], n2 = nsub * nsub, tid = threadIdx.x;
   T* s = s_all + mb.off[m];
-  T* acc = reinterpret_cast<T*>(smem);
-  for (int i = tid; i < ns * ns; i += kLtT) acc[i] = (T)0;
+  double* acc = reinterpret_cast<double*>(smem);
+  for (int i = tid; i < ns * ns; i += kLtT) acc[i] = 0.0;
   __syncthreads();
   const int lo = (int)blockIdx.x * per;   // per: a multiple of 64
   for (int i = tid; i < per; i += kLtT) {
@@ -140,8 +142,8 @@ __global__ void __launch_bounds__(kLtT) k_apply_LT(const double* __restrict__ uv
   }
   __syncthreads();
   for (int i = tid; i < ns * ns; i += kLtT) {
-    const T v = acc[i];
-    if (v != (T)0) atomicAdd(&s[i], v);   // (true for NaN)
+    const double v = acc[i];
+    if (v != 0.0) atomicAdd(&s[i], (T)v);   // (true for NaN)
   }
 }
 
@@ -560,8 +562,10 @@ static int apply_L_impl(const double* uv, int n_members, const sl_image_grid* im
   return check_launch("k_apply_L");
 }
 
-// Largest LDS copy of a source grid (two blocks of 512 threads still fit on a CU).
-constexpr size_t kLtLds = 78 * 1024;
+// Largest LDS copy of a source grid: up to 78 KB two blocks of 512 threads share a
+// CU, up to 158 KB (142 nodes a side) one has it alone, which still beats the
+// atomics in memory.
+constexpr size_t kLtLds = 158 * 1024;
 
 template <typename T>
 static int apply_LT_impl(const double* uv, int n_members, const sl_image_grid* img, const int32_t* ns,
@@ -572,7 +576,7 @@ static int apply_LT_impl(const double* uv, int n_members, const sl_image_grid* i
   hipLaunchKernelGGL(k_fill<T>, dim3(nblocks(total, 256)), dim3(256), 0, st, (T*)s, total, (T)0);
   SL_HIP(hipFuncSetAttribute((const void*)k_apply_LT<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLtLds));
   for_batches(ns, n_members, [&](int) { return (long)J + kLtT; }, [&](int m0, const Batch& mb, int n, int big) {
-    const size_t lds = sizeof(T) * (size_t)big * big;
+    const size_t lds = sizeof(double) * (size_t)big * big;
     // about 256 blocks over the batch, each with at least two pixels a thread: every block adds its nodes to
     // memory, so more of them cost more atomics than they save
     const int want = std::max(1, std::min((256 + n - 1) / n, (J + 2 * kLtT - 1) / (2 * kLtT)));
@@ -606,6 +610,9 @@ static size_t lt_ordered_ws(const sl_image_grid* img, const int32_t* ns, int n_m
   return sizeof(int) * (size_t)(g * ordered_ints(I, 4L * img->nx * img->ny * img->nsub * img->nsub));
 }
 
+// Largest LDS histogram of a source grid (two blocks of 512 threads still fit on a CU).
+constexpr size_t kBinLds = 78 * 1024;
+
 template <bool LDS>
 static void launch_bins(const double* uv, long nsp, const Batch& mb, int n, size_t lds, int* ws, long I_max,
                         hipStream_t st) {
@@ -625,9 +632,9 @@ static int apply_LT_ordered_impl(const double* uv, int n_members, const sl_image
   long I_max = 0;
   const int group = (int)ordered_group(img, ns, n_members, &I_max);
   SL_HIP(hipFuncSetAttribute((const void*)k_lt_bin<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)kLtLds));
+                             (int)kBinLds));
   SL_HIP(hipFuncSetAttribute((const void*)k_lt_bin<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)kLtLds));
+                             (int)kBinLds));
   long off = 0;
   for (int m0 = 0; m0 < n_members; m0 += group) {
     const int n = std::min(group, n_members - m0);
@@ -643,7 +650,7 @@ static int apply_LT_ordered_impl(const double* uv, int n_members, const sl_image
     int* w = (int*)ws;
     hipLaunchKernelGGL(k_lt_zero, dim3(nblocks((long)big * big, 256), n), dim3(256), 0, st, mb, w, I_max, 4 * nsp);
     const size_t lds = sizeof(int) * (size_t)big * big;
-    if (lds <= kLtLds) launch_bins<true>(uvm, nsp, mb, n, lds, w, I_max, st);
+    if (lds <= kBinLds) launch_bins<true>(uvm, nsp, mb, n, lds, w, I_max, st);
     else launch_bins<false>(uvm, nsp, mb, n, 0, w, I_max, st);
     hipLaunchKernelGGL(k_lt_gather<T>, dim3(nblocks((long)big * big, kGatherW), n), dim3(64 * kGatherW), 0, st, uvm,
                        n2, nsp, mb, w, I_max, (const T*)in + (long)m0 * J, (T*)s);

@@ -47,3 +47,11 @@ def test_large_grid_has_a_thread_per_pixel(dtype):
     """A grid that LDS cannot hold: as many threads as pixels, not a few blocks that walk them."""
     (grid, block, lds) = _call(512, 1, [200], dtype, check=(0,))[-1]
     assert lds == 0 and grid[0] * block[0] >= 512 * 512
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("nx,ns", [(64, 64), (96, 99), (32, 142)])
+def test_lds_copy_is_fp64(nx, ns, dtype):
+    """ds_add_f32 takes several times as long as ds_add_f64, so both types add in FP64 copies."""
+    (_, _, lds) = _call(nx, 2, [ns], dtype, check=(0,))[-1]
+    assert lds == 8 * ns * ns
