@@ -31,6 +31,12 @@ struct Batch {
   long off[kBatch];
 };
 
+// The same for a launch of some members of the call, and which ones they are.
+struct Picked {
+  int ns[kBatch], id[kBatch];
+  long off[kBatch];
+};
+
 // A subpixel's (u, v): 16 bytes in one access, 8-byte aligned as the caller's array.
 struct alignas(8) UV {
   double u, v;
@@ -126,11 +132,11 @@ __device__ __forceinline__ void add_pixel(const UV* __restrict__ p, int n2, int 
 // region's neighbouring pixels, which share nodes, do not meet in one LDS access.
 constexpr int kLtT = 512;
 template <typename T>
-__global__ void __launch_bounds__(kLtT) k_apply_LT(const double* __restrict__ uv, int J, int nsub, Batch mb, int per,
+__global__ void __launch_bounds__(kLtT) k_apply_LT(const double* __restrict__ uv, int J, int nsub, Picked mb, int per,
                                                    const T* __restrict__ img, T* __restrict__ s_all) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int m = blockIdx.y, ns = mb.ns[m], n2 = nsub * nsub, tid = threadIdx.x;
-  T* s = s_all + mb.off[m];
+  const int m = mb.id[blockIdx.y], ns = mb.ns[blockIdx.y], n2 = nsub * nsub, tid = threadIdx.x;
+  T* s = s_all + mb.off[blockIdx.y];
   double* acc = reinterpret_cast<double*>(smem);
   for (int i = tid; i < ns * ns; i += kLtT) acc[i] = 0.0;
   __syncthreads();
@@ -152,12 +158,12 @@ __global__ void __launch_bounds__(kLtT) k_apply_LT(const double* __restrict__ uv
 // LDS form's do, were slower than this: a 1024 x 1024 image with 512 x 512 nodes 867
 // against 541 us.)
 template <typename T>
-__global__ void __launch_bounds__(256) k_apply_LT_mem(const double* __restrict__ uv, int J, int nsub, Batch mb,
+__global__ void __launch_bounds__(256) k_apply_LT_mem(const double* __restrict__ uv, int J, int nsub, Picked mb,
                                                       const T* __restrict__ img, T* __restrict__ s_all) {
-  const int j = blockIdx.x * 256 + threadIdx.x, m = blockIdx.y, n2 = nsub * nsub;
+  const int j = blockIdx.x * 256 + threadIdx.x, m = mb.id[blockIdx.y], n2 = nsub * nsub;
   if (j >= J) return;
-  add_pixel(reinterpret_cast<const UV*>(uv) + ((long)m * J + j) * n2, n2, mb.ns[m], img[(long)m * J + j] / (T)n2,
-            s_all + mb.off[m]);
+  add_pixel(reinterpret_cast<const UV*>(uv) + ((long)m * J + j) * n2, n2, mb.ns[blockIdx.y],
+            img[(long)m * J + j] / (T)n2, s_all + mb.off[blockIdx.y]);
 }
 
 // Ordered L^T (fixed summation order).  A counting sort by node of the keys
@@ -180,10 +186,10 @@ __device__ __forceinline__ OrderedWs ordered_ws(int* ws, int m, long I_max, long
 // any order).  With LDS, a block counts its subpixels per node there first and
 // takes each node's places with one atomic in memory.
 template <bool FILL, bool LDS>
-__global__ void __launch_bounds__(kLtT) k_lt_bin(const double* __restrict__ uv, long nsubpix, Batch mb, int per,
+__global__ void __launch_bounds__(kLtT) k_lt_bin(const double* __restrict__ uv, long nsubpix, Picked mb, int per,
                                                  int* __restrict__ ws, long I_max) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int m = blockIdx.y, ns = mb.ns[m], tid = threadIdx.x;
+  const int m = mb.id[blockIdx.y], ns = mb.ns[blockIdx.y], tid = threadIdx.x;
   const OrderedWs w = ordered_ws(ws, m, I_max, 4 * nsubpix);
   int* total = FILL ? w.cur : w.cnt;
   int* h = LDS ? reinterpret_cast<int*>(smem) : total;
@@ -562,33 +568,66 @@ static int apply_L_impl(const double* uv, int n_members, const sl_image_grid* im
   return check_launch("k_apply_L");
 }
 
-// Largest LDS copy of a source grid: up to 78 KB two blocks of 512 threads share a
-// CU, up to 158 KB (142 nodes a side) one has it alone, which still beats the
-// atomics in memory.
+// Calls launch(batch, members of the batch, largest side) for batches of the
+// members whose side is at most `cut` (below = true) or more (false), each of at
+// most kBatch members and 2^31 threads (`threads` of one member).
+template <typename Launch>
+static void for_picked(const int32_t* ns, int n_members, int cut, bool below, long threads, Launch launch) {
+  const int most = (int)std::max(1L, std::min((long)kBatch, (1L << 31) / threads));
+  long off = 0;
+  Picked mb;
+  int n = 0, big = 0;
+  for (int m = 0; m < n_members; ++m) {
+    if ((ns[m] <= cut) == below) {
+      mb.ns[n] = ns[m];
+      mb.id[n] = m;
+      mb.off[n] = off;
+      big = std::max(big, (int)ns[m]);
+      if (++n == most) {
+        launch(mb, n, big);
+        n = big = 0;
+      }
+    }
+    off += (long)ns[m] * ns[m];
+  }
+  if (n > 0) launch(mb, n, big);
+}
+
+// Largest side of a grid whose copy of `size` bytes per node fits in `lds` bytes.
+static int side_that_fits(size_t lds, size_t size) {
+  int n = 1;
+  while (size * (n + 1) * (n + 1) <= lds) ++n;
+  return n;
+}
+
+// Each member takes the form that its own grid allows: with the batch's largest
+// grid deciding, one member of 150 nodes a side sent 62 of 40 to the memory
+// atomics (128 x 128 image, 2 x 2 subpixels: 482 us; 44 so, and 2.7 -> 1.4 ms for the
+// ordered form, which bins by the same rule).  Up to 78 KB of LDS two blocks of
+// 512 threads share a CU, up to 158 KB (142 nodes) one has it alone, which still
+// beats the atomics in memory.
 constexpr size_t kLtLds = 158 * 1024;
 
 template <typename T>
 static int apply_LT_impl(const double* uv, int n_members, const sl_image_grid* img, const int32_t* ns,
                          const void* in, void* s, hipStream_t st) {
-  const int J = img->nx * img->ny, n2 = img->nsub * img->nsub;
+  const int J = img->nx * img->ny;
   long total = 0;
   for (int m = 0; m < n_members; ++m) total += (long)ns[m] * ns[m];
   hipLaunchKernelGGL(k_fill<T>, dim3(nblocks(total, 256)), dim3(256), 0, st, (T*)s, total, (T)0);
   SL_HIP(hipFuncSetAttribute((const void*)k_apply_LT<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLtLds));
-  for_batches(ns, n_members, [&](int) { return (long)J + kLtT; }, [&](int m0, const Batch& mb, int n, int big) {
-    const size_t lds = sizeof(double) * (size_t)big * big;
+  static const int cut = side_that_fits(kLtLds, sizeof(double));
+  for_picked(ns, n_members, cut, true, (long)J + kLtT, [&](const Picked& mb, int n, int big) {
     // about 256 blocks over the batch, each with at least two pixels a thread: every block adds its nodes to
     // memory, so more of them cost more atomics than they save
     const int want = std::max(1, std::min((256 + n - 1) / n, (J + 2 * kLtT - 1) / (2 * kLtT)));
     const int per = ((J + want - 1) / want + 63) / 64 * 64;
-    const dim3 grid(nblocks(J, per), n);
-    const double* uvm = uv + (long)m0 * J * n2 * 2;
-    if (lds <= kLtLds)
-      hipLaunchKernelGGL(k_apply_LT<T>, grid, dim3(kLtT), lds, st, uvm, J, img->nsub, mb, per,
-                         (const T*)in + (long)m0 * J, (T*)s);
-    else
-      hipLaunchKernelGGL(k_apply_LT_mem<T>, dim3(nblocks(J, 256), n), dim3(256), 0, st, uvm, J, img->nsub, mb,
-                         (const T*)in + (long)m0 * J, (T*)s);
+    hipLaunchKernelGGL(k_apply_LT<T>, dim3(nblocks(J, per), n), dim3(kLtT), sizeof(double) * (size_t)big * big, st, uv,
+                       J, img->nsub, mb, per, (const T*)in, (T*)s);
+  });
+  for_picked(ns, n_members, cut, false, (long)J + 256, [&](const Picked& mb, int n, int) {
+    hipLaunchKernelGGL(k_apply_LT_mem<T>, dim3(nblocks(J, 256), n), dim3(256), 0, st, uv, J, img->nsub, mb,
+                       (const T*)in, (T*)s);
   });
   return check_launch("k_apply_LT");
 }
@@ -613,15 +652,21 @@ static size_t lt_ordered_ws(const sl_image_grid* img, const int32_t* ns, int n_m
 // Largest LDS histogram of a source grid (two blocks of 512 threads still fit on a CU).
 constexpr size_t kBinLds = 78 * 1024;
 
-template <bool LDS>
-static void launch_bins(const double* uv, long nsp, const Batch& mb, int n, size_t lds, int* ws, long I_max,
-                        hipStream_t st) {
-  const int want = (int)std::max(1L, std::min((256L + n - 1) / n, (nsp + 8L * kLtT - 1) / (8L * kLtT)));
-  const int per = (int)((nsp + want - 1) / want);
-  const dim3 grid(nblocks(nsp, per), n);
-  hipLaunchKernelGGL((k_lt_bin<false, LDS>), grid, dim3(kLtT), lds, st, uv, nsp, mb, per, ws, I_max);
-  hipLaunchKernelGGL(k_lt_scan, dim3(n), dim3(1024), 0, st, mb, ws, I_max, 4 * nsp);
-  hipLaunchKernelGGL((k_lt_bin<true, LDS>), grid, dim3(kLtT), lds, st, uv, nsp, mb, per, ws, I_max);
+// One pass of k_lt_bin over a group of members, each in the form its grid allows.
+template <bool FILL>
+static void launch_bins(const double* uv, long nsp, const int32_t* ns, int n, int* ws, long I_max, hipStream_t st) {
+  static const int cut = side_that_fits(kBinLds, sizeof(int));
+  for (const bool lds : {true, false})
+    for_picked(ns, n, cut, lds, nsp + kLtT, [&](const Picked& mb, int np, int big) {
+      const int want = (int)std::max(1L, std::min((256L + np - 1) / np, (nsp + 8L * kLtT - 1) / (8L * kLtT)));
+      const int per = (int)((nsp + want - 1) / want);
+      const dim3 grid(nblocks(nsp, per), np);
+      if (lds)
+        hipLaunchKernelGGL((k_lt_bin<FILL, true>), grid, dim3(kLtT), sizeof(int) * (size_t)big * big, st, uv, nsp, mb,
+                           per, ws, I_max);
+      else
+        hipLaunchKernelGGL((k_lt_bin<FILL, false>), grid, dim3(kLtT), 0, st, uv, nsp, mb, per, ws, I_max);
+    });
 }
 
 template <typename T>
@@ -649,9 +694,9 @@ static int apply_LT_ordered_impl(const double* uv, int n_members, const sl_image
     const double* uvm = uv + (long)m0 * nsp * 2;
     int* w = (int*)ws;
     hipLaunchKernelGGL(k_lt_zero, dim3(nblocks((long)big * big, 256), n), dim3(256), 0, st, mb, w, I_max, 4 * nsp);
-    const size_t lds = sizeof(int) * (size_t)big * big;
-    if (lds <= kBinLds) launch_bins<true>(uvm, nsp, mb, n, lds, w, I_max, st);
-    else launch_bins<false>(uvm, nsp, mb, n, 0, w, I_max, st);
+    launch_bins<false>(uvm, nsp, ns + m0, n, w, I_max, st);
+    hipLaunchKernelGGL(k_lt_scan, dim3(n), dim3(1024), 0, st, mb, w, I_max, 4 * nsp);
+    launch_bins<true>(uvm, nsp, ns + m0, n, w, I_max, st);
     hipLaunchKernelGGL(k_lt_gather<T>, dim3(nblocks((long)big * big, kGatherW), n), dim3(64 * kGatherW), 0, st, uvm,
                        n2, nsp, mb, w, I_max, (const T*)in + (long)m0 * J, (T*)s);
     if (int e = check_launch("ordered L^T")) return e;

@@ -55,3 +55,14 @@ def test_lds_copy_is_fp64(nx, ns, dtype):
     """ds_add_f32 takes several times as long as ds_add_f64, so both types add in FP64 copies."""
     (_, _, lds) = _call(nx, 2, [ns], dtype, check=(0,))[-1]
     assert lds == 8 * ns * ns
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_each_member_takes_its_own_form(dtype):
+    """One grid past LDS among small ones: they keep their LDS form, whatever the order."""
+    ns = [40] * 10 + [150] + [38] * 20
+    launches = _call(64, 2, ns, dtype, check=(0, 10, 11, 30))
+    assert sorted((g[1], lds > 0) for g, b, lds in launches if b[0] in (256, 512))[-2:] == [(1, False), (30, True)]
+    # the ordered form's two binning passes, in the LDS and the memory form each
+    bins = [(g[1], lds > 0) for g, b, lds in _call(64, 2, ns, dtype, ordered=True, check=(0, 10, 11, 30)) if b[0] == 512]
+    assert sorted(bins) == [(1, False), (1, False), (30, True), (30, True)]
