@@ -118,11 +118,12 @@ int sl_apply_LT(int dtype, const double* uv, int n_members, const sl_image_grid*
  * every node's terms added in ascending (pixel, subpixel, corner) order --
  * the order of a sequential scatter over the image -- so the result is
  * bitwise reproducible.  The terms of each node are found by a counting sort
- * in `workspace` (device, 4-byte aligned, at least
- * sl_apply_LT_ordered_workspace_size(img, ns, n_members) bytes; contents
- * need not be initialised; calls sharing it must not overlap).  Other
- * arguments as sl_apply_LT.  The workspace-size query returns 0 for invalid
- * arguments.
+ * in `workspace` (device, 4-byte aligned; contents need not be initialised;
+ * calls sharing it must not overlap).  The query gives the size for members
+ * taken up to 64 at a time (as many as 256 MB hold); any workspace of at least
+ * the size for one member with the call's largest grid is accepted, and holds
+ * that many members at a time.  Other arguments as sl_apply_LT.  The
+ * workspace-size query returns 0 for invalid arguments.
  */
 size_t sl_apply_LT_ordered_workspace_size(const sl_image_grid* img, const int32_t* ns, int n_members);
 int sl_apply_LT_ordered(int dtype, const double* uv, int n_members, const sl_image_grid* img,

@@ -634,18 +634,20 @@ static int apply_LT_impl(const double* uv, int n_members, const sl_image_grid* i
 
 // Workspace of the ordered L^T: per member (I + 1) + 2 I ints of counts, row
 // starts and cursors and 4 J n^2 keys, all sized for the largest grid, for as
-// many members at a time as fit in 256 MB (at least one).
-static long ordered_group(const sl_image_grid* img, const int32_t* ns, int n_members, long* I_max) {
+// many members at a time as fit in `limit` bytes (at least one).
+static long ordered_group(const sl_image_grid* img, const int32_t* ns, int n_members, size_t limit, long* I_max) {
   long I = 0;
   for (int m = 0; m < n_members; ++m) I = std::max(I, (long)ns[m] * ns[m]);
   *I_max = I;
-  const long bytes = 4 * ordered_ints(I, 4L * img->nx * img->ny * img->nsub * img->nsub);
-  return std::max(1L, std::min({(long)n_members, (long)kBatch, (256L << 20) / bytes}));
+  const size_t bytes = sizeof(int) * ordered_ints(I, 4L * img->nx * img->ny * img->nsub * img->nsub);
+  return std::max(1L, std::min({(long)n_members, (long)kBatch, (long)(limit / bytes)}));
 }
 
-static size_t lt_ordered_ws(const sl_image_grid* img, const int32_t* ns, int n_members) {
+constexpr size_t kOrderedWs = 256u << 20;   // the most that the query asks for, beyond one member's
+
+static size_t lt_ordered_ws(const sl_image_grid* img, const int32_t* ns, int n_members, size_t limit) {
   long I = 0;
-  const long g = ordered_group(img, ns, n_members, &I);
+  const long g = ordered_group(img, ns, n_members, limit, &I);
   return sizeof(int) * (size_t)(g * ordered_ints(I, 4L * img->nx * img->ny * img->nsub * img->nsub));
 }
 
@@ -671,11 +673,11 @@ static void launch_bins(const double* uv, long nsp, const int32_t* ns, int n, in
 
 template <typename T>
 static int apply_LT_ordered_impl(const double* uv, int n_members, const sl_image_grid* img, const int32_t* ns,
-                                 const void* in, void* s, void* ws, hipStream_t st) {
+                                 const void* in, void* s, void* ws, size_t ws_bytes, hipStream_t st) {
   const int J = img->nx * img->ny, n2 = img->nsub * img->nsub;
   const long nsp = (long)J * n2;
   long I_max = 0;
-  const int group = (int)ordered_group(img, ns, n_members, &I_max);
+  const int group = (int)ordered_group(img, ns, n_members, ws_bytes, &I_max);
   SL_HIP(hipFuncSetAttribute((const void*)k_lt_bin<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)kBinLds));
   SL_HIP(hipFuncSetAttribute((const void*)k_lt_bin<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -838,7 +840,7 @@ int sl_apply_LT(int dtype, const double* uv, int n_members, const sl_image_grid*
 
 size_t sl_apply_LT_ordered_workspace_size(const sl_image_grid* img, const int32_t* ns, int n_members) {
   if (check_grid(img) != SL_OK || check_ns(ns, n_members) != SL_OK) return 0;
-  return lt_ordered_ws(img, ns, n_members);
+  return lt_ordered_ws(img, ns, n_members, kOrderedWs);
 }
 
 int sl_apply_LT_ordered(int dtype, const double* uv, int n_members, const sl_image_grid* img, const int32_t* ns,
@@ -848,12 +850,14 @@ int sl_apply_LT_ordered(int dtype, const double* uv, int n_members, const sl_ima
   SL_REQUIRE(uv && img_in && s_out && workspace, "NULL device pointer");
   SL_REQUIRE(((uintptr_t)workspace & 3) == 0, "workspace must be 4-byte aligned");
   SL_REQUIRE(4L * img->nx * img->ny * img->nsub * img->nsub < (1L << 31), "image too large for 32-bit keys");
-  const size_t need = lt_ordered_ws(img, ns, n_members);
+  const size_t need = lt_ordered_ws(img, ns, n_members, 0);   // one member at a time
   SL_REQUIRE(workspace_bytes >= need, "workspace too small: %zu < %zu bytes", workspace_bytes, need);
   if (dtype == SL_F32)
-    return apply_LT_ordered_impl<float>(uv, n_members, img, ns, img_in, s_out, workspace, (hipStream_t)stream);
+    return apply_LT_ordered_impl<float>(uv, n_members, img, ns, img_in, s_out, workspace, workspace_bytes,
+                                        (hipStream_t)stream);
   if (dtype == SL_F64)
-    return apply_LT_ordered_impl<double>(uv, n_members, img, ns, img_in, s_out, workspace, (hipStream_t)stream);
+    return apply_LT_ordered_impl<double>(uv, n_members, img, ns, img_in, s_out, workspace, workspace_bytes,
+                                        (hipStream_t)stream);
   SL_REQUIRE(false, "unknown dtype %d", dtype);
 }
 
