@@ -274,10 +274,13 @@ __global__ void __launch_bounds__(1024) k_lt_scan(Batch mb, int* __restrict__ ws
 
 // One wave per node.  Its keys are distinct, so a key's rank is the count of
 // smaller ones: up to kSortCap of them at a time in LDS.  A longer row is taken
-// in ascending ranges of keys that hold no more than that.  (With one thread
-// per node sorting its segment in memory by insertion, and five launches per
-// member, a chain of operators with the ordered L^T took 81 ms for 16 members
-// of a 128 x 128 image; 0.36 ms so.)
+// in ascending ranges of keys that hold no more than that, a range half as wide
+// as one that held more and twice as wide after one that held less than half
+// (each range scans the row: with widths that only shrank, a row of 3001 keys in
+// one dense cluster among 4 M was scanned some 3000 times).  (With one thread per
+// node sorting its segment in memory by insertion, and five launches per member,
+// a chain of operators with the ordered L^T took 81 ms for 16 members of a 128 x
+// 128 image; 0.36 ms so.)
 constexpr int kSortCap = 512, kGatherW = 4;
 template <typename T>
 __global__ void __launch_bounds__(64 * kGatherW) k_lt_gather(const double* __restrict__ uv, int n2, long nsubpix,
@@ -339,6 +342,7 @@ __global__ void __launch_bounds__(64 * kGatherW) k_lt_gather(const double* __res
     for (int x = 0; x < c; ++x) acc += tw[x] * tv[x];
     wave_sync();
     lo = hi;
+    if (c <= kSortCap / 2) width <<= 1;
   }
   if (lane == 0) s[mb.off[m] + i] = acc;
 }
