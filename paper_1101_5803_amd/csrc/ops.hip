@@ -8,6 +8,7 @@
 // chip idle and cost 16 members of a 128 x 128 image 48 launches per operator
 // chain (trace 74, L 58, L^T 285 and H^T H 63 us in all).
 #include <algorithm>
+#include <climits>
 #include <cstdarg>
 #include <vector>
 
@@ -282,29 +283,41 @@ __global__ void __launch_bounds__(1024) k_lt_scan(Batch mb, int* __restrict__ ws
 // a chain of operators with the ordered L^T took 81 ms for 16 members of a 128 x
 // 128 image; 0.36 ms so.)
 constexpr int kSortCap = 512, kGatherW = 4;
+
+// What a row's gather reads, and this wave's LDS.
 template <typename T>
-__global__ void __launch_bounds__(64 * kGatherW) k_lt_gather(const double* __restrict__ uv, int n2, long nsubpix,
-                                                             Batch mb, int* __restrict__ ws, long I_max,
-                                                             const T* __restrict__ img, T* __restrict__ s) {
-  __shared__ int ks_[kGatherW][kSortCap];
-  __shared__ T tw_[kGatherW][kSortCap], tv_[kGatherW][kSortCap];
-  const int m = blockIdx.y, ns = mb.ns[m], lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kGatherW + wid));
-  if (i >= ns * ns) return;
-  int* ks = ks_[wid];
-  T *tw = tw_[wid], *tv = tv_[wid];
-  const OrderedWs w = ordered_ws(ws, m, I_max, 4 * nsubpix);
-  const int* keys = w.keys + w.ptr[i];
-  const int n = w.ptr[i + 1] - w.ptr[i];
-  const UV* p = reinterpret_cast<const UV*>(uv) + m * nsubpix;
-  img += (long)m * (nsubpix / n2);
+struct RowView {
+  const UV* p;
+  const T* img;
+  int ns, n2;
+  int* ks;
+  T *tw, *tv;
+};
+
+// Weight and value of a key's term.
+template <typename T>
+__device__ __forceinline__ void row_term(const RowView<T>& o, int key, T& w, T& v) {
+  const long t = key >> 2;
+  const UV q = o.p[t];
+  int cell;
+  double fx, fy;
+  grid_cell(q.u, q.v, o.ns, cell, fx, fy);
+  const T tx = (T)fx, ty = (T)fy;
+  const int corner = key & 3;
+  w = (corner & 1 ? tx : 1 - tx) * (corner & 2 ? ty : 1 - ty);
+  v = o.img[t / o.n2] / (T)o.n2;
+}
+
+// The sum of the row of n keys by the whole wave (n, keys: the same in every lane).
+template <typename T>
+__device__ __forceinline__ T row_by_wave(const RowView<T>& o, const int* keys, int n, long all) {
+  const int lane = threadIdx.x & 63;
   const auto wave_sync = [] {   // this wave's LDS accesses complete in order; keep the compiler's order too
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
   T acc = 0;
-  const long all = 4 * nsubpix;
   long width = n <= kSortCap ? all : all / ((n + kSortCap - 1) / kSortCap);
   for (long lo = 0; lo < all && n > 0;) {
     if (width < kSortCap) width = kSortCap;   // never more than that many distinct keys
@@ -315,7 +328,7 @@ __global__ void __launch_bounds__(64 * kGatherW) k_lt_gather(const double* __res
       const bool in = k >= lo && k < hi;
       const unsigned long long bal = __ballot(in);
       const int at = c + __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-      if (in && at < kSortCap) ks[at] = k;
+      if (in && at < kSortCap) o.ks[at] = k;
       c += __popcll(bal);
     }
     c = __builtin_amdgcn_readfirstlane(c);
@@ -325,26 +338,69 @@ __global__ void __launch_bounds__(64 * kGatherW) k_lt_gather(const double* __res
       continue;
     }
     for (int e = lane; e < c; e += 64) {
-      const int key = ks[e];
+      const int key = o.ks[e];
       int rank = 0;
-      for (int x = 0; x < c; ++x) rank += ks[x] < key;
-      const long t = key >> 2;
-      const UV q = p[t];
-      int cell;
-      double fx, fy;
-      grid_cell(q.u, q.v, ns, cell, fx, fy);
-      const T tx = (T)fx, ty = (T)fy;
-      const int corner = key & 3;
-      tw[rank] = (corner & 1 ? tx : 1 - tx) * (corner & 2 ? ty : 1 - ty);
-      tv[rank] = img[t / n2] / (T)n2;
+      for (int x = 0; x < c; ++x) rank += o.ks[x] < key;
+      T w, v;
+      row_term(o, key, w, v);
+      o.tw[rank] = w;
+      o.tv[rank] = v;
     }
     wave_sync();
-    for (int x = 0; x < c; ++x) acc += tw[x] * tv[x];
+    for (int x = 0; x < c; ++x) acc += o.tw[x] * o.tv[x];
     wave_sync();
     lo = hi;
     if (c <= kSortCap / 2) width <<= 1;
   }
-  if (lane == 0) s[mb.off[m] + i] = acc;
+  return acc;
+}
+
+// SHORT: for grids with more nodes than the image has subpixels (at most four
+// keys a row on average), one lane takes a row of up to kShortRow keys, and the
+// wave its 64 rows' longer ones in turn.  (A wave per node there too: 512 x 512
+// pixels, 2 x 2 subpixels, 2048 x 2048 nodes 5.7 ms in FP32, 6.3 in FP64; 4.7 so.)
+constexpr int kShortRow = 8;
+template <typename T, bool SHORT>
+__global__ void __launch_bounds__(64 * kGatherW) k_lt_gather(const double* __restrict__ uv, int n2, long nsubpix,
+                                                             Batch mb, int* __restrict__ ws, long I_max,
+                                                             const T* __restrict__ img, T* __restrict__ s) {
+  __shared__ int ks_[kGatherW][kSortCap];
+  __shared__ T tw_[kGatherW][kSortCap], tv_[kGatherW][kSortCap];
+  const int m = blockIdx.y, ns = mb.ns[m], lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const OrderedWs w = ordered_ws(ws, m, I_max, 4 * nsubpix);
+  const RowView<T> o{reinterpret_cast<const UV*>(uv) + m * nsubpix, img + (long)m * (nsubpix / n2), ns, n2,
+                     ks_[wid], tw_[wid], tv_[wid]};
+  const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kGatherW + wid));
+  if (!SHORT) {
+    if (wave >= ns * ns) return;
+    const T acc = row_by_wave(o, w.keys + w.ptr[wave], w.ptr[wave + 1] - w.ptr[wave], 4 * nsubpix);
+    if (lane == 0) s[mb.off[m] + wave] = acc;
+    return;
+  }
+  const int i = 64 * wave + lane;
+  const int e0 = i < ns * ns ? w.ptr[i] : 0, n = i < ns * ns ? w.ptr[i + 1] - e0 : 0;
+  T acc = 0;
+  if (n <= kShortRow) {
+    int key[kShortRow];
+#pragma unroll
+    for (int e = 0; e < kShortRow; ++e) key[e] = e < n ? w.keys[e0 + e] : INT_MAX;   // (no key is that large)
+    int last = -1;
+    for (int r = 0; r < n; ++r) {   // the keys in ascending order
+      int next = INT_MAX;
+#pragma unroll
+      for (int e = 0; e < kShortRow; ++e) next = key[e] > last ? min(next, key[e]) : next;
+      T wt, v;
+      row_term(o, next, wt, v);
+      acc += wt * v;
+      last = next;
+    }
+  }
+  for (unsigned long long lng = __ballot(n > kShortRow); lng; lng &= lng - 1) {   // uniform
+    const int l = __ffsll(lng) - 1;
+    const T a = row_by_wave(o, w.keys + __builtin_amdgcn_readlane(e0, l), __builtin_amdgcn_readlane(n, l), 4 * nsubpix);
+    if (lane == l) acc = a;
+  }
+  if (i < ns * ns) s[mb.off[m] + i] = acc;
 }
 
 template <typename T>
@@ -658,13 +714,19 @@ static size_t lt_ordered_ws(const sl_image_grid* img, const int32_t* ns, int n_m
 // Largest LDS histogram of a source grid (two blocks of 512 threads still fit on a CU).
 constexpr size_t kBinLds = 78 * 1024;
 
-// One pass of k_lt_bin over a group of members, each in the form its grid allows.
+// One pass of k_lt_bin over a group of members, each in the form its grid allows;
+// a histogram of more nodes than there are subpixels costs more to clear and
+// read out than the atomics in memory that it saves (one 32 x 32 image, 100 x 100
+// nodes: the operator 40 -> 35 us).
 template <bool FILL>
 static void launch_bins(const double* uv, long nsp, const int32_t* ns, int n, int* ws, long I_max, hipStream_t st) {
-  static const int cut = side_that_fits(kBinLds, sizeof(int));
+  static const int fits = side_that_fits(kBinLds, sizeof(int));
+  int cut = 1;
+  while (cut < fits && (long)(cut + 1) * (cut + 1) <= nsp) ++cut;
   for (const bool lds : {true, false})
     for_picked(ns, n, cut, lds, nsp + kLtT, [&](const Picked& mb, int np, int big) {
-      const int want = (int)std::max(1L, std::min((256L + np - 1) / np, (nsp + 8L * kLtT - 1) / (8L * kLtT)));
+      const int want = lds ? (int)std::max(1L, std::min((256L + np - 1) / np, (nsp + 8L * kLtT - 1) / (8L * kLtT)))
+                           : (int)nblocks(nsp, kLtT);   // a thread per subpixel
       const int per = (int)((nsp + want - 1) / want);
       const dim3 grid(nblocks(nsp, per), np);
       if (lds)
@@ -691,10 +753,12 @@ static int apply_LT_ordered_impl(const double* uv, int n_members, const sl_image
     const int n = std::min(group, n_members - m0);
     Batch mb;
     int big = 0;
+    long nodes = 0;
     for (int i = 0; i < n; ++i) {
       mb.ns[i] = ns[m0 + i];
       mb.off[i] = off;
       off += (long)ns[m0 + i] * ns[m0 + i];
+      nodes += (long)ns[m0 + i] * ns[m0 + i];
       big = std::max(big, ns[m0 + i]);
     }
     const double* uvm = uv + (long)m0 * nsp * 2;
@@ -703,8 +767,10 @@ static int apply_LT_ordered_impl(const double* uv, int n_members, const sl_image
     launch_bins<false>(uvm, nsp, ns + m0, n, w, I_max, st);
     hipLaunchKernelGGL(k_lt_scan, dim3(n), dim3(1024), 0, st, mb, w, I_max, 4 * nsp);
     launch_bins<true>(uvm, nsp, ns + m0, n, w, I_max, st);
-    hipLaunchKernelGGL(k_lt_gather<T>, dim3(nblocks((long)big * big, kGatherW), n), dim3(64 * kGatherW), 0, st, uvm,
-                       n2, nsp, mb, w, I_max, (const T*)in + (long)m0 * J, (T*)s);
+    const bool rows_short = nodes >= n * nsp;   // at most four keys a row
+    hipLaunchKernelGGL((rows_short ? k_lt_gather<T, true> : k_lt_gather<T, false>),
+                       dim3(nblocks((long)big * big, rows_short ? 64 * kGatherW : kGatherW), n), dim3(64 * kGatherW), 0,
+                       st, uvm, n2, nsp, mb, w, I_max, (const T*)in + (long)m0 * J, (T*)s);
     if (int e = check_launch("ordered L^T")) return e;
   }
   return SL_OK;

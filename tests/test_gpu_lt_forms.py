@@ -66,3 +66,29 @@ def test_each_member_takes_its_own_form(dtype):
     # the ordered form's two binning passes, in the LDS and the memory form each
     bins = [(g[1], lds > 0) for g, b, lds in _call(64, 2, ns, dtype, ordered=True, check=(0, 10, 11, 30)) if b[0] == 512]
     assert sorted(bins) == [(1, False), (1, False), (30, True), (30, True)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_ordered_rows_of_every_length_on_a_sparse_grid(dtype):
+    """A grid with more nodes than the image has subpixels takes a lane per row; bits as a wave per row."""
+    import paper_1101_5803_amd as sl
+    grid = sl.Grid(32, 32, 0.1, 2)
+    rng = np.random.default_rng(4)
+    uv = torch.full((1, 4096, 2), float("nan"), dtype=torch.float64)
+    at = rng.permutation(4096)
+    for cell, n in enumerate([1, 2, 7, 8, 9, 63, 64, 70, 511, 600]):   # cells two apart: no node has two cells
+        k, at = at[:n], at[n:]
+        uv[0, k, 0] = torch.tensor(2 * (cell % 4) + rng.uniform(0, 1, n))
+        uv[0, k, 1] = torch.tensor(2 * (cell // 4) + rng.uniform(0, 1, n))
+    uv = uv.to(DEV)
+    img = torch.tensor(rng.standard_normal((1, 1024)), dtype=dtype, device=DEV)
+    out, launches = {}, {}
+    for ns in (12, 100):   # 144 nodes: a wave per row; 10000: sparse
+        out[ns] = sl.apply_LT_ordered(uv, grid, [ns], img).reshape(ns, ns)
+        nodes = kernel_launches(lambda: sl.apply_LT_ordered(uv, grid, [ns], img))
+        launches[ns] = nodes[-1]
+        assert [lds > 0 for _, block, lds in nodes if block[0] == 512] == [ns == 12] * 2   # the binning passes
+    assert torch.equal(out[100][:12, :12], out[12]) and not out[100][12:].any() and not out[100][:, 12:].any()
+    assert launches[12][0][0] * launches[12][1][0] == 64 * 144
+    assert launches[100][0][0] * launches[100][1][0] < 2 * 10000
+    _call(48, 1, [200], dtype, ordered=True, check=(0,))
