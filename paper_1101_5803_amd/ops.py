@@ -455,9 +455,7 @@ def mlp_forward(params: torch.Tensor, x: torch.Tensor, out: torch.Tensor | None 
     x = x.contiguous()
     B = x.shape[0]
     y = out if out is not None else torch.empty(B, dtype=torch.float32, device=x.device)
-    ws = _mlp_workspace(B, x.device)
-    L.check(L.lib().sl_mlp_forward(L.ptr(params), L.ptr(x), B, L.ptr(y), L.ptr(ws), L.stream_handle()),
-            "sl_mlp_forward")
+    L.check(L.lib().sl_mlp_forward_noalloc(L.ptr(params), L.ptr(x), B, L.ptr(y), L.stream_handle()), "sl_mlp_forward")
     return y
 
 
