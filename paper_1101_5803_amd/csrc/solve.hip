@@ -144,6 +144,8 @@ struct SolveArgs {
   int nx, ny, nsub, n2, K, ck, ckt, reg, n_members, n_lambda, max_ns, maxit, lds_frame_cap;
   int q_off, red_off, pc_off, frame_off;   // byte offsets in dynamic LDS
   int lds_bytes;                   // dynamic LDS of the solve kernels
+  int frames_fit;                  // FP64: the whole image's frame fits in LDS beside the largest grid's vectors
+  int one_vector;                  // k_chi2_src: no second vector, and one member only
   int gframe_elems;                // per-block global frame size (elements)
   int slot_cap;                    // trace-table slots per member (J + 64)
   double pix, R, sigma, tol;
@@ -443,7 +445,7 @@ struct LdsPlan {
   int p, q, red, frame;
 };
 template <typename T>
-__device__ __forceinline__ LdsPlan lds_plan(const SolveArgs& a, int I, int mem) {
+__host__ __device__ __forceinline__ LdsPlan lds_plan(const SolveArgs& a, int I, int mem) {
   if (sizeof(T) == 4) return {0, a.q_off, a.red_off, a.frame_off};
   const int red = 64 * (int)sizeof(double), v = ((int)sizeof(T) * I + 255) & ~255;
   return {red, red + v, 0, red + (mem == kMemLdsQGlobal ? v : 2 * v)};
@@ -459,21 +461,30 @@ __host__ __device__ constexpr int lds_mem(int ckt) {
   return sizeof(T) == 8 && ckt > 2 ? kMemLdsQGlobal : kMemLds;
 }
 
-// FP64 members with more nodes keep a global frame.  p alone takes 72 KB or
-// more of theirs, so a 128 x 128 lens's frame fits beside it for some members
-// and not for others, and the others' items, the longest of their launch, set
-// its time either way (64 members of 32..96 nodes per side with Monte Carlo
-// degrees of freedom, against one earlier build: 1.67x with the limit, 1.64x
-// without).
+// Where a launch's frames are not all sure to fit, FP64 members with more nodes
+// keep a global frame, unless theirs fits at the offsets of the largest grid.  p
+// alone takes 72 KB or more of theirs, so some members' frames would fit beside
+// it and others' not, and the others' items, the longest of the launch, set its
+// time: 64 members of 32..96 nodes per side on a 128 x 128 image with Monte Carlo
+// degrees of freedom take the same time within its spread with the limit and
+// without (1.67x and 1.64x of one earlier build's speed), so the line stays where
+// the common offsets had it on such images (the global form is tested there, at
+// 95 and 96 nodes).  Where all frames fit, LDS is the faster place: 64 members of
+// 95..100 nodes on a 64 x 64 image, K = 15, 24.1 ms in global memory, 19.5 in LDS.
 constexpr int kLdsNodesF64 = 9000;
+
+// Elements of the frame of an h x w box.
+__host__ __device__ __forceinline__ long frame_size(int h, int w, int ckt) {
+  return (long)(h + 4 * ckt + kSegR) * ((w + 4 * ckt) | 1);
+}
 
 // Mem of a member whose frame has `elems` elements.
 template <typename T>
-__device__ __forceinline__ int mem_of(const SolveArgs& a, int I, long elems) {
+__host__ __device__ __forceinline__ int mem_of(const SolveArgs& a, int I, long elems) {
   if (sizeof(T) == 4) return elems <= a.lds_frame_cap ? kMemLds : kMemGlobal;
-  if (I > kLdsNodesF64) return kMemGlobal;
-  const int mem = lds_mem<T>(a.ckt);
-  return lds_plan<T>(a, I, mem).frame + elems * (long)sizeof(T) <= a.lds_bytes ? mem : (int)kMemGlobal;
+  const int mem = a.one_vector ? (int)kMemLdsQGlobal : lds_mem<T>(a.ckt);
+  if (lds_plan<T>(a, I, mem).frame + elems * (long)sizeof(T) > a.lds_bytes) return kMemGlobal;
+  return I <= kLdsNodesF64 || a.frames_fit || elems <= a.lds_frame_cap ? mem : (int)kMemGlobal;
 }
 
 // ------------------------------------------------------------------ member set-up (k_prep_*)
@@ -689,8 +700,7 @@ __global__ void __launch_bounds__(kPrepT) k_prep_place(SolveArgs a) {
         mi.r0 = mi.c0 = 0;
         mi.r1 = mi.c1 = -1;
       }
-      const int fh = mi.r1 - mi.r0 + 1, fw = mi.c1 - mi.c0 + 1;
-      mi.lds_frame = mem_of<T>(a, mi.I, (long)(fh + 4 * a.ckt + kSegR) * ((fw + 4 * a.ckt) | 1));
+      mi.lds_frame = mem_of<T>(a, mi.I, frame_size(mi.r1 - mi.r0 + 1, mi.c1 - mi.c0 + 1, a.ckt));
       mi.sell = 0;
       mi.pc_c = 0.0f;
       a.minfo[m] = mi;
@@ -913,8 +923,8 @@ __global__ void __launch_bounds__(1024) k_prep_layout(SolveArgs a) {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
   __syncthreads();
-  const int fh = mi.r1 - mi.r0 + 1, fw = mi.c1 - mi.c0 + 1;
-  const bool pair_ok = mi.lds_frame != kMemGlobal && (long)(fh + 4 * a.ckt + kSegR) * ((fw + 4 * a.ckt) | 1) <= 65536;
+  const bool pair_ok =
+      mi.lds_frame != kMemGlobal && frame_size(mi.r1 - mi.r0 + 1, mi.c1 - mi.c0 + 1, a.ckt) <= 65536;
   for (int g = wid; g < ngroups; g += 16) {
     int mx = pcnt[64 * g + lane];
 #pragma unroll
@@ -3352,12 +3362,16 @@ static int configure(SolveArgs& A, const Layout& L, const sl_tuning& v, LaunchCf
   // sine table 2 (max_ns + 1) and eigenvalues max_ns of the spectral preconditioner
   A.frame_off = A.pc_off + (int)align256(sizeof(float) * (3 * A.max_ns + 8));
   const size_t fixed = (size_t)A.frame_off;
-  size_t lds = fixed + sz * (size_t)(A.ny + 4 * ckt + kSegR) * (size_t)((A.nx + 4 * ckt) | 1);
+  size_t lds = fixed + sz * (size_t)frame_size(A.ny, A.nx, ckt);
   const size_t lds_max = 160 * 1024 - 1024;
   if (lds > lds_max) lds = lds_max;
   SL_REQUIRE(lds > fixed + 64 * sz, "source grid too large for LDS");
   A.lds_frame_cap = (int)((lds - fixed) / sz);
   A.lds_bytes = (int)lds;
+  // the candidate-source kernel's one member has no launch to hold up: its own frame decides
+  A.frames_fit = A.one_vector;
+  if (sizeof(T) == 8 && !A.one_vector)
+    A.frames_fit = lds_plan<T>(A, L.I_max, lds_mem<T>(ckt)).frame + frame_size(A.ny, A.nx, ckt) * (long)sz <= (long)lds;
   c->ks = ks;
   c->ksd = ksd;
   if (sizeof(T) == 4 && A.reg == SL_H_CURVATURE && !A.plain_cg && !A.implicit) {
@@ -3723,6 +3737,7 @@ int sl_chi2_sources(const sl_problem* pb, const double* lens, int ns, const doub
   Layout L;
   LamList lams;
   if (int e = prepare(pb, lens, ns_dev, ns, 1, &lam1, 1, &opt, workspace, base, &dummy, &A, &L, &lams)) return e;
+  A.one_vector = 1;
   LaunchCfg c;
   const sl_tuning dflt{0, 0, 0, 1, 0, 0};
   if (int e = configure_any(pb->dtype, A, L, dflt, &c)) return e;
