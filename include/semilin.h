@@ -249,10 +249,11 @@ size_t sl_solve_workspace_size(const sl_problem* pb, int max_ns, int n_members, 
  * the corners are known, a second system (A^T A + lambda H^T H) x = A^T bhat
  * (A = B L) is solved at every member's corner lambda, and
  * dof[m] = bhat^T (bhat - A xhat), computed as bhat^T bhat - <A^T bhat, xhat>
- * in FP64.  SL_F64: as the paper does, the corner lambda's data system is
- * solved again by plain CG from s = 0 and the second system is advanced in
- * lockstep with the data system's coefficients alpha_k, beta_k (about two
- * solves per member).  SL_F32: that fixed-coefficient recurrence amplifies
+ * in FP64.  SL_F64: as the paper does, the second system is advanced with the
+ * data system's CG coefficients alpha_k, beta_k.  The solve keeps them in
+ * workspace that it otherwise leaves unused (about one solve more per member);
+ * for an item with more iterations than that has room for, the data system is
+ * solved again from s = 0 in lockstep (about two), with the same bits.  SL_F32: that fixed-coefficient recurrence amplifies
  * FP32 rounding without bound on long solves, so the second system is solved
  * by its own CG to the same relative tolerance (one solve per member); both
  * converge to the same xhat.  The expectation of dof over bhat is J - gamma,

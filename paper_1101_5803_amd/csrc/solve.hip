@@ -62,7 +62,6 @@ constexpr int kUpd = 4;        // CG vector-update chunk (nodes per thread)
 constexpr int kPcThetaPct = 15;   // default theta = 0.15 (sl_tuning.pc_theta_pct = 0)
 constexpr int kFillW = 16;     // waves that fill the transposed operator in parallel in k_prep_fill
 constexpr int kHeavy = 4;      // default count of smallest lambdas of each member queued ahead of the rest
-constexpr int kCoefCap = 1024; // CG iterations per item whose step lengths are kept for the Monte Carlo pass
 constexpr int kMaxCK = 31;
 
 struct alignas(16) MemberInfo {
@@ -98,7 +97,7 @@ struct alignas(16) Consts {
 };
 
 struct Layout {
-  size_t consts, lam, taps_d, taps_f, minfo, queues, pqueues, pix, cell, fx, fy, pmask, btd, pcpart, b, bh, dofk, coef, s_all, gframe, gz, rbuf, mcbuf, ibuf,
+  size_t consts, lam, taps_d, taps_f, minfo, queues, pqueues, pix, cell, fx, fy, pmask, btd, pcpart, b, bh, dofk, s_all, gframe, gz, rbuf, mcbuf, ibuf,
       lt_ptr, lt_perm, lt_base, lt_cnt,
       lt_ent,
       total;
@@ -202,7 +201,6 @@ struct SolveArgs {
   double* btd;       // [2][J] B^T d and B^T bhat (FP64)
   double* pcpart;    // [member][rhs_blocks][2] parts of the preconditioner scale's two sums
   int rhs_blocks;    // blocks of k_prep_rhs per member
-  double2* coef;     // [member][n_lambda][kCoefCap] FP64 CG's step lengths (alpha, beta), for k_mcdof
   int32_t* lt_base;  // [member][I_max] index of each node's first entry of the transposed operator
   int32_t* lt_cnt;   // [member][I_max] entries of each node
   void* mcbuf;       // [n_wg][5][I_max] r, xhat, rhat, phat, saved p of the pass
@@ -2235,6 +2233,27 @@ __device__ __forceinline__ double apply_normal(const OpView<T>& o, const T* __re
   return gather_LT<T, NT, false, sizeof(T) == 4 && CKT <= 7>(o, P, Q);
 }
 
+// Where an FP64 solve with Monte Carlo draws keeps an item's step lengths for
+// k_mcdof: (alpha, beta) of iteration i at p[1 + i], for up to `cap` iterations,
+// and the count of iterations in p[0].x (cap -1: no room).  They lie in what the
+// member's L^T entries leave free of its region, shared out among its lambdas:
+// the region is sized for twice the entries without padding, so that at least
+// three eighths of it are free where the entries are paired (128 x 128 pixels, 2 x
+// 2 subpixels, 16 lambdas: 12000 iterations or more).
+struct CoefRoom {
+  double2* p;
+  int cap;
+};
+template <typename T>
+__device__ __forceinline__ CoefRoom coef_room(const SolveArgs& a, const MemberInfo& mi, int m, int kl) {
+  const long size = (long)sizeof(LtEntry<T>) * a.lt_cap;
+  const long E = a.lt_ptr[(long)m * (a.I_max + 65) + (mi.sell ? (mi.I + 63) / 64 : mi.I)];   // entries with padding
+  const long used = (E * (long)(mi.sell == 2 ? sizeof(unsigned short) + sizeof(T) : sizeof(LtEntry<T>)) + 15) & ~15L;
+  const int each = (int)((size - used) / (long)sizeof(double2) / a.n_lambda);
+  return {reinterpret_cast<double2*>(reinterpret_cast<unsigned char*>(a.lt_ent) + m * size + used) + (long)kl * each,
+          each - 1};
+}
+
 template <typename T, int CKT, int MEM, bool PC, bool DIR>
 __device__ __forceinline__ void run_item(const SolveArgs& a, const MemberInfo& mi, int m, int kl, unsigned char* smem) {
   constexpr int NT = kNTof<T>;   // threads of this block
@@ -2319,6 +2338,9 @@ __device__ __forceinline__ void run_item(const SolveArgs& a, const MemberInfo& m
                   reinterpret_cast<const float*>(r_g), mi.pc_c, (float)a.lamv[kl], 0.0, 1, red);
     __syncthreads();
   }
+  CoefRoom cf{nullptr, -1};
+  if constexpr (sizeof(T) == 8)
+    if (a.mcn) cf = coef_room<T>(a, mi, m, kl);
   int st = SL_ST_MAXIT, it = 0;
   for (it = 0; it < a.maxit; ++it) {
     if (__builtin_amdgcn_readfirstlane((int)(rr <= stop2))) {
@@ -2372,8 +2394,7 @@ __device__ __forceinline__ void run_item(const SolveArgs& a, const MemberInfo& m
     } else {
       const T beta = (T)(rn / rr);
       if constexpr (sizeof(T) == 8) {
-        if (a.mcn && it < kCoefCap)   // the same value from every thread
-          a.coef[out_idx * kCoefCap + it] = make_double2((double)alT, (double)beta);
+        if (it < cf.cap) cf.p[1 + it] = make_double2((double)alT, (double)beta);   // the same value from every thread
       }
       if (I <= kUpd * NT) {
 #pragma unroll
@@ -2400,6 +2421,8 @@ __device__ __forceinline__ void run_item(const SolveArgs& a, const MemberInfo& m
     __syncthreads();
   }
   if (st == SL_ST_MAXIT && rr <= stop2) st = SL_ST_OK;
+  if constexpr (sizeof(T) == 8)
+    if (cf.cap >= 0) cf.p[0] = make_double2((double)it, 0.0);
   // ---- chi^2 and ||H s||^2 from the explicit solution
   __syncthreads();
   for (int i = tid; i < I; i += NT) P[i] = s_g[i];
@@ -2492,10 +2515,11 @@ __device__ __forceinline__ int fetch_counter(int* counter, int* sh_m) {
 }
 
 // Monte Carlo degrees of freedom of one member at its corner lambda (Sec. 2.5).
-// FP64: plain CG on the data system, and in lockstep the system with
-// right-hand side A^T bhat advanced with the data system's alpha_k and beta_k
-// (not its own); p of the data system stays in LDS (P), and the second
-// system's direction is swapped into P for its operator application.  FP32:
+// FP64: the system with right-hand side A^T bhat is advanced with the data
+// system's alpha_k and beta_k (not its own).  Where the solve had room for all of
+// them (CoefRoom) they are read back; otherwise the data system's plain CG runs
+// again in lockstep, with its p in LDS (P) and the second system's direction
+// swapped into P for its operator application; both give the same bits.  FP32:
 // the second system by its own CG (see below).  Then gamma = <A^T bhat, xhat>
 // = bhat^T A xhat and dof = bhat^T bhat - gamma.  Per-block scratch (global):
 // r, xhat, rhat, phat and the saved p.
@@ -2574,83 +2598,85 @@ __device__ __forceinline__ void run_mc_item(const SolveArgs& a, const MemberInfo
       rr = rn;
       __syncthreads();
     }
-  } else if (__builtin_amdgcn_readfirstlane((int)(a.iters[(long)m * a.n_lambda + kl] <= kCoefCap))) {
-    // The data system's step lengths as k_solve left them: only the second
-    // system is advanced (solving the data system again in lockstep, as below,
-    // took twice the operator applications: 170 ms for 64 c3 members, 83 ms so).
-    const int n_it = __builtin_amdgcn_readfirstlane(a.iters[(long)m * a.n_lambda + kl]);
-    const double2* cf = a.coef + ((long)m * a.n_lambda + kl) * kCoefCap;
-    for (int i = tid; i < I; i += NT) {
-      const T nv = (T)bhm[i];
-      P[i] = nv;
-      rh_g[i] = nv;
-      xh_g[i] = (T)0;
-    }
-    __syncthreads();
-    for (int it = 0; it < n_it; ++it) {
-      (void)apply_normal<T, CKT, NT, DIR>(ov, P, Q);
-      __syncthreads();   // every gather has read P and the frame
-      clear_rows<T, CKT, NT, DIR>(ov);
-      const T alT = (T)cf[it].x, beta = (T)cf[it].y;
+  } else {
+    const CoefRoom cf = coef_room<T>(a, mi, m, kl);
+    const int n_it = __builtin_amdgcn_readfirstlane(cf.cap >= 0 ? (int)cf.p[0].x : INT_MAX);
+    if (n_it <= cf.cap) {
+      // The data system's step lengths as k_solve left them: only the second
+      // system is advanced (solving the data system again in lockstep, as below,
+      // took twice the operator applications: 170 ms for 64 c3 members, 83 ms so).
       for (int i = tid; i < I; i += NT) {
-        const T ph = P[i];
-        xh_g[i] += alT * ph;
-        const T rk = rh_g[i] - alT * Q[i];
-        rh_g[i] = rk;
-        P[i] = rk + beta * ph;
+        const T nv = (T)bhm[i];
+        P[i] = nv;
+        rh_g[i] = nv;
+        xh_g[i] = (T)0;
       }
       __syncthreads();
+      for (int it = 0; it < n_it; ++it) {
+        (void)apply_normal<T, CKT, NT, DIR>(ov, P, Q);
+        __syncthreads();   // every gather has read P and the frame
+        clear_rows<T, CKT, NT, DIR>(ov);
+        const T alT = (T)cf.p[1 + it].x, beta = (T)cf.p[1 + it].y;
+        for (int i = tid; i < I; i += NT) {
+          const T ph = P[i];
+          xh_g[i] += alT * ph;
+          const T rk = rh_g[i] - alT * Q[i];
+          rh_g[i] = rk;
+          P[i] = rk + beta * ph;
+        }
+        __syncthreads();
+      }
+    } else {
+      double rr = 0.0;
+      for (int i = tid; i < I; i += NT) {
+        const T bv = (T)bm[i], nv = (T)bhm[i];
+        P[i] = bv;
+        r_g[i] = bv;
+        rr += (double)bv * (double)bv;
+        xh_g[i] = (T)0;
+        rh_g[i] = nv;
+        ph_g[i] = nv;
+      }
+      rr = block_sum1<NT / kWave>(rr, red, 0);
+      const double stop2 = a.tol * a.tol * rr;
+      for (int it = 0; it < a.maxit; ++it) {
+        if (__builtin_amdgcn_readfirstlane((int)(rr <= stop2))) break;
+        // data system: q = A p, alpha, r update, beta, new p (saved to global)
+        double pq = apply_normal<T, CKT, NT, DIR>(ov, P, Q);
+        pq = block_sum1<NT / kWave>(pq, red, 0);
+        clear_rows<T, CKT, NT, DIR>(ov);
+        if (__builtin_amdgcn_readfirstlane((int)!(pq > 0.0))) break;
+        const T alT = (T)(rr / pq);
+        double rn = 0.0;
+        for (int i = tid; i < I; i += NT) {
+          const T rk = r_g[i] - alT * Q[i];
+          r_g[i] = rk;
+          rn += (double)rk * (double)rk;
+        }
+        rn = block_sum1<NT / kWave>(rn, red, 1);
+        const T beta = (T)(rn / rr);
+        for (int i = tid; i < I; i += NT) {
+          pd_g[i] = r_g[i] + beta * P[i];
+          P[i] = ph_g[i];
+        }
+        __syncthreads();
+        // second system with the same alpha and beta
+        double pqh = apply_normal<T, CKT, NT, DIR>(ov, P, Q);
+        pqh = block_sum1<NT / kWave>(pqh, red, 0);   // its barrier: every gather has read P and the frame
+        (void)pqh;
+        clear_rows<T, CKT, NT, DIR>(ov);
+        for (int i = tid; i < I; i += NT) {
+          const T ph = P[i];
+          xh_g[i] += alT * ph;
+          const T rk = rh_g[i] - alT * Q[i];
+          rh_g[i] = rk;
+          ph_g[i] = rk + beta * ph;
+          P[i] = pd_g[i];
+        }
+        rr = rn;
+        __syncthreads();
+      }
     }
-  } else {
-  double rr = 0.0;
-  for (int i = tid; i < I; i += NT) {
-    const T bv = (T)bm[i], nv = (T)bhm[i];
-    P[i] = bv;
-    r_g[i] = bv;
-    rr += (double)bv * (double)bv;
-    xh_g[i] = (T)0;
-    rh_g[i] = nv;
-    ph_g[i] = nv;
-  }
-  rr = block_sum1<NT / kWave>(rr, red, 0);
-  const double stop2 = a.tol * a.tol * rr;
-  for (int it = 0; it < a.maxit; ++it) {
-    if (__builtin_amdgcn_readfirstlane((int)(rr <= stop2))) break;
-    // data system: q = A p, alpha, r update, beta, new p (saved to global)
-    double pq = apply_normal<T, CKT, NT, DIR>(ov, P, Q);
-    pq = block_sum1<NT / kWave>(pq, red, 0);
-    clear_rows<T, CKT, NT, DIR>(ov);
-    if (__builtin_amdgcn_readfirstlane((int)!(pq > 0.0))) break;
-    const T alT = (T)(rr / pq);
-    double rn = 0.0;
-    for (int i = tid; i < I; i += NT) {
-      const T rk = r_g[i] - alT * Q[i];
-      r_g[i] = rk;
-      rn += (double)rk * (double)rk;
-    }
-    rn = block_sum1<NT / kWave>(rn, red, 1);
-    const T beta = (T)(rn / rr);
-    for (int i = tid; i < I; i += NT) {
-      pd_g[i] = r_g[i] + beta * P[i];
-      P[i] = ph_g[i];
-    }
-    __syncthreads();
-    // second system with the same alpha and beta
-    double pqh = apply_normal<T, CKT, NT, DIR>(ov, P, Q);
-    pqh = block_sum1<NT / kWave>(pqh, red, 0);   // its barrier: every gather has read P and the frame
-    (void)pqh;
-    clear_rows<T, CKT, NT, DIR>(ov);
-    for (int i = tid; i < I; i += NT) {
-      const T ph = P[i];
-      xh_g[i] += alT * ph;
-      const T rk = rh_g[i] - alT * Q[i];
-      rh_g[i] = rk;
-      ph_g[i] = rk + beta * ph;
-      P[i] = pd_g[i];
-    }
-    rr = rn;
-    __syncthreads();
-  }
   }
   double g = 0.0;
   for (int i = tid; i < I; i += NT) g += bhm[i] * (double)xh_g[i];
@@ -3158,7 +3184,6 @@ static Layout make_layout(const sl_problem* pb, int max_ns, int M, int NL, int n
   L.pcpart = take(2 * sizeof(double) * (size_t)M * rhs_grid(L.I_max, M));
   L.b = take(sizeof(double) * (size_t)M * L.I_max);
   L.bh = take(sizeof(double) * (size_t)M * L.I_max);   // A^T bhat (Monte Carlo degrees of freedom)
-  if (pb->dtype == SL_F64) L.coef = take(sizeof(double2) * (size_t)M * NL * kCoefCap);
   L.dofk = take(sizeof(double) * (size_t)M * NL);      // per-iterate estimate of the implicit solve
   L.s_all = take(sz * (size_t)M * NL * L.I_max);
   L.gframe_elems = (pb->img.ny + 4 * 16 + kSegR) * ((pb->img.nx + 4 * 16) | 1);   // widest window's halo
@@ -3636,7 +3661,6 @@ static int prepare(const sl_problem* pb, const double* lens, const int32_t* ns, 
   A.b = (double*)(ws + L.b);
   A.bh = (double*)(ws + L.bh);
   A.dofk = (double*)(ws + L.dofk);
-  A.coef = pb->dtype == SL_F64 ? (double2*)(ws + L.coef) : nullptr;
   A.pmask = (unsigned long long*)(ws + L.pmask);
   A.btd = (double*)(ws + L.btd);
   A.pcpart = (double*)(ws + L.pcpart);
