@@ -197,7 +197,7 @@ struct SolveArgs {
   double* dofv;      // [n_members] result: bhat^T (bhat - A xhat) at the corner
   double* bh;        // [member][I_max] A^T bhat (FP64)
   double* dofk;      // [member][n_lambda] implicit solve: the estimate after each iterate
-  unsigned long long* pmask;   // [member][slot_cap] first-occurrence mask of a slot's (subpixel, corner) pairs
+  void* pmask;       // [member][slot_cap] first-occurrence mask of a slot's (subpixel, corner) pairs (PairMasks)
   double* btd;       // [2][J] B^T d and B^T bhat (FP64)
   double* pcpart;    // [member][rhs_blocks][2] parts of the preconditioner scale's two sums
   int rhs_blocks;    // blocks of k_prep_rhs per member
@@ -610,6 +610,22 @@ __global__ void __launch_bounds__(kPrepT) k_prep_trace(SolveArgs a) {
   }
 }
 
+// A member's masks (below): 16 bits each hold those of up to 2 x 2 subpixels.
+__host__ __device__ __forceinline__ size_t mask_bytes(int n2) { return n2 <= 4 ? 2 : 8; }
+struct PairMasks {
+  void* p;
+  bool narrow;
+  __device__ PairMasks(const SolveArgs& a, int m)
+      : p(static_cast<unsigned char*>(a.pmask) + mask_bytes(a.n2) * (size_t)m * a.slot_cap), narrow(a.n2 <= 4) {}
+  __device__ unsigned long long operator[](int t) const {
+    return narrow ? static_cast<const unsigned short*>(p)[t] : static_cast<const unsigned long long*>(p)[t];
+  }
+  __device__ void set(int t, unsigned long long mask) const {
+    if (narrow) static_cast<unsigned short*>(p)[t] = (unsigned short)mask;
+    else static_cast<unsigned long long*>(p)[t] = mask;
+  }
+};
+
 // First-occurrence mask of a pixel's 4 n^2 (subpixel, corner) pairs: bit 4 k +
 // corner is set when subpixel k lies on the grid and no earlier subpixel
 // reaches that node.  (corner 0..3: nodes c, c + 1, c + ns, c + ns + 1)
@@ -651,6 +667,7 @@ __global__ void __launch_bounds__(kPrepT) k_prep_place(SolveArgs a) {
   const int m = blockIdx.x / tiles, tile = blockIdx.x % tiles, j = tile * kPrepT + tid;
   const int n2 = a.n2;
   const PixTmp<T> tmp(a, m);
+  const PairMasks pm(a, m);
   const int ns = a.minfo[m].ns;
   const int w0 = tile * (kPrepT / 64) + wid;   // this wave's word
   int before = 0, total = 0;
@@ -680,7 +697,7 @@ __global__ void __launch_bounds__(kPrepT) k_prep_place(SolveArgs a) {
     if (tid < 64 && Mtrue + tid < slots) {   // fewer than 64 empty slots
       const int p = Mtrue + tid, slot = (p % S) * 64 + p / S;
       pix[slot] = -1;
-      a.pmask[(long)m * a.slot_cap + slot] = 0ull;
+      pm.set(slot, 0ull);
       for (int k = 0; k < n2; ++k) {
         cellp[(long)slot * n2 + k] = -1;
         fxp[(long)slot * n2 + k] = (T)0;
@@ -724,14 +741,14 @@ __global__ void __launch_bounds__(kPrepT) k_prep_place(SolveArgs a) {
       }
     }
     const int32_t cl[4] = {c4.x, c4.y, c4.z, c4.w};
-    a.pmask[(long)m * a.slot_cap + slot] = pair_mask(cl, 4, ns);
+    pm.set(slot, pair_mask(cl, 4, ns));
   } else {
     for (int k = 0; k < n2; ++k) {
       cellp[(long)slot * n2 + k] = tmp.cell[(long)j * n2 + k];
       fxp[(long)slot * n2 + k] = tmp.fx[(long)j * n2 + k];
       fyp[(long)slot * n2 + k] = tmp.fy[(long)j * n2 + k];
     }
-    a.pmask[(long)m * a.slot_cap + slot] = pair_mask(tmp.cell + (long)j * n2, n2, ns);
+    pm.set(slot, pair_mask(tmp.cell + (long)j * n2, n2, ns));
   }
 }
 
@@ -841,7 +858,7 @@ __global__ void __launch_bounds__(1024) k_prep_layout(SolveArgs a) {
   int* whist = pcnt + I + 64;                // per-wave bucket histograms, later positions
   int* slen = whist + 16 * 128;              // slice lengths, then slice starts
   const int32_t* cellp = a.cell + (long)m * a.slot_cap * n2;
-  const unsigned long long* pm = a.pmask + (long)m * a.slot_cap;
+  const PairMasks pm(a, m);
   int32_t* rp = a.lt_ptr + (long)m * (a.I_max + 65);
   int32_t* perm = a.lt_perm + (long)m * a.I_max;
   int32_t* lbase = a.lt_base + (long)m * a.I_max;
@@ -999,7 +1016,7 @@ __global__ void __launch_bounds__(1024) k_prep_fill(SolveArgs a, int bands) {
   int* all = reinterpret_cast<int*>(smem);
   int* base = all + (long)kFillW * cap;
   const int32_t* cellp = a.cell + (long)m * a.slot_cap * n2;
-  const unsigned long long* pm = a.pmask + (long)m * a.slot_cap;
+  const PairMasks pm(a, m);
   const int32_t* lbase = a.lt_base + (long)m * a.I_max;
   LtEntry<T>* ent = reinterpret_cast<LtEntry<T>*>(a.lt_ent) + (long)m * a.lt_cap;
   const int E = a.lt_ptr[(long)m * (a.I_max + 65) + (mi.I + 63) / 64];   // sliced-ELL entries
@@ -3179,7 +3196,7 @@ static Layout make_layout(const sl_problem* pb, int max_ns, int M, int NL, int n
   L.cell = take(sizeof(int32_t) * (size_t)M * L.slot_cap * L.n2);
   L.fx = take(sz * (size_t)M * L.slot_cap * L.n2);
   L.fy = take(sz * (size_t)M * L.slot_cap * L.n2);
-  L.pmask = take(sizeof(unsigned long long) * (size_t)M * L.slot_cap);
+  L.pmask = take(mask_bytes(L.n2) * (size_t)M * L.slot_cap);
   L.btd = take(sizeof(double) * 2 * (size_t)L.J);
   L.pcpart = take(2 * sizeof(double) * (size_t)M * rhs_grid(L.I_max, M));
   L.b = take(sizeof(double) * (size_t)M * L.I_max);
@@ -3661,7 +3678,7 @@ static int prepare(const sl_problem* pb, const double* lens, const int32_t* ns, 
   A.b = (double*)(ws + L.b);
   A.bh = (double*)(ws + L.bh);
   A.dofk = (double*)(ws + L.dofk);
-  A.pmask = (unsigned long long*)(ws + L.pmask);
+  A.pmask = ws + L.pmask;
   A.btd = (double*)(ws + L.btd);
   A.pcpart = (double*)(ws + L.pcpart);
   A.rhs_blocks = rhs_grid(L.I_max, n_members);
