@@ -97,10 +97,8 @@ struct alignas(16) Consts {
 };
 
 struct Layout {
-  size_t consts, lam, taps_d, taps_f, minfo, queues, pqueues, pix, cell, fx, fy, pmask, btd, pcpart, b, bh, dofk, s_all, gframe, gz, rbuf, mcbuf, ibuf,
-      lt_ptr, lt_perm, lt_base, lt_cnt,
-      lt_ent,
-      total;
+  size_t consts, lam, taps_d, taps_f, minfo, queues, pqueues, pix, cell, fx, fy, pmask, btd, pcpart, b, bh, dofk, s_all,
+      gframe, gz, rbuf, mcbuf, ibuf, lt_ptr, lt_perm, lt_base, lt_cnt, lt_ent, total;
   long long lt_cap;
   int qcap, n_wg, I_max, J, n2, gframe_elems, slot_cap;
 };
@@ -1469,7 +1467,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // accumulator element r is C[4 (l/16) + r][l%16].
 template <bool SA, int NTL>
 __device__ __forceinline__ void sine_tiles(Lds<const float> tab, Lds<const float> mu, int n, int pitch,
-                                           Lds<const float> D, Lds<float> C, int blk, int o0, int ostep, bool scale, float c, float lam) {
+                                           Lds<const float> D, Lds<float> C, int blk, int o0, int ostep, bool scale,
+                                           float c, float lam) {
   constexpr int G = 4;
   const int lane = threadIdx.x & 63, lc = lane & 15, lq = lane >> 4;
   const unsigned nn2 = 2 * (n + 1);
@@ -1930,21 +1929,21 @@ __device__ __forceinline__ double gather_LT(const OpView<T>& o, const T* __restr
         } else {
           int j = 0;
           if constexpr (!PIPE) {
-          constexpr int U = 8;
-          for (; j + U <= npair; j += U) {   // 2 U entries in flight
-            unsigned ov[U];
-            EntryPair<T> wv[U];
+            constexpr int U = 8;
+            for (; j + U <= npair; j += U) {   // 2 U entries in flight
+              unsigned ov[U];
+              EntryPair<T> wv[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-              ov[u] = op[64L * (j + u)];
-              wv[u] = wq[64L * (j + u)];
-            }
+              for (int u = 0; u < U; ++u) {
+                ov[u] = op[64L * (j + u)];
+                wv[u] = wq[64L * (j + u)];
+              }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-              acc += wv[u].x * F[ov[u] & 0xFFFFu];
-              acc += wv[u].y * F[ov[u] >> 16];
+              for (int u = 0; u < U; ++u) {
+                acc += wv[u].x * F[ov[u] & 0xFFFFu];
+                acc += wv[u].y * F[ov[u] >> 16];
+              }
             }
-          }
           }
           for (; j < npair; ++j) {
             const unsigned o0 = op[64L * j];
@@ -2406,8 +2405,8 @@ __device__ __forceinline__ void run_item(const SolveArgs& a, const MemberInfo& m
     if constexpr (PC && sizeof(T) == 4) {
       float* tab = reinterpret_cast<float*>(smem + a.pc_off);
       rz = pc_apply(reinterpret_cast<float*>(P), reinterpret_cast<float*>(Q), reinterpret_cast<float*>(F),
-                    (a.red_off - a.q_off) / 4, a.lds_frame_cap, tab, tab + 2 * (ns + 1), ns, reinterpret_cast<const float*>(r_g), mi.pc_c, (float)a.lamv[kl], rz, 0,
-                    red);
+                    (a.red_off - a.q_off) / 4, a.lds_frame_cap, tab, tab + 2 * (ns + 1), ns,
+                    reinterpret_cast<const float*>(r_g), mi.pc_c, (float)a.lamv[kl], rz, 0, red);
     } else {
       const T beta = (T)(rn / rr);
       if constexpr (sizeof(T) == 8) {
