@@ -126,7 +126,7 @@ __device__ __forceinline__ void add_pixel(const UV* __restrict__ p, int n2, int 
 // L^T of part of one member's pixels: the terms are added in an LDS copy of the
 // member's source grid first and only its nonzero nodes go to memory, where
 // atomics across the XCDs run at about 36 G/s (every term there: 285 us for 16
-// members of a 128 x 128 image, 4.2 M terms; so 13 us).  The copy is FP64 for both
+// members of a 128 x 128 image, 4.2 M terms; so 9 us).  The copy is FP64 for both
 // types: ds_add_f32 takes two cycles a lane where ds_add_f64 takes a fraction of
 // one (19 us for those 16 members with an FP32 copy, and one 64 x 64 image 22
 // against 6 us).  The lanes of a wave take pixels n/64 apart, so that a magnified
