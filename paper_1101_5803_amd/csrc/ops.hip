@@ -355,12 +355,13 @@ __device__ __forceinline__ T row_by_wave(const RowView<T>& o, const int* keys, i
   return acc;
 }
 
-// SHORT: for grids with more nodes than the image has subpixels (at most four
-// keys a row on average), one lane takes a row of up to kShortRow keys, and the
-// wave its 64 rows' longer ones in turn.  (A wave per node there too: 512 x 512
-// pixels, 2 x 2 subpixels, 2048 x 2048 nodes 5.7 ms in FP32, 6.3 in FP64; 4.7 so.)
+// On grids with more nodes than the image has subpixels (at most four keys a row
+// on average) one lane takes a row of up to kShortRow keys, and the wave its 64
+// rows' longer ones in turn.  (A wave per node there too: 512 x 512 pixels, 2 x 2
+// subpixels, 2048 x 2048 nodes 5.7 ms in FP32, 6.3 in FP64; 4.7 so.)
 constexpr int kShortRow = 8;
-template <typename T, bool SHORT>
+__host__ __device__ __forceinline__ bool rows_short(int ns, long nsubpix) { return (long)ns * ns >= nsubpix; }
+template <typename T>
 __global__ void __launch_bounds__(64 * kGatherW) k_lt_gather(const double* __restrict__ uv, int n2, long nsubpix,
                                                              Batch mb, int* __restrict__ ws, long I_max,
                                                              const T* __restrict__ img, T* __restrict__ s) {
@@ -371,7 +372,7 @@ __global__ void __launch_bounds__(64 * kGatherW) k_lt_gather(const double* __res
   const RowView<T> o{reinterpret_cast<const UV*>(uv) + m * nsubpix, img + (long)m * (nsubpix / n2), ns, n2,
                      ks_[wid], tw_[wid], tv_[wid]};
   const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kGatherW + wid));
-  if (!SHORT) {
+  if (!rows_short(ns, nsubpix)) {   // uniform
     if (wave >= ns * ns) return;
     const T acc = row_by_wave(o, w.keys + w.ptr[wave], w.ptr[wave + 1] - w.ptr[wave], 4 * nsubpix);
     if (lane == 0) s[mb.off[m] + wave] = acc;
@@ -753,12 +754,13 @@ static int apply_LT_ordered_impl(const double* uv, int n_members, const sl_image
     const int n = std::min(group, n_members - m0);
     Batch mb;
     int big = 0;
-    long nodes = 0;
+    unsigned rows = 0;   // blocks of k_lt_gather that the member with the most needs
     for (int i = 0; i < n; ++i) {
       mb.ns[i] = ns[m0 + i];
       mb.off[i] = off;
       off += (long)ns[m0 + i] * ns[m0 + i];
-      nodes += (long)ns[m0 + i] * ns[m0 + i];
+      rows = std::max(rows, nblocks((long)ns[m0 + i] * ns[m0 + i],
+                                    rows_short(ns[m0 + i], nsp) ? 64 * kGatherW : kGatherW));
       big = std::max(big, ns[m0 + i]);
     }
     const double* uvm = uv + (long)m0 * nsp * 2;
@@ -767,10 +769,8 @@ static int apply_LT_ordered_impl(const double* uv, int n_members, const sl_image
     launch_bins<false>(uvm, nsp, ns + m0, n, w, I_max, st);
     hipLaunchKernelGGL(k_lt_scan, dim3(n), dim3(1024), 0, st, mb, w, I_max, 4 * nsp);
     launch_bins<true>(uvm, nsp, ns + m0, n, w, I_max, st);
-    const bool rows_short = nodes >= n * nsp;   // at most four keys a row
-    hipLaunchKernelGGL((rows_short ? k_lt_gather<T, true> : k_lt_gather<T, false>),
-                       dim3(nblocks((long)big * big, rows_short ? 64 * kGatherW : kGatherW), n), dim3(64 * kGatherW), 0,
-                       st, uvm, n2, nsp, mb, w, I_max, (const T*)in + (long)m0 * J, (T*)s);
+    hipLaunchKernelGGL(k_lt_gather<T>, dim3(rows, n), dim3(64 * kGatherW), 0, st, uvm, n2, nsp, mb, w, I_max,
+                       (const T*)in + (long)m0 * J, (T*)s);
     if (int e = check_launch("ordered L^T")) return e;
   }
   return SL_OK;

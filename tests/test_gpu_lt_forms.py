@@ -92,3 +92,9 @@ def test_ordered_rows_of_every_length_on_a_sparse_grid(dtype):
     assert launches[12][0][0] * launches[12][1][0] == 64 * 144
     assert launches[100][0][0] * launches[100][1][0] < 2 * 10000
     _call(48, 1, [200], dtype, ordered=True, check=(0,))
+
+
+def test_rows_of_a_small_grid_beside_a_sparse_one():
+    """Lane or wave per row is each member's own choice: 3600 nodes (fewer than subpixels) beside 4900 and 22500."""
+    (grid, block, _) = _call(32, 2, [70, 60, 150], torch.float64, ordered=True, check=(0, 1, 2))[-1]
+    assert grid[0] * block[0] >= 64 * 3600
