@@ -822,6 +822,7 @@ static double blur_cost(int N, int nx, int ny, int n_images, int k, double* bare
     work = (double)k * ((k + 7) / 8) * 4 * (N / 4 + 1);
   }
   *bare = fit * waves <= 3 * blocks ? 1.6 : fit <= 2 ? 1.2 : 1.0;
+  if (N > 1 && blocks * n_images * kBlurT >= 2147483648.0) return HUGE_VAL;   // its grid has one dimension
   const double rounds = std::max(1.0, blocks * n_images / ((double)cus * fit));
   return rounds * (c.block + c.chain * work) + c.wave * waves * n_images * work / cus;
 }

@@ -40,3 +40,18 @@ def test_blur_form(dtype, n, ny, nx, K, tiled):
             bound = 2 * (K * K + 4) * U[dtype] * op(P, np.abs(img)) + 1e-300
             assert np.all(np.abs(got[i].double().cpu().numpy() - op(P, img)) <= bound)
             assert torch.equal(got[i], f(pt, xt[i].contiguous()))   # alone: k_blur_small, unless the image is large
+
+
+def test_more_tiles_than_one_grid_dimension():
+    """The register-tiled forms' grid has one dimension: past 2^31 threads the other form is taken (nothing runs here)."""
+    import paper_1101_5803_amd as sl
+    pt = torch.tensor(np.random.default_rng(7).uniform(0.1, 1.0, (21, 21)), device=DEV)
+    sl.apply_B(pt, torch.zeros((1, 17, 17), device=DEV))
+    blocks = []
+    for n in (4096, 8_400_000):
+        x = torch.empty((n, 17, 17), device=DEV)
+        (_, block, _), = kernel_launches(lambda: sl.apply_B(pt, x))
+        blocks.append(block)
+        del x
+    torch.cuda.empty_cache()
+    assert blocks == [(256, 1, 1), (16, 16, 1)]
