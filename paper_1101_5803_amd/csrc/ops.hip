@@ -278,7 +278,7 @@ __global__ void __launch_bounds__(1024) k_lt_scan(Batch mb, int* __restrict__ ws
 // in ascending ranges of keys that hold no more than that, a range half as wide
 // as one that held more and twice as wide after one that held less than half
 // (each range scans the row: with widths that only shrank, a row of 3001 keys in
-// one dense cluster among 4 M was scanned some 3000 times).  (With one thread per
+// one dense cluster among 4 M was scanned some 3000 times, 26.9 ms; 0.9 so).  (With one thread per
 // node sorting its segment in memory by insertion, and five launches per member,
 // a chain of operators with the ordered L^T took 81 ms for 16 members of a 128 x
 // 128 image; 0.36 ms so.)
